@@ -2,11 +2,13 @@
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libeprl.so")
-SOURCES = ["sixj.hip", "assemble.hip", "ring.hip", "wide.hip", "contract.hip", "adjoint_ring.hip", "network.hip", "boosters.hip",
+SOURCES = ["sixj.hip", "assemble.hip", "ring.hip", "chain.hip", "contract.hip", "adjoint_ring.hip", "network.hip", "boosters.hip",
            "eprl_plan.cpp", "api.cpp"]
 
 FLAGS = [
@@ -14,7 +16,6 @@ FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     # keep the compiler from emitting packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall",
@@ -25,13 +26,21 @@ FLAGS = [
 def build(verbose=False):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + ".tmp"
-    cmd = [hipcc] + FLAGS + ["-o", tmp] + [os.path.join(CSRC, s) for s in SOURCES]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libeprl.so")
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            sys.stderr.write(res.stdout + res.stderr)
+            raise RuntimeError("hipcc failed building libeprl.so")
+
+    # One compilation per source, at most eight at a time, then the link.
+    with tempfile.TemporaryDirectory() as objs, ThreadPoolExecutor(8) as pool:
+        out = [os.path.join(objs, s + ".o") for s in SOURCES]
+        list(pool.map(run, [[hipcc] + FLAGS + ["-c", "-o", o, os.path.join(CSRC, s)]
+                            for s, o in zip(SOURCES, out)]))
+        run([hipcc] + FLAGS + ["-shared", "-o", tmp] + out)
     os.replace(tmp, LIB)
     return LIB
 

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <tuple>
 #include <new>
@@ -18,6 +19,9 @@ struct BatchEntry {
   Plan plan;
   bool ring = false;
   size_t tables = 0, boff = 0, kr = 0, sched = 0, partial = 0;  // byte offsets in the workspace
+  size_t derived = 0;           // derived tables of the x-outer kernel
+  int pass = 0;                 // pass of the batch it runs in (bounds the derived tables)
+  int index = -1;               // among the factorised configurations
   int towner = -1;              // configuration whose 6j tables this one reads (itself: builds them)
   int nchunk = 0;
   int64_t chunk = 0;
@@ -29,18 +33,23 @@ struct BatchEntry {
 // enqueued directly when per-kernel timing is on.
 struct BatchSeq {
   std::vector<BatchEntry> ent;
+  std::vector<RingParams> params;  // of the factorised configurations (BatchEntry::index)
   std::vector<const double *> B;
   std::vector<double *> A;
   int nring = 0, ncu = 256;
-  // One persistent launch per group of items: a tile class and, for the 8-wide classes, one nd
-  // (their LDS, and so their occupancy, is sized for the group's nd); items [begin, end) of the
-  // work list, estimated cost (sum of item costs), work-queue counter `group index`.
+  // One launch per group of items [begin, end) of the work list, estimated cost (sum of item costs):
+  // a variant and workgroup size of the x-outer kernel within a pass, one workgroup per item; or a
+  // tile class and nd of ring.hip's kernels, persistent, work-queue counter `group index`.
   struct Group {
-    int cls, nd, begin, end;
+    bool chain;
+    int cls, nd;             // ring.hip
+    int key, waves, pass;    // x-outer
+    size_t smem;
+    int begin, end;
     double cost;
-    int xoff;  // wide class: index (in ints, from items_off) of its nine per-XCD list offsets
   };
   std::vector<Group> groups;
+  int npass = 1;
   size_t params_off = 0, items_off = 0, counters_off = 0;
 };
 
@@ -294,6 +303,8 @@ int plan_for(eprl_ctx *c, const int two_j[10], int dl, const Plan **out) {
 // workgroups on 256 CUs, so that cost-balanced chunks finish together.  A batch uses the same
 // schedule per configuration, which keeps its tensors bitwise equal to those of plain calls.
 constexpr int kRingTargetWG = 8192;
+constexpr int kChainTargetWG = 8192;
+int default_target(const Plan &p) { return p.chain ? kChainTargetWG : kRingTargetWG; }
 
 struct Prepared {
   Plan plan;
@@ -305,10 +316,12 @@ struct Prepared {
 };
 
 // Plan, size the workspace (tables + metadata + `extra` bytes), upload metadata (and `sched`,
-// if given) and build the 6j tables.  `extra` is placed at `prep.tail`.
+// if given) and build the 6j tables.  `extra` is placed at `prep.tail`; its first `more` bytes are
+// uploaded too, as `fill` writes them once the addresses are known.
 int prepare(eprl_ctx *c, const int two_j[10], int dl, size_t extra, Prepared &prep,
             bool ring_tables = false, const std::vector<int> *sched = nullptr,
-            const Plan *known = nullptr, bool any_dims = false) {
+            const Plan *known = nullptr, bool any_dims = false, size_t more = 0,
+            const std::function<void(Prepared &, char *)> &fill = nullptr) {
   int rc = EPRL_OK;
   if (known)
     prep.plan = *known;
@@ -332,12 +345,13 @@ int prepare(eprl_ctx *c, const int two_j[10], int dl, size_t extra, Prepared &pr
   prep.sched = sched ? reinterpret_cast<int *>(c->ws + tbytes + bbytes + kbytes) : nullptr;
   prep.tail = c->ws + tbytes + bbytes + kbytes + sbytes;
   char *st;
-  rc = staging(c, bbytes + kbytes + sbytes, &st);
+  rc = staging(c, bbytes + kbytes + sbytes + more, &st);
   if (rc) return rc;
   std::memcpy(st, p.boff.data(), p.boff.size() * sizeof(int64_t));
   std::memcpy(st + bbytes, p.kr.data(), p.kr.size() * sizeof(int));
   if (sched) std::memcpy(st + bbytes + kbytes, sched->data(), sched->size() * sizeof(int));
-  rc = upload(c, prep.boff, bbytes + kbytes + sbytes);
+  if (fill) fill(prep, st + bbytes + kbytes + sbytes);
+  rc = upload(c, prep.boff, bbytes + kbytes + sbytes + more);
   if (rc) return rc;
   TableParams tp;
   std::memcpy(tp.two_j, p.two_j, sizeof(tp.two_j));
@@ -440,9 +454,49 @@ RingParams ring_params(const Prepared &prep, const double *B) {
   rp.B = B;
   rp.boff = prep.boff;
   rp.kr = prep.kr;
-  rp.kw = p.ring_kw;
   rp.nrb = ring_row_blocks(p);
   return rp;
+}
+
+size_t chain_derived_bytes(const Plan &p) {
+  return (size_t)(p.ch.t5 + p.ch.t2 + p.ch.m4 + p.ch.m3 + p.ch.steps) * sizeof(double);
+}
+
+// x-outer evaluation over the cores [core_lo, core_hi) (core_hi < 0: all cores): the derived tables,
+// one workgroup per (chunk, i1, row block), then the reduction.
+int chain_impl(eprl_ctx *c, const int two_j[10], int dl, const double *B, int accumulate, double *A,
+               const Plan &p, int nchunk, int core_lo, int core_hi) {
+  const size_t rbytes = align_up(sizeof(RingParams), 256), dbytes = align_up(chain_derived_bytes(p), 256);
+  const size_t pbytes = align_up((size_t)nchunk * p.a_size * sizeof(double), 256);
+  Prepared prep;
+  RingParams rp;
+  auto fill = [&](Prepared &pr, char *st) {
+    rp = ring_params(pr, B);
+    chain_params(p, reinterpret_cast<double *>(pr.tail + rbytes), rp);
+    rp.partial = reinterpret_cast<double *>(pr.tail + rbytes + dbytes);
+    rp.bounds = pr.sched;
+    rp.nchunk = nchunk;
+    if (core_hi >= 0) {
+      rp.core_lo = core_lo;
+      rp.core_hi = core_hi;
+    }
+    std::memcpy(st, &rp, sizeof(rp));
+  };
+  int rc = prepare(c, two_j, dl, rbytes + dbytes + pbytes, prep, true, &c->sched_bounds, &p, false, rbytes, fill);
+  if (rc) return rc;
+  {
+    TimedLaunch tl(c, 0);
+    HIP_TRY(c, launch_chain_prep(rp, c->stream));
+  }
+  {
+    TimedLaunch tl(c, 4);
+    HIP_TRY(c, launch_chain(reinterpret_cast<const RingParams *>(prep.tail), nullptr, nchunk * p.i[0].n * p.ch.nrb,
+                            p.ch.key, p.ch.waves, chain_smem_bytes(p), c->stream));
+  }
+  ReduceParams red = reduce_params(p, rp.partial, nchunk, A, accumulate);
+  TimedLaunch tl(c, 2);
+  HIP_TRY(c, launch_reduce(red, c->stream));
+  return EPRL_OK;
 }
 
 // Factorised evaluation over the cores [core_lo, core_hi) (core_hi < 0: all cores), every
@@ -450,37 +504,35 @@ RingParams ring_params(const Prepared &prep, const double *B) {
 int ring_impl(eprl_ctx *c, const int two_j[10], int dl, const double *B, int accumulate,
               double *A, const Plan &probe, int core_lo = 0, int core_hi = -1) {
   const int cls = probe.ring_cls;
-  const int target = c->tune_wg[cls] > 0 ? c->tune_wg[cls] : kRingTargetWG;
+  const int target = c->tune_wg[cls] > 0 ? c->tune_wg[cls] : default_target(probe);
   std::vector<int> key(two_j, two_j + 10);
   key.push_back(dl);
   key.push_back(target);
   key.push_back(cls);
+  key.push_back(probe.chain);
   key.push_back(core_lo);
   key.push_back(core_hi);
   if (key != c->sched_key) {
-    c->sched_nchunk = ring_schedule(probe, target, c->sched_bounds, nullptr, core_lo, core_hi);
+    c->sched_key.clear();
+    c->sched_nchunk = probe.chain ? chain_schedule(probe, target, c->sched_bounds, nullptr, core_lo, core_hi)
+                                  : ring_schedule(probe, target, c->sched_bounds, nullptr, core_lo, core_hi);
     c->sched_key = key;
   }
   const std::vector<int> &bounds = c->sched_bounds;
   const int nchunk = c->sched_nchunk;
+  if (probe.chain) return chain_impl(c, two_j, dl, B, accumulate, A, probe, nchunk, core_lo, core_hi);
   const size_t pbytes = align_up((size_t)nchunk * probe.a_size * sizeof(double), 256);
   Prepared prep;
-  // Partial sums, then the eight work-queue counters of the persistent wide kernel.
-  int rc = prepare(c, two_j, dl, pbytes + 256, prep, true, &bounds, &probe);
+  int rc = prepare(c, two_j, dl, pbytes, prep, true, &bounds, &probe);
   if (rc) return rc;
   const Plan &p = prep.plan;
   RingParams rp = ring_params(prep, B);
   rp.partial = reinterpret_cast<double *>(prep.tail);
   rp.bounds = prep.sched;
   rp.nchunk = nchunk;
-  rp.kw = p.ring_kw;
-  rp.nrb = ring_row_blocks(p);
   {
     TimedLaunch tl(c, 4);
-    if (p.ring_cls == kWideClass)
-      HIP_TRY(c, launch_wide(rp, reinterpret_cast<int *>(prep.tail + pbytes), c->ncu, c->stream));
-    else
-      HIP_TRY(c, launch_ring(rp, p.ring_cls, c->tune_stg[p.ring_cls], c->stream));
+    HIP_TRY(c, launch_ring(rp, p.ring_cls, c->tune_stg[p.ring_cls], c->stream));
   }
   ReduceParams red = reduce_params(p, rp.partial, nchunk, A, accumulate);
   {
@@ -510,9 +562,10 @@ int vertex_range_impl(eprl_ctx *c, const int two_j[10], int dl, double gamma, co
                 "the factorised path needs the full shell range, i and k ranges <= 16 and core "
                 "windows <= 32");
   if (full && c->algo != EPRL_ALGO_SHELL && probe.ring_KW != 0) {
-    if (c->algo == EPRL_ALGO_RING_VALU && probe.ring_cls != probe.ring_cls8) {
+    if (c->algo == EPRL_ALGO_RING_VALU && probe.chain) {
       Plan q = probe;
       q.ring_cls = q.ring_cls8;
+      q.chain = false;
       return ring_impl(c, two_j, dl, B, accumulate, A, q);
     }
     return ring_impl(c, two_j, dl, B, accumulate, A, probe);
@@ -571,9 +624,10 @@ int vertex_cores_impl(eprl_ctx *c, const int two_j[10], int dl, double gamma, co
   if (probe.ring_KW == 0)
     return fail(c, EPRL_ERANGE,
                 "the factorised path needs i and k ranges <= 16 and core windows <= 32");
-  if (c->algo == EPRL_ALGO_RING_VALU && probe.ring_cls != probe.ring_cls8) {
+  if (c->algo == EPRL_ALGO_RING_VALU && probe.chain) {
     Plan q = probe;
     q.ring_cls = q.ring_cls8;
+    q.chain = false;
     return ring_impl(c, two_j, dl, B, accumulate, A, q, (int)cb, (int)ce);
   }
   return ring_impl(c, two_j, dl, B, accumulate, A, probe, (int)cb, (int)ce);
@@ -655,10 +709,14 @@ void booster_r_nodes(int n, const std::vector<double> (&gx)[2], const std::vecto
 // tensor is bitwise identical to a separate eprl_vertex_tensor call.
 
 
+// Most memory the derived tables of a batch's x-outer configurations take at a time.
+constexpr size_t kDerivedBytes = size_t(24) << 30;
+
 int batch_chunks(const Plan &p, bool ring, int target_wg, int &nchunk, int64_t &chunk,
                  std::vector<int> &bounds, std::vector<double> &ccost) {
   if (ring) {
-    nchunk = ring_schedule(p, target_wg > 0 ? target_wg : kRingTargetWG, bounds, &ccost);
+    const int target = target_wg > 0 ? target_wg : default_target(p);
+    nchunk = p.chain ? chain_schedule(p, target, bounds, &ccost) : ring_schedule(p, target, bounds, &ccost);
     chunk = 0;
   } else {
     const int target_wg = p.D == 8 ? 4096 : 1024;
@@ -709,65 +767,59 @@ hipError_t enqueue_batch(eprl_ctx *c) {
   }
   int *counters = reinterpret_cast<int *>(ws + seq.counters_off);
   const int ngroup = (int)seq.groups.size();
-  if (e == hipSuccess && ngroup > 0) e = launch_reset_counters(counters, 8 * ngroup, c->stream);
-  // Inside a capture the groups run on up to 1 + kBatchSide streams (graph branches), the
-  // costliest group first, each on the stream with the least work so far; outside a capture
-  // (timed launches) they run one after the other on the context's stream.
+  if (e == hipSuccess && ngroup > 0) e = launch_reset_counters(counters, ngroup, c->stream);
+  const RingParams *params = reinterpret_cast<const RingParams *>(ws + seq.params_off);
   hipStream_t main = c->stream;
-  const int nstream = c->capturing ? std::min(ngroup, 1 + kBatchSide) : 1;
-  std::vector<hipStream_t> streams(std::max(nstream, 1), main);
-  if (e == hipSuccess && nstream > 1) {
-    e = hipEventRecord(c->batch.fork, main);
+  for (int pass = 0; pass < seq.npass && e == hipSuccess; ++pass) {
+    for (int q = 0; q < n && e == hipSuccess; ++q) {
+      const BatchEntry &b = seq.ent[q];
+      if (!b.ring || !b.plan.chain || b.pass != pass) continue;
+      TimedLaunch tl(c, 0);
+      e = launch_chain_prep(seq.params[b.index], c->stream);
+    }
+    // Inside a capture the groups run on up to 1 + kBatchSide streams (graph branches), the
+    // costliest group first, each on the stream with the least work so far; outside a capture
+    // (timed launches) they run one after the other on the context's stream.
+    std::vector<int> order;
+    for (int g = 0; g < ngroup; ++g)
+      if (seq.groups[g].pass == pass) order.push_back(g);
+    const int nstream = c->capturing ? std::min((int)order.size(), 1 + kBatchSide) : 1;
+    std::vector<hipStream_t> streams(std::max(nstream, 1), main);
+    if (e == hipSuccess && nstream > 1) {
+      e = hipEventRecord(c->batch.fork, main);
+      for (int q = 1; q < nstream && e == hipSuccess; ++q) {
+        streams[q] = c->batch.side[q - 1];
+        e = hipStreamWaitEvent(streams[q], c->batch.fork, 0);
+      }
+    }
+    std::vector<double> load(streams.size(), 0.0);
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int a, int b) { return seq.groups[a].cost > seq.groups[b].cost; });
+    for (size_t oi = 0; oi < order.size() && e == hipSuccess; ++oi) {
+      const int g = order[oi];
+      const BatchSeq::Group &gr = seq.groups[g];
+      const int cls = gr.cls, nit = gr.end - gr.begin;
+      const int si = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+      load[si] += gr.cost;
+      c->stream = streams[si];
+      const int *items = reinterpret_cast<const int *>(ws + seq.items_off) + 4 * gr.begin;
+      if (gr.chain) {
+        TimedLaunch tl(c, 6);
+        e = launch_chain(params, items, nit, gr.key, gr.waves, gr.smem, c->stream);
+      } else {
+        // Enough workgroups to fill the chip at the occupancy the group's LDS allows.
+        const size_t shm = ring_smem_bytes(cls, gr.nd, c->tune_stg[cls]);
+        const int per_cu = std::max(1, std::min(8, (int)(160 * 1024 / std::max<size_t>(shm, 1))));
+        const int grid = (int)std::min<int>(nit, seq.ncu * per_cu);
+        TimedLaunch tl(c, 6);
+        e = launch_ring_batch(params, items, nit, cls, gr.nd, c->tune_stg[cls], grid, counters + g, c->stream);
+      }
+    }
+    c->stream = main;
     for (int q = 1; q < nstream && e == hipSuccess; ++q) {
-      streams[q] = c->batch.side[q - 1];
-      e = hipStreamWaitEvent(streams[q], c->batch.fork, 0);
+      e = hipEventRecord(c->batch.join[q - 1], streams[q]);
+      if (e == hipSuccess) e = hipStreamWaitEvent(main, c->batch.join[q - 1], 0);
     }
-  }
-  std::vector<double> load(streams.size(), 0.0);
-  std::vector<int> order(ngroup);
-  for (int g = 0; g < ngroup; ++g) order[g] = g;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int a, int b) { return seq.groups[a].cost > seq.groups[b].cost; });
-  for (int oi = 0; oi < ngroup && e == hipSuccess; ++oi) {
-    const int g = order[oi];
-    const BatchSeq::Group &gr = seq.groups[g];
-    const int cls = gr.cls, nit = gr.end - gr.begin;
-    const int si = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-    load[si] += gr.cost;
-    c->stream = streams[si];
-    const int *items = reinterpret_cast<const int *>(ws + seq.items_off) + 4 * gr.begin;
-    const RingParams *params = reinterpret_cast<const RingParams *>(ws + seq.params_off);
-    if (cls == kWideClass) {
-      // One 8-wavefront workgroup per CU, LDS sized for the largest configuration of the class;
-      // booster blocks staged when every configuration's fit.
-      size_t shm = 0, shm_stg = 0;
-      bool stg = true;
-      for (const BatchEntry &b : seq.ent)
-        if (b.ring && b.plan.ring_cls == kWideClass) {
-          int dims[5];
-          for (int q = 0; q < 5; ++q) dims[q] = b.plan.i[q].n;
-          shm = std::max(shm, wide_smem_bytes(b.plan.nd, dims, b.plan.ring_kw, b.plan.ring_nrb, false));
-          shm_stg = std::max(shm_stg, wide_smem_bytes(b.plan.nd, dims, b.plan.ring_kw, b.plan.ring_nrb, true));
-          stg = stg && wide_fits(b.plan.nd, dims, b.plan.ring_kw, b.plan.ring_nrb, true);
-        }
-      TimedLaunch tl(c, 6);
-      const int *xoff = reinterpret_cast<const int *>(ws + seq.items_off) + gr.xoff;
-      e = launch_wide_batch(params, items, xoff, nit, stg ? shm_stg : shm, stg,
-                            std::min(nit, seq.ncu), counters + 8 * g, c->stream);
-    } else {
-      // Enough workgroups to fill the chip at the occupancy the group's LDS allows.
-      const size_t shm = ring_smem_bytes(cls, gr.nd, c->tune_stg[cls]);
-      const int per_cu = std::max(1, std::min(8, (int)(160 * 1024 / std::max<size_t>(shm, 1))));
-      const int grid = (int)std::min<int>(nit, seq.ncu * per_cu);
-      TimedLaunch tl(c, 6);
-      e = launch_ring_batch(params, items, nit, cls, gr.nd, c->tune_stg[cls], grid, counters + 8 * g,
-                            c->stream);
-    }
-  }
-  c->stream = main;
-  for (int q = 1; q < nstream && e == hipSuccess; ++q) {
-    e = hipEventRecord(c->batch.join[q - 1], streams[q]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(main, c->batch.join[q - 1], 0);
   }
   for (int q = 0; q < n && e == hipSuccess; ++q) {
     const BatchEntry &b = seq.ent[q];
@@ -862,7 +914,10 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     b.ring = c->algo != EPRL_ALGO_SHELL && p.ring_KW != 0;
     if ((c->algo == EPRL_ALGO_RING || c->algo == EPRL_ALGO_RING_VALU) && !b.ring)
       return fail(c, EPRL_ERANGE, "the factorised path does not apply to every configuration");
-    if (c->algo == EPRL_ALGO_RING_VALU) b.plan.ring_cls = b.plan.ring_cls8;
+    if (c->algo == EPRL_ALGO_RING_VALU) {
+      b.plan.ring_cls = b.plan.ring_cls8;
+      b.plan.chain = false;
+    }
     batch_chunks(p, b.ring, p.ring_cls >= 0 ? c->tune_wg[p.ring_cls] : 0, b.nchunk, b.chunk,
                  b.bounds, b.ccost);
     fact_max = std::max(fact_max, p.fact_max);
@@ -904,19 +959,38 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     double cost;
     int cfg, chunk, n1, rb;
   };
-  // Groups: (tile class, nd) for the 8-wide classes, the whole wide class as one.
-  std::map<std::pair<int, int>, std::vector<Item>> grouped;
+  // Derived tables of the x-outer kernel: as many configurations at a time (a pass) as keep them
+  // within kDerivedBytes; the passes run one after the other on the same memory.
+  size_t dmax = 0, dsum = 0;
+  int npass = 1;
+  for (int q = 0; q < n; ++q) {
+    if (!ent[q].ring || !ent[q].plan.chain) continue;
+    const size_t need = align_up(chain_derived_bytes(ent[q].plan), 256);
+    if (dsum > 0 && dsum + need > kDerivedBytes) {
+      ++npass;
+      dsum = 0;
+    }
+    ent[q].pass = npass - 1;
+    ent[q].derived = off + dsum;
+    dsum += need;
+    dmax = std::max(dmax, dsum);
+  }
+  off += dmax;
+  // Groups of items that one launch can take.
+  std::map<std::tuple<int, int, int, int>, std::vector<Item>> grouped;
   std::vector<int> ring_index(n, -1);
   int nring = 0;
   for (int q = 0; q < n; ++q) {
     if (!ent[q].ring) continue;
-    ring_index[q] = nring++;
-    // Cost of an item: the chunk's x iterations (from the schedule) times the size of the
-    // A(i1) slice, which sets the work of the final contraction of each iteration.
+    ent[q].index = ring_index[q] = nring++;
+    // Cost of an item: for the x-outer kernel its matrix-core steps (from the schedule), else the
+    // chunk's x iterations times the size of the A(i1) slice, which sets the work of the final
+    // contraction of each iteration.
     const Plan &p = ent[q].plan;
-    const double slice = (double)p.i[1].n * p.i[2].n * p.i[3].n * p.i[4].n;
+    const double slice = p.chain ? 1.0 : (double)p.i[1].n * p.i[2].n * p.i[3].n * p.i[4].n;
     const int cls = p.ring_cls, nrb = ring_row_blocks(p), nch = ent[q].nchunk;
-    std::vector<Item> &dst = grouped[{cls, cls == kWideClass ? 0 : p.nd}];
+    std::vector<Item> &dst = p.chain ? grouped[std::make_tuple(1, ent[q].pass, p.ch.key, p.ch.waves)]
+                                     : grouped[std::make_tuple(0, 0, cls, p.nd)];
     for (int ch = 0; ch < nch; ++ch)
       for (int n1 = 0; n1 < p.i[0].n; ++n1) {
         const double cost = ent[q].ccost[(size_t)n1 * nch + ch] * slice;
@@ -925,57 +999,33 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
   }
   std::vector<Item> items;
   std::vector<BatchSeq::Group> groups;
-  std::vector<int> xoffs;  // per wide group: nine per-XCD list offsets
   for (auto &kv : grouped) {
     std::vector<Item> &v = kv.second;
-    BatchSeq::Group g{kv.first.first, kv.first.second, (int)items.size(), 0, 0.0, -1};
-    for (const Item &it : v) g.cost += it.cost;
-    if (g.cls != kWideClass) {
-      std::stable_sort(v.begin(), v.end(), [](const Item &a, const Item &b) { return a.cost > b.cost; });
-      items.insert(items.end(), v.begin(), v.end());
-    } else {
-      // Chunks (configuration, chunk, row block) with all their i1 items, longest first, each to
-      // the XCD list with the least work so far; in a list the chunks keep that order and the
-      // items of a chunk stay together (longest first).
-      std::map<std::tuple<int, int, int>, std::vector<Item>> chunks;
-      for (const Item &it : v) chunks[std::make_tuple(it.cfg, it.chunk, it.rb)].push_back(it);
-      std::vector<std::pair<double, std::vector<Item> *>> order;
-      for (auto &ck : chunks) {
-        double cost = 0.0;
-        for (const Item &it : ck.second) cost += it.cost;
-        std::stable_sort(ck.second.begin(), ck.second.end(),
-                         [](const Item &a, const Item &b) { return a.cost > b.cost; });
-        order.push_back({cost, &ck.second});
-      }
-      std::stable_sort(order.begin(), order.end(),
-                       [](const std::pair<double, std::vector<Item> *> &a,
-                          const std::pair<double, std::vector<Item> *> &b) { return a.first > b.first; });
-      std::vector<Item> lists[8];
-      double load[8] = {0.0};
-      for (auto &o : order) {
-        const int x = (int)(std::min_element(load, load + 8) - load);
-        load[x] += o.first;
-        lists[x].insert(lists[x].end(), o.second->begin(), o.second->end());
-      }
-      g.xoff = (int)xoffs.size();
-      for (int x = 0; x < 8; ++x) {
-        xoffs.push_back((int)(items.size() - g.begin));
-        items.insert(items.end(), lists[x].begin(), lists[x].end());
-      }
-      xoffs.push_back((int)(items.size() - g.begin));
-    }
+    BatchSeq::Group g;
+    g.chain = std::get<0>(kv.first) == 1;
+    g.pass = std::get<1>(kv.first);
+    g.key = g.cls = std::get<2>(kv.first);
+    g.waves = g.nd = std::get<3>(kv.first);
+    g.smem = 0;
+    g.begin = (int)items.size();
+    g.cost = 0.0;
+    for (const Item &it : v) g.cost += it.cost * (g.chain ? g.waves : 1);
+    if (g.chain)
+      for (int q = 0; q < n; ++q)
+        if (ent[q].ring && ent[q].plan.chain && ent[q].pass == g.pass && ent[q].plan.ch.key == g.key &&
+            ent[q].plan.ch.waves == g.waves)
+          g.smem = std::max(g.smem, chain_smem_bytes(ent[q].plan));
+    std::stable_sort(v.begin(), v.end(), [](const Item &a, const Item &b) { return a.cost > b.cost; });
+    items.insert(items.end(), v.begin(), v.end());
     g.end = (int)items.size();
     groups.push_back(g);
   }
-  // The per-XCD offsets follow the items in the same device array.
-  for (BatchSeq::Group &g : groups)
-    if (g.xoff >= 0) g.xoff += 4 * (int)items.size();
   const size_t params_off = off;
   off += align_up((size_t)std::max(nring, 1) * sizeof(RingParams), 256);
   const size_t items_off = off;
-  off += align_up((std::max<size_t>(items.size(), 1) * 4 + xoffs.size()) * sizeof(int), 256);
-  const size_t counters_off = off;  // eight work-queue counters per group
-  off += align_up(std::max<size_t>(groups.size(), 1) * 8 * sizeof(int), 256);
+  off += align_up(std::max<size_t>(items.size(), 1) * 4 * sizeof(int), 256);
+  const size_t counters_off = off;  // one work-queue counter per group
+  off += align_up(std::max<size_t>(groups.size(), 1) * sizeof(int), 256);
   int rc = ensure_fexp(c, fact_max);
   if (rc) return rc;
   // Drop the previous graph and workspace.
@@ -1028,8 +1078,8 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     rp.partial = reinterpret_cast<double *>(ws + ent[q].partial);
     rp.bounds = reinterpret_cast<const int *>(ws + ent[q].sched);
     rp.nchunk = ent[q].nchunk;
-    rp.kw = p.ring_kw;
     rp.nrb = ring_row_blocks(p);
+    if (p.chain) chain_params(p, reinterpret_cast<double *>(ws + ent[q].derived), rp);
   }
   // Compact staging of the metadata blocks: (workspace offset, bytes) in staging order.
   std::vector<std::pair<size_t, size_t>> blocks;
@@ -1055,14 +1105,13 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
       so += ent[q].partial - ent[q].boff;
     }
     std::memcpy(st + so, params.data(), params.size() * sizeof(RingParams));
-    std::vector<int> flat(std::max<size_t>(items.size(), 1) * 4 + xoffs.size(), 0);
+    std::vector<int> flat(std::max<size_t>(items.size(), 1) * 4, 0);
     for (size_t k = 0; k < items.size(); ++k) {
       flat[4 * k] = items[k].cfg;
       flat[4 * k + 1] = items[k].chunk;
       flat[4 * k + 2] = items[k].n1;
       flat[4 * k + 3] = items[k].rb;
     }
-    std::copy(xoffs.begin(), xoffs.end(), flat.begin() + 4 * items.size());
     std::memcpy(st + so + (items_off - params_off), flat.data(), flat.size() * sizeof(int));
     so = 0;
     for (auto &b : blocks) {
@@ -1077,6 +1126,8 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
   seq.ent = std::move(ent);
   seq.B.assign(boosters, boosters + n);
   seq.A.assign(A, A + n);
+  seq.params = std::move(params);
+  seq.npass = npass;
   seq.nring = nring;
   seq.groups = std::move(groups);
   seq.params_off = params_off;
@@ -1222,7 +1273,7 @@ int eprl_autotune(eprl_ctx *c, const int two_j[10], int dl, const double *B, dou
     return hip_fail(c, hipGetLastError(), "hipEventCreate");
   }
   float best = 0.0f;
-  int best_wg = kRingTargetWG, best_stg = -1;
+  int best_wg = default_target(p), best_stg = -1;
   for (int li = 0; li < nl && rc == EPRL_OK; ++li) {
     for (int t : kTargets) {
       c->tune_wg[cls] = t;

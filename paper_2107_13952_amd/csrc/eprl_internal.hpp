@@ -20,6 +20,22 @@ struct Range {
 // Link indices in the order (12, 13, 14, 15, 23, 24, 25, 34, 35, 45).
 enum Link { L12 = 0, L13, L14, L15, L23, L24, L25, L34, L35, L45 };
 
+// Shape of the x-outer factorised kernel (chain.hip) for one configuration.
+struct ChainGeom {
+  int n4t = 0, n3t = 0;   // k4 (k3) values per l45 (l23) of its derived tables
+  int ts = 0;             // entries of a row of those tables (i5 or i2, padded)
+  int wm = 0, smax = 0;   // widest k4 or k3 window: positions, steps of four
+  int tpre = 0, tpost = 0;  // zero rows before and after the T rows in LDS
+  int ct = 0;             // column tiles of A(i1)
+  int nrb = 1, rtb = 1;   // row blocks, row tiles per block
+  int waves = 1;          // wavefronts per workgroup
+  int rt = 1;             // row tiles per wavefront
+  int lds = 0;            // LDS of a workgroup, in doubles
+  int mr4 = 0, mr3 = 0;   // entries of a row of M4, M3
+  int key = 0;            // kernel variant
+  int64_t t5 = 0, t2 = 0, m4 = 0, m3 = 0, steps = 0;  // derived tables, in doubles
+};
+
 // Everything the kernels need to know about one configuration (two_j, dl); built on the host.
 struct Plan {
   int two_j[10];
@@ -45,10 +61,9 @@ struct Plan {
   int ring_KW = 0;            // 16 or 32 when the ring path applies, else 0
   int ring_DI = 0, ring_DK = 0;  // padded boundary / virtual intertwiner tile sizes (8 or 16)
   int ring_cls = -1;          // tile class of the ring kernel, -1 when it does not apply
-  // Wide (all-matrix-core) kernel, tile class kWideClass: k windows padded to a multiple of 4
-  // and the number of row blocks of A(i1) per work item.
-  int ring_kw = 0, ring_nrb = 1;
   int ring_cls8 = -1;         // class among 0..7 (half chains on vector ALUs), -1 when none
+  bool chain = false;         // evaluated by the x-outer kernel
+  ChainGeom ch;
 };
 
 // Largest 6j argument (two-units) the device evaluation is built for: up to it the alternating
@@ -95,6 +110,13 @@ struct VertexParams {
   int nchunk;
 };
 
+// One step of the x-outer kernel, (l24, x, l35; l34): sizes of the k4 and k3 windows, offsets of
+// the windows' starts in U3, M4, M3 and in the T rows (of k = 0's row), whether the unit has more.
+struct alignas(32) ChainStep {
+  int n4, n3, u3, m4, m3, t5, t2;
+  short o34, more;
+};
+
 struct RingParams {
   int two_j[10];
   int nd;
@@ -113,7 +135,14 @@ struct RingParams {
   double *partial;        // [nchunk][i1][i2][i3][i4][i5]
   const int *bounds;      // [i1][nchunk + 1]: first core of each chunk of that i1
   int nchunk;
-  int kw, nrb;            // wide kernel: padded k window, row blocks of A(i1)
+  int nrb;                // row blocks of A(i1)
+  // x-outer kernel: derived tables and their shape (ChainGeom), own x count, own windows of k3
+  // (0) and k4 (1), range of cores; bounds then holds units (l24, l25, x, l35).
+  double *T5, *T2, *M4, *M3;
+  ChainStep *steps;
+  int n4t, n3t, ts, wm, smax, tpre, tpost, rtb, nx, lds, mr4, mr3;
+  int wlo[2], whi[2];
+  int core_lo, core_hi;
 };
 
 struct ReduceParams {
@@ -135,26 +164,26 @@ hipError_t launch_sixj_batch(const int *args, int n, double *out, const uint16_t
 hipError_t launch_assemble(const VertexParams &vp, int D, hipStream_t s);
 hipError_t launch_reduce(const ReduceParams &rp, hipStream_t s);
 int ring_class(int DI, int DK, int KW);
-// Tile classes: 0..7 the 8/16-wide kernels of ring.hip, kWideClass the all-matrix-core kernel of
-// wide.hip (boundary dimensions above 8).
+// Tile classes: 0..7 by the padded tiles of ring.hip's kernels, kWideClass a boundary dimension
+// above 8 in the x-outer kernel of chain.hip (which also runs classes 0..3).
 constexpr int kWideClass = 8;
 constexpr int kRingClasses = 9;
-// Largest dl + 1 the wide kernel takes (its per-spin tiles must fit in LDS beside G and H).
-constexpr int kWideMaxNd = 11;
-// LDS bytes of the wide kernel; stg: with the core's booster blocks staged.
-size_t wide_smem_bytes(int nd, const int i_n[5], int kw, int nrb, bool stg);
-// Row blocks of A(i1) per work item so that each wavefront holds at most 12 accumulator tiles
-// (0 when even one row tile needs more).
-int wide_row_blocks(const int i_n[5]);
-bool wide_fits(int nd, const int i_n[5], int kw, int nrb, bool stg = false);
-hipError_t wide_init_attributes();
-// Plain call, persistent (one workgroup per CU, ncu of them at most); next: eight device ints
-// of scratch for the per-XCD counters (reset by the launch).
-hipError_t launch_wide(const RingParams &rp, int *next, int ncu, hipStream_t s);
-// Persistent launch over per-XCD item lists: list x is items [xoff[x], xoff[x + 1]) of
-// items_dev (offsets relative to items_dev, device memory), next[0..7] its counters (zeroed).
-hipError_t launch_wide_batch(const RingParams *cfgs_dev, const int *items_dev, const int *xoff_dev,
-                             int nitems, size_t smem, bool stg, int grid, int *next, hipStream_t s);
+// x-outer factorised kernel (chain.hip).  chain_plan sets p.chain and p.ch (false when the
+// configuration's windows or tiles do not fit); derived tables of p.ch.t5 + t2 + m4 + m3 doubles.
+constexpr size_t kChainMaxLds = 160 * 1024 - 256;
+bool chain_plan(Plan &p);
+size_t chain_smem_bytes(const Plan &p);
+hipError_t chain_init_attributes();
+void chain_params(const Plan &p, double *derived, RingParams &rp);
+hipError_t launch_chain_prep(const RingParams &rp, hipStream_t s);
+// items: (configuration, chunk, i1, row block) in device memory, or null for every item of
+// configuration 0; waves: wavefronts per workgroup (the largest rtb of the items).
+hipError_t launch_chain(const RingParams *cfgs_dev, const int *items_dev, int nitems, int key, int waves,
+                        size_t smem, hipStream_t s);
+// Chunks of units (l24, l25, x, l35) of equal estimated cost for each i1, as ring_schedule does
+// with cores.
+int chain_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
+                   std::vector<double> *chunk_cost = nullptr, int core_lo = 0, int core_hi = -1);
 // Splits the cores of the factorised path, for each i1, into chunks of equal estimated cost
 // (x iterations plus the per-core set-up), about target_wg workgroups in all and at most
 // kRingMaxPartialBytes of partial sums; fills bounds ([i1][nchunk + 1]) and, if asked for, the

@@ -174,6 +174,7 @@ int make_plan(const int two_j[10], int dl, Plan &p, std::string &err) {
   p.tsize[4] = nd * nK2 * n1 * NX;
   p.toff[0] = 0;
   for (int t = 0; t < 5; ++t) p.toff[t + 1] = p.toff[t] + ((p.tsize[t] + 31) / 32) * 32;
+  p.toff[5] += 128;  // zeros: operand reads of the x-outer kernel run past a table's end
   p.a_size = 1;
   for (int e = 0; e < 5; ++e) p.a_size *= p.i[e].n;
   // Widest core windows of the factorised path.
@@ -210,13 +211,9 @@ int make_plan(const int two_j[10], int dl, Plan &p, std::string &err) {
   if (p.ring_DI == 0 || p.ring_DK == 0 || p.ring_KW == 0 || nd > kRingMaxNd) p.ring_KW = 0;
   p.ring_cls = p.ring_KW ? ring_class(p.ring_DI, p.ring_DK, p.ring_KW) : -1;
   p.ring_cls8 = p.ring_cls;
-  // Boundary dimensions above 8: the all-matrix-core kernel, when its tiles fit in LDS.
-  int dims[5];
-  for (int e = 0; e < 5; ++e) dims[e] = p.i[e].n;
-  p.ring_kw = (w + 3) / 4 * 4;
-  p.ring_nrb = wide_row_blocks(dims);
-  if (p.ring_cls >= 4 && nd <= kWideMaxNd && wide_fits(nd, dims, p.ring_kw, p.ring_nrb))
-    p.ring_cls = kWideClass;
+  // The x-outer kernel for every class whose tiles fit, except the 16-wide ones with all boundary
+  // dimensions at most 8 that ring_DI already tells apart; boundary dimensions above 8 are class 8.
+  if (p.ring_cls >= 0 && chain_plan(p) && p.ring_cls >= 4) p.ring_cls = kWideClass;
   return EPRL_OK;
 }
 
@@ -277,18 +274,8 @@ int ring_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
   }
   bounds.assign((size_t)d1 * (nchunk + 1), 0);
   if (chunk_cost) chunk_cost->assign((size_t)d1 * nchunk, 0.0);
-  // The wide kernel splits the cores the same way for every i1 (by the cost summed over i1):
-  // the work items of one chunk then read the same 6j table slices and booster blocks, which
-  // the XCD-aware launch order keeps in one L2.
-  const bool shared = p.ring_cls == kWideClass;
-  std::vector<double> sum_cost;
-  if (shared) {
-    sum_cost.assign(ncore, 0.0);
-    for (int n1 = 0; n1 < d1; ++n1)
-      for (int k = core_lo; k < core_hi; ++k) sum_cost[k] += cost[(size_t)n1 * ncore + k];
-  }
   for (int n1 = 0; n1 < d1; ++n1) {
-    const double *cs = shared ? sum_cost.data() : cost.data() + (size_t)n1 * ncore;
+    const double *cs = cost.data() + (size_t)n1 * ncore;
     double total = 0.0;
     for (int k = core_lo; k < core_hi; ++k) total += cs[k];
     int *bd = bounds.data() + (size_t)n1 * (nchunk + 1);
@@ -305,6 +292,77 @@ int ring_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
       for (int ch = 0; ch < nchunk; ++ch)
         for (int q = bd[ch]; q < bd[ch + 1]; ++q)
           (*chunk_cost)[(size_t)n1 * nchunk + ch] += cost[(size_t)n1 * ncore + q];
+  }
+  return nchunk;
+}
+
+int chain_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
+                   std::vector<double> *chunk_cost, int core_lo, int core_hi) {
+  const int nd = p.nd, nd2 = nd * nd, d1 = p.i[0].n, nx = p.X.n;
+  const int ncore = nd2 * nd2;
+  if (core_hi < 0) core_hi = ncore;
+  const bool all = core_lo == 0 && core_hi == ncore;
+  const int *J = p.two_j;
+  const ChainGeom &g = p.ch;
+  const int w4lo = p.K[2].lo2, w4hi = w4lo + 2 * (p.K[2].n - 1);
+  const int w3lo = p.K[1].lo2, w3hi = w3lo + 2 * (p.K[1].n - 1);
+  // Cost of the pairs (unit, l34) with non-empty windows, in matrix-core steps of a wavefront: the
+  // update and P, and about as much again as thirty of them for the G / H stage and the barrier.
+  auto pair_cost = [&](int o24, int xi, int o35, int o34) {
+    const int x = p.X.lo2 + 2 * xi, l24 = J[L24] + 2 * o24, l34 = J[L34] + 2 * o34, l35 = J[L35] + 2 * o35;
+    const int a4 = std::max(std::max(std::abs(l24 - l34), std::abs(l35 - x)), w4lo);
+    const int a3 = std::max(std::max(std::abs(l34 - l35), std::abs(l24 - x)), w3lo);
+    const int n4 = (std::min(std::min(l24 + l34, l35 + x), w4hi) - a4) / 2 + 1;
+    const int n3 = (std::min(std::min(l34 + l35, l24 + x), w3hi) - a3) / 2 + 1;
+    if (a4 > std::min(std::min(l24 + l34, l35 + x), w4hi) || a3 > std::min(std::min(l34 + l35, l24 + x), w3hi))
+      return 0.0;
+    const int s4 = (n4 + 3) / 4, s3 = (n3 + 3) / 4, nq = (n3 + 15) / 16;
+    return 30.0 + g.ct * s3 + nq * s4;
+  };
+  std::vector<double> unit((size_t)nd * nx * nd, 0.0);  // [o24][x][o35], every l34
+  for (int o24 = 0; o24 < nd; ++o24)
+    for (int xi = 0; xi < nx; ++xi)
+      for (int o35 = 0; o35 < nd; ++o35) {
+        double c = 0.0;
+        for (int o34 = 0; o34 < nd; ++o34) c += pair_cost(o24, xi, o35, o34);
+        unit[((size_t)o24 * nx + xi) * nd + o35] = c > 0.0 ? c + 15.0 : 0.05;
+      }
+  // Units of a core range: those of its (l24, l25) pairs; a partial pair keeps the whole pair's cost.
+  const int pair_lo = core_lo / nd2, pair_hi = core_hi > core_lo ? (core_hi + nd2 - 1) / nd2 : pair_lo;
+  const int u_lo = pair_lo * nx * nd, u_hi = (all ? nd2 : pair_hi) * nx * nd;
+  int nchunk = std::max(1, target_wg / (d1 * g.nrb));
+  nchunk = (int)std::min<int64_t>(nchunk, std::max<int64_t>(1, (int64_t)(kRingMaxPartialBytes / ((size_t)p.a_size * sizeof(double)))));
+  nchunk = std::min(nchunk, std::max(1, u_hi - u_lo));
+  bounds.assign((size_t)d1 * (nchunk + 1), 0);
+  if (chunk_cost) chunk_cost->assign((size_t)d1 * nchunk, 0.0);
+  std::vector<double> cs((size_t)std::max(0, u_hi - u_lo));
+  for (int n1 = 0; n1 < d1; ++n1) {
+    const int i1 = p.i[0].lo2 + 2 * n1;
+    double total = 0.0;
+    size_t k = 0;
+    for (int pr = pair_lo; pr < (all ? nd2 : pair_hi); ++pr) {
+      const int o24 = pr / nd, l25 = J[L25] + 2 * (pr % nd);
+      for (int xi = 0; xi < nx; ++xi) {
+        const int x = p.X.lo2 + 2 * xi;
+        const bool live = x >= std::abs(i1 - l25) && x <= i1 + l25;
+        const double *uc = unit.data() + ((size_t)o24 * nx + xi) * nd;
+        for (int o35 = 0; o35 < nd; ++o35) total += cs[k++] = live ? uc[o35] : 0.01;
+      }
+    }
+    int *bd = bounds.data() + (size_t)n1 * (nchunk + 1);
+    double run = 0.0;
+    int q = 0;
+    const int nu = u_hi - u_lo;
+    for (int ch = 1; ch < nchunk; ++ch) {
+      const double target = total * ch / nchunk;
+      while (q < nu && run + 0.5 * cs[q] < target) run += cs[q++];
+      bd[ch] = u_lo + q;
+    }
+    bd[0] = u_lo;
+    bd[nchunk] = u_hi;
+    if (chunk_cost)
+      for (int ch = 0; ch < nchunk; ++ch)
+        for (int u = bd[ch]; u < bd[ch + 1]; ++u) (*chunk_cost)[(size_t)n1 * nchunk + ch] += cs[u - u_lo];
   }
   return nchunk;
 }
@@ -353,27 +411,6 @@ int triad_count(int lo, int n, int a, int x) {
 }
 
 }  // namespace
-
-// Accumulator tiles the wide kernel's A update multiplies per k step, summed over the row
-// blocks and the eight wavefronts of a workgroup: wavefront w holds the tiles w + 8 j of its
-// block and runs them in groups of three (the last group of the fourteen holds two), a group
-// whole once it holds one of them.
-// k steps of four the wide kernel's T stage multiplies for a spin value with s active steps:
-// three unconditionally, the last two when the fourth is active.
-static int t_steps(int s) { return s <= 3 ? 3 : 5; }
-
-static int wide_update_tiles(int RT, int CT, int nrb) {
-  const int RTb = (RT + nrb - 1) / nrb;
-  int total = 0;
-  for (int rb = 0; rb < nrb; ++rb) {
-    const int ntile = std::max(0, std::min(RTb, RT - rb * RTb)) * CT;
-    for (int w = 0; w < 8; ++w) {
-      const int ntw = std::max(0, (ntile - w + 7) / 8);
-      total += std::min(14, (ntw + 2) / 3 * 3);
-    }
-  }
-  return total;
-}
 
 void count_work(const Plan &p, double out[5]) {
   const int nd = p.nd, nd3 = nd * nd * nd;
@@ -472,32 +509,11 @@ void count_work(const Plan &p, double out[5]) {
               useful += 2.0 * d5 * d4 * na4 * na3 + 2.0 * d5 * d4 * na3 * d3 * d2;
               const int s4 = ((b4 - w4lo) / 2) / 4 - ((a4 - w4lo) / 2) / 4 + 1;
               const int s3 = ((b3 - w3lo) / 2) / 4 - ((a3 - w3lo) / 2) / 4 + 1;
-              if (p.ring_cls == kWideClass) {
-                // Every stage on 16x16x4 tiles (2048 flops each): T5 / T2 over the active k5 /
-                // k2 values in steps of 4 (at least three steps, else five), G / H per k4 / k3
-                // position of the windows rounded out to multiples of 4 over the spin values in
-                // steps of 4 (repeated per row block), P over the row tiles and one or two k3
-                // column tiles, the update over the wavefronts' groups of tiles.
-                int tsteps = 0;
-                for (int o = 0; o < nd && o < 64; ++o) {
-                  if (n5[o] > 0) {
-                    const int ka = std::max(lo5[o], std::abs(x - J[L14]));
-                    const int kb = std::min(lo5[o] + 2 * (n5[o] - 1), x + J[L14]);
-                    if (kb >= ka) tsteps += t_steps(((kb - lo5[o]) / 2) / 4 - ((ka - lo5[o]) / 2) / 4 + 1);
-                  }
-                  if (n2[o] > 0) {
-                    const int ka = std::max(lo2[o], std::abs(J[L13] - x));
-                    const int kb = std::min(lo2[o] + 2 * (n2[o] - 1), J[L13] + x);
-                    if (kb >= ka) tsteps += t_steps(((kb - lo2[o]) / 2) / 4 - ((ka - lo2[o]) / 2) / 4 + 1);
-                  }
-                }
-                const int RT = (d5 * d4 + 15) / 16, CT = (d3 * d2 + 15) / 16;
-                const int nq = ((((b3 - w3lo) / 2) | 3) + 16) / 16;
-                const int upd_tiles = wide_update_tiles(RT, CT, p.ring_nrb);
-                const int nG = (((b4 - w4lo) / 2) | 3) - (((a4 - w4lo) / 2) & ~3) + 1;
-                const int nH = (((b3 - w3lo) / 2) | 3) - (((a3 - w3lo) / 2) & ~3) + 1;
-                const double per_block = tsteps + (double)(nG + nH) * ((nd + 3) / 4);
-                executed += 2048.0 * (p.ring_nrb * per_block + (double)RT * nq * s4 + (double)upd_tiles * s3);
+              if (p.chain) {
+                // 16x16x4 matrix-core steps (2048 flops each) of P and the update; T and G / H run
+                // on the vector ALUs.
+                const int RT = (d5 * d4 + 15) / 16, q4 = (na4 + 3) / 4, q3 = (na3 + 3) / 4;
+                executed += 2048.0 * RT * ((p.ch.smax > 4 ? 2 : 1) * q4 + p.ch.ct * q3);
               } else {
                 executed += 2.0 * rows * KW * 4 * s4 + 2.0 * rows * cols * 4 * s3;
               }

@@ -680,13 +680,13 @@ int ring_class(int DI, int DK, int KW) {
 }
 
 int ring_row_blocks(const Plan &p) {
-  if (p.ring_cls == kWideClass) return p.ring_nrb;
+  if (p.chain) return p.ch.nrb;
   return p.ring_cls >= 4 ? 4 : 1;
 }
 
 size_t ring_smem_bytes(int cls, int nd, int stg) {
   size_t out = 0;
-  if (cls == kWideClass) return 0;  // sized per configuration (wide_smem_bytes)
+  if (cls == kWideClass) return 0;  // sized per configuration (chain_smem_bytes)
   dispatch(
       cls, nd,
       [&](auto v) {
@@ -698,7 +698,7 @@ size_t ring_smem_bytes(int cls, int nd, int stg) {
 }
 
 int ring_stage_levels(int cls, int nd, int levels[3]) {
-  if (cls == kWideClass) {  // reads boosters straight into the matrix-core operands
+  if (cls == kWideClass) {  // no staging
     levels[0] = 0;
     return 1;
   }
@@ -728,7 +728,7 @@ hipError_t ring_init_attributes() {
     hipError_t e = dispatch(cls, 0, [](auto v) { return decltype(v)::init(); });
     if (e != hipSuccess) return e;
   }
-  hipError_t e = wide_init_attributes();
+  hipError_t e = chain_init_attributes();
   if (e != hipSuccess) return e;
   return adjoint_ring_init_attributes();
 }

@@ -383,7 +383,10 @@ __global__ void ring_table_kernel(TableParams tp, int64_t total) {
     case 3: size = (int64_t)nd * nd * NX * nK3 * nK2; break;
     default: size = (int64_t)nd * NX * nK2 * n1; break;
   }
-  if (idx >= size) return;
+  if (idx >= size) {  // padding: read (times zero) by operand reads that run past a table's end
+    tp.tables[g] = 0.0;
+    return;
+  }
   int64_t r = idx;
   double v = 0.0;
   int ph = 0;  // exponent of -1 (two-units, halved below)

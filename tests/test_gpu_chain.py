@@ -1,0 +1,74 @@
+"""The x-outer kernel of the factorised order at the edges of its tiles, against the CPU oracle.
+
+One workload per row and column tile count (one and two row tiles per wavefront, one and two row
+blocks, one to sixteen column tiles), for one to fourteen shells per link (one to four groups of
+four spin values) and k windows of at most and of more than sixteen positions; the ones with many
+shells over a few cores, on the oracle's shells.  Tolerance: an output entry is a sum of at most
+16^2 shells of a core times 16 k3, k4 and x values each, every product rounded a few times:
+about 16^3 units of 2^-53 relative to the largest entry, 5e-13.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import workloads
+from oracle import ranges as R
+from oracle import vertex as V
+
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-13
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2107_13952_amd as lib
+    return lib
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    return torch
+
+
+# Twice the spins, dl, cores (None: all), dimensions
+CASES = [([2, 6, 3, 1, 7, 6, 5, 7, 8, 8], 0, None, (1, 3, 7, 4, 2)),
+         ([8, 10, 4, 6, 9, 4, 7, 10, 7, 4], 1, None, (5, 5, 8, 2, 5)),
+         ([9, 15, 4, 6, 0, 7, 16, 12, 15, 15], 0, None, (3, 1, 1, 5, 7)),
+         ([4, 4, 5, 3, 5, 5, 6, 4, 3, 6], 2, None, (4, 5, 4, 5, 4)),
+         ([10, 3, 2, 13, 9, 9, 12, 7, 13, 10], 1, None, (2, 9, 4, 3, 11)),
+         ([9, 9, 7, 7, 9, 9, 7, 8, 10, 8], 0, None, (8, 8, 9, 8, 7)),
+         ([13, 12, 8, 11, 14, 11, 14, 14, 8, 7], 0, None, (9, 12, 9, 7, 7)),
+         ([10, 13, 11, 12, 12, 16, 14, 14, 11, 13], 0, None, (11, 11, 12, 12, 12)),
+         ([15, 12, 15, 16, 13, 15, 13, 14, 13, 14], 0, None, (13, 14, 13, 15, 13)),
+         ([15] * 10, 0, None, (16, 16, 16, 16, 16)),
+         ([14, 5, 14, 1, 3, 14, 9, 5, 9, 7], 9, (4321, 4326), (2, 4, 3, 6, 2)),
+         ([8, 8, 6, 2, 15, 7, 8, 8, 13, 13], 9, (777, 779), (3, 5, 8, 5, 3)),
+         ([1, 6, 9, 8, 10, 7, 8, 9, 9, 5], 9, (9990, 10000), (2, 2, 7, 6, 6)),
+         ([7, 7, 8, 10, 6, 8, 9, 10, 9, 6], 9, (0, 1), (7, 7, 7, 7, 7)),
+         ([3, 2, 3, 2, 4, 3, 4, 3, 3, 3], 13, (20000, 20004), (3, 4, 3, 4, 3))]
+
+
+@pytest.mark.parametrize("two_j,dl,cores,dims", CASES)
+def test_tile_edges(lib, torch, two_j, dl, cores, dims):
+    assert tuple(lib.layout(two_j, dl)[0]) == dims
+    b = workloads.synthetic_boosters(400 + dl, R.block_shapes(two_j, dl))
+    bd = torch.from_numpy(b).cuda()
+    print(f"tile edges {two_j} dl={dl} cores={cores}", flush=True)
+    sys.stdout.flush()
+    if cores is None:
+        a, ref = lib.vertex_tensor(two_j, dl, 1.2, bd), V.vertex_tensor(two_j, dl, b)
+    else:
+        nd = dl + 1
+        lo, hi = cores
+        shells = []
+        for core in range(lo, hi):
+            o24, o25, o34, o35 = core // nd ** 3, core // nd ** 2 % nd, core // nd % nd, core % nd
+            shells += [(o23, o24, o25, o34, o35, o45) for o23 in range(nd) for o45 in range(nd)]
+        a = lib.vertex_tensor_cores(two_j, dl, 1.2, bd, lo, hi)
+        ref = V.vertex_tensor(two_j, dl, b, shells=shells)
+    scale = np.abs(ref).max()
+    assert scale > 0
+    assert np.abs(a.cpu().numpy() - ref).max() <= TOL * scale
