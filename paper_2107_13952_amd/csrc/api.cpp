@@ -303,7 +303,7 @@ int plan_for(eprl_ctx *c, const int two_j[10], int dl, const Plan **out) {
 // workgroups on 256 CUs, so that cost-balanced chunks finish together.  A batch uses the same
 // schedule per configuration, which keeps its tensors bitwise equal to those of plain calls.
 constexpr int kRingTargetWG = 8192;
-constexpr int kChainTargetWG = 8192;
+constexpr int kChainTargetWG = 6144;
 int default_target(const Plan &p) { return p.chain ? kChainTargetWG : kRingTargetWG; }
 
 struct Prepared {

@@ -38,6 +38,7 @@
 // A[c & 3][g], operand B[g][c & 3], result D[g][c & 3].
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "eprl_internal.hpp"
 
@@ -254,43 +255,29 @@ __device__ __forceinline__ ChainStep step_at(const ChainStep *p) {
   return s;
 }
 
-// How the four blocks of a v_mfma_f64_4x4x4 are used for the products of a side (T rows x booster
-// columns, dt x dm, one product per window position): 2^wj blocks along the booster columns, 2^wp
-// positions; nq instructions cover the T rows (from LDS), so that no lane reads a booster entry
-// from memory that another lane of the instruction reads.
-struct Blocks {
-  int wj, wp, nq;
-  __host__ __device__ Blocks(int dt, int dm) {
-    wj = dm <= 4 ? 0 : dm <= 8 ? 1 : 2;
-    wp = 2 - wj;
-    nq = (dt + 3) >> 2;
-  }
-};
-
 // Doubles of one window position of M4 (M3): pairs of groups of four spin values, [g][column][group of
 // the pair], then an odd last group, [g][column].
 __host__ __device__ inline int chain_mrow(int nd, int dm) { return 4 * ((nd + 3) / 4) * (dm <= 4 ? 4 : dm <= 8 ? 8 : 16); }
 
-// RT row tiles per wavefront, CT column tiles; windows of at most 16 NQ positions.
-template <int RT, int CT, int NQ>
-__device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int n1, int rb, double *smem) {
-  constexpr int SM = 4 * NQ;  // steps of four window positions
-  constexpr int NB = 4;       // groups of a chunk of the G / H stage
+// RT row tiles per wavefront, CT column tiles, KS groups of four spin values; windows of at most 32
+// positions.
+template <int RT, int CT, int KS>
+__device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int n1, int cb, double *smem) {
+  constexpr int SM = 8;                      // steps of four window positions
+  constexpr int NB = RT * CT >= 14 ? 2 : 4;  // instructions per T row group in a chunk (registers)
   const int tid = threadIdx.x, nthr = blockDim.x, nw = nthr >> 6;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, c = l & 15;
   const int nd = rp.nd, nx = rp.nx;
   const int d1 = rp.i_n[0], d2 = rp.i_n[1], d3 = rp.i_n[2], d4 = rp.i_n[3], d5 = rp.i_n[4];
   const int R = d5 * d4, C = d3 * d2;
-  const int rho0 = rb * rp.rtb * 16, GW = imin(R - rho0, rp.rtb * 16);  // rows of this block
-  const int S = rp.ts, t5n = nd * rp.n4t * S, t2n = nd * rp.n3t * S, SP = (rp.smax + 1) / 2;
+  const int sig0 = cb * rp.ctb * 16, CW = imin(C - sig0, rp.ctb * 16);  // columns of this block
+  const int S = rp.ts, t5n = nd * rp.n4t * S, t2n = nd * rp.n3t * S;
   // LDS: T rows of the unit between zero rows (a k outside a spin's rows reads another spin's or a zero
   // row, times a zero booster entry), G, H.
   double *T5s = smem + rp.tpre * S, *T2s = T5s + t5n;
-  double *Gs = T2s + t2n + rp.tpost * S, *Hs = Gs + SP * 8 * GW;
-  const int nK3 = rp.K_n[1], ks = (nd + 3) >> 2;
-  const Blocks bg(d5, d4), bh(d2, d3);
-  const int mr4 = rp.mr4, mr3 = rp.mr3;  // booster entries of one window position
-  const double *M4 = rp.M4, *M3 = rp.M3, *U3 = rp.U3;
+  double *Gs = T2s + t2n + rp.tpost * S, *Hs = Gs + rp.sp * 8 * R;
+  const int nK3 = rp.K_n[1];
+  const double *U3 = rp.U3;
   const double *T5 = rp.T5 + n1 * t5n, *T2 = rp.T2 + n1 * t2n;
   const int two_i1 = rp.i_lo2[0] + 2 * n1, l25_0 = rp.two_j[L25], xlo2 = rp.xlo2;
   const int core_lo = rp.core_lo, core_hi = rp.core_hi;
@@ -301,114 +288,151 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
 #pragma unroll
     for (int t = 0; t < CT; ++t) acc[r][t] = d4v{0.0, 0.0, 0.0, 0.0};
 
-  // This lane's block along the booster columns (bj) and the positions (bp), each side; its place in
-  // the operands: spin value 4 s + g, T row (booster column) c & 3 of the block.
-  const int bj4 = (c >> 2) & ((1 << bg.wj) - 1), bp4 = (c >> 2) >> bg.wj, jm4 = 4 * bj4 + (c & 3);
-  const int bj3 = (c >> 2) & ((1 << bh.wj) - 1), bp3 = (c >> 2) >> bh.wj, jm3 = 4 * bj3 + (c & 3);
-  const uint32_t mp4 = bp4 * mr4 + ((g * 4 << bg.wj) + jm4) * 2, ms4 = bp4 * mr4 + (g * 4 << bg.wj) + jm4;
-  const uint32_t mp3 = bp3 * mr3 + ((g * 4 << bh.wj) + jm3) * 2, ms3 = bp3 * mr3 + (g * 4 << bh.wj) + jm3;
-  int to4[4], to3[4];  // T rows of spin value 4 s + g for k = 0 (a spin beyond nd: times a zero booster)
+  // One side of the G / H stage: T rows (dt) x booster columns (dm), one product per window position.
+  // The four blocks of a v_mfma_f64_4x4x4 are 4 / 2^wp groups of four booster columns times 2^wp
+  // positions; nq instructions cover the T rows (from LDS), so that no lane reads a booster entry
+  // from memory that another lane of the instruction reads.  A chunk is NB instructions per T row
+  // group: positions p, p + 4 and, for NB = 4, the same astep further on.
+  struct Side {
+    const double *M;
+    int mr, wp, astep, lgs, nq;  // lgs: log2 of the positions of a chunk
+    int wstep;                   // doubles of the buffer from a position to the one astep further on
+    int W, rel0, relq;           // columns of the buffer; this lane's for T row group 0, step per group
+    int rows;                    // T rows (none: a column of the padding)
+    uint32_t mp, ms;
+    int to[KS];  // T row of spin value 4 s + g, k = 0 (a spin beyond nd: times a zero booster)
+    int wo;
+  };
+  auto make_side = [&](bool h) {
+    Side q;
+    const int dt = h ? d2 : d5, dm = h ? d3 : d4, wj = dm <= 4 ? 0 : dm <= 8 ? 1 : 2;
+    q.M = h ? rp.M3 : rp.M4;
+    q.mr = h ? rp.mr3 : rp.mr4;
+    q.wp = 2 - wj;
+    q.astep = q.wp == 2 ? 8 : 1 << q.wp;
+    q.lgs = (NB == 4 ? 2 : 1) + q.wp;
+    q.nq = (dt + 3) >> 2;
+    const int b = c >> 2, bp = b >> wj, jm = 4 * (b & ((1 << wj) - 1)) + (c & 3);
+    q.W = h ? CW : R;
+    q.wstep = imin(q.astep, 4) * 2 * q.W;
+    q.rel0 = h ? jm * d2 + g - sig0 : g * d4 + jm;
+    q.relq = h ? 4 : 4 * d4;
+    q.rows = jm < dm ? dt : 0;
+    q.mp = bp * q.mr + ((g * 4 << wj) + jm) * 2;
+    q.ms = bp * q.mr + (KS - 1) * (16 << wj) + (g * 4 << wj) + jm;
+    const int nt = h ? rp.n3t : rp.n4t;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int o = imin(4 * s + g, nd - 1);
-    to4[s] = (o * rp.n4t * 2 - chain_klo(rp.two_j, rp.wlo, rp.whi, false, o)) * (S / 2) + bp4 * S + (c & 3);
-    to3[s] = (o * rp.n3t * 2 - chain_klo(rp.two_j, rp.wlo, rp.whi, true, o)) * (S / 2) + bp3 * S + (c & 3);
-  }
-  // Entry (position p, column) of G and H: ((p >> 3) * 4 + (p & 3)) * 2 W + 2 column + (p >> 2 & 1), so
-  // that the operands of two consecutive steps of four positions are one 16-byte read; a lane's
-  // results have T row 4 q + g and booster column jm.
-  const int wo4 = bp4 * 2 * GW + 2 * (g * d4 + jm4 - rho0), wo3 = bp3 * 2 * C + 2 * (jm3 * d2 + g);
+    for (int s = 0; s < KS; ++s) {
+      const int o = imin(4 * s + g, nd - 1);
+      q.to[s] = (o * nt * 2 - chain_klo(rp.two_j, rp.wlo, rp.whi, h, o)) * (S / 2) + bp * S + (c & 3);
+    }
+    // Entry (position p, column) of G and H: ((p >> 3) * 4 + (p & 3)) * 2 W + 2 column + (p >> 2 & 1),
+    // so that the operands of two consecutive steps of four positions are one 16-byte read.
+    q.wo = bp * 2 * q.W;
+    return q;
+  };
+  const Side sg = make_side(false), sh = make_side(true);
 
-  // Booster operands of a chunk of NB groups: two groups of four spin values to a read, an odd last
-  // group by itself.
+  // Booster operands of a chunk: two groups of four spin values to a read, an odd last one by itself.
   struct Mops {
-    d2v p[NB];
+    d2v p[KS / 2 > 0 ? KS / 2 : 1][NB];
     double s[NB];
   };
-  // Chunk ch of a step: side and first position; false past the last.
-  auto chunk_of = [&](const ChainStep &st, int ch, bool &h, int &pos) {
-    const int cg = ((((st.n4 + 3) & ~3) >> bg.wp) + NB - 1) / NB;
-    const int cht = cg + ((((st.n3 + 3) & ~3) >> bh.wp) + NB - 1) / NB;
-    h = ch >= cg;
-    pos = h ? ((ch - cg) * NB) << bh.wp : (ch * NB) << bg.wp;
-    return ch < cht;
+  auto chunks = [&](const Side &q, int n) {
+    return q.lgs >= 3 ? (n + (1 << q.lgs) - 1) >> q.lgs : ((n + 7) >> 3) << (3 - q.lgs);
   };
-  auto load_m = [&](const ChainStep &st, int ch, Mops &m) {
-    bool h;
-    int pos;
-    if (!chunk_of(st, ch, h, pos)) return;
-    const double *base = h ? M3 + st.m3 + pos * mr3 : M4 + st.m4 + pos * mr4;
-    const int step = h ? mr3 << bh.wp : mr4 << bg.wp;
-    if (ks > 1) {
+  auto first_of = [&](const Side &q, int ch) {
+    const int sub = 3 - q.lgs;
+    return sub <= 0 ? ch << q.lgs : (ch >> sub) * 8 + ((ch & ((1 << sub) - 1)) << (q.lgs - 1));
+  };
+  auto load_m = [&](const Side &q, int m0, int ch, Mops &m) {
+    const int at = m0 + first_of(q, ch) * q.mr;
 #pragma unroll
-      for (int i = 0; i < NB; ++i) m.p[i] = ldg2_at(base + i * step, h ? mp3 : mp4);
-    }
-    if (ks & 1) {
-      base += (ks - 1) * (4 * 4) << (h ? bh.wj : bg.wj);
+    for (int i = 0; i < NB; ++i) {
+      const uint32_t off = at + (i % (NB / 2) * q.astep + i / (NB / 2) * 4) * q.mr;
 #pragma unroll
-      for (int i = 0; i < NB; ++i) m.s[i] = ldg_at(base + i * step, h ? ms3 : ms4);
+      for (int s = 0; s < KS / 2; ++s) m.p[s][i] = ldg2_at(q.M, q.mp + off + s * (8 * 16 >> q.wp));
+      if (KS & 1) m.s[i] = ldg_at(q.M, q.ms + off);
     }
   };
-  auto multiply = [&](const ChainStep &st, int ch, const Mops &m) {
-    bool h;
-    int pos;
-    chunk_of(st, ch, h, pos);
-    const int wp = h ? bh.wp : bg.wp, nq = h ? bh.nq : bg.nq;
-    const int np = ((h ? st.n3 : st.n4) + 3) & ~3, W = h ? C : GW;
-    const double *Ts = (h ? T2s + st.t2 : T5s + st.t5) + pos * S;
-    double *dst = (h ? Hs + wo3 : Gs + wo4);
-    d2v m2[NB];  // spin values 8 .. 15 when there are four groups of them
-    if (ks == 4) {
-      const double *base = (h ? M3 + st.m3 + pos * mr3 : M4 + st.m4 + pos * mr4) + (4 * 8 << (h ? bh.wj : bg.wj));
+  // T row groups q0 .. q0 + QN - 1 of a chunk.
+  auto multiply_rows = [&](const Side &q, int (&ta)[KS], bool two, double *dst, int q0, const Mops &m, auto qn) {
+    constexpr int QN = decltype(qn)::value;
+    double d[QN][NB];
 #pragma unroll
-      for (int i = 0; i < NB; ++i) m2[i] = ldg2_at(base + i * (h ? mr3 << wp : mr4 << wp), h ? mp3 : mp4);
+    for (int k = 0; k < QN; ++k)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) d[k][i] = 0.0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      double t[QN][NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int k = 0; k < QN; ++k)
+          t[k][i] = T5s[ta[s] + (i % (NB / 2) * q.astep + i / (NB / 2) * 4) * S + 4 * k];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (i == NB / 2 && !two) break;
+        const double b = s < (KS & ~1) ? ((s & 1) ? m.p[s / 2][i].y : m.p[s / 2][i].x) : m.s[i];
+#pragma unroll
+        for (int k = 0; k < QN; ++k) d[k][i] = mfma4(t[k][i], b, d[k][i]);
+      }
     }
-    for (int q = 0; q < nq; ++q) {
-      double d[NB];
 #pragma unroll
-      for (int i = 0; i < NB; ++i) d[i] = 0.0;
-      auto step = [&](int s, auto operand) {
-        double t[NB];
-        const double *tq = Ts + (h ? to3[s] : to4[s]) + 4 * q;
+    for (int k = 0; k < QN; ++k) {
+      const int rel = q.rel0 + (q0 + k) * q.relq;
+      if (4 * (q0 + k) + g < q.rows && (unsigned)rel < (unsigned)q.W) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) t[i] = tq[(i << wp) * S];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) d[i] = mfma4(t[i], operand(i), d[i]);
-      };
-      if (ks > 1) {
-        step(0, [&](int i) { return m.p[i].x; });
-        step(1, [&](int i) { return m.p[i].y; });
-      }
-      if (ks & 1) {
-        if (ks == 1) step(0, [&](int i) { return m.s[i]; });
-        else step(2, [&](int i) { return m.s[i]; });
-      }
-      if (ks == 4) {
-        step(2, [&](int i) { return m2[i].x; });
-        step(3, [&](int i) { return m2[i].y; });
-      }
-      const int it = 4 * q + g, rho = it * d4 + jm4 - rho0;
-      if (h ? it < d2 && jm3 < d3 : it < d5 && jm4 < d4 && (unsigned)rho < (unsigned)GW) {
-        double *dq = dst + (h ? 8 * q : 8 * q * d4);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int p = pos + (i << wp);  // uniform; a multiple of 2^wp
-          if (p < np) dq[((p >> 3) * 4 + (p & 3)) * 2 * W + ((p >> 2) & 1)] = d[i];
-        }
+        for (int i = 0; i < NB / 2; ++i)
+          *reinterpret_cast<d2v *>(dst + i * q.wstep + 2 * rel) = d2v{d[k][i], d[k][i + NB / 2]};
       }
     }
   };
-  Mops ma, mb;
-  double u3[SM][NQ];
+  auto multiply = [&](const Side &q, double *buf, int trow, int n, int ch, const Mops &m) {
+    const int p0 = first_of(q, ch);
+    const bool two = (p0 & ~7) + 4 < n;  // (else the second half is past the window)
+    double *dst = buf + ((p0 >> 3) * 4 + (p0 & 3)) * 2 * q.W + q.wo;
+    int ta[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) ta[s] = q.to[s] + trow + p0 * S;
+    int k = 0;
+    for (; k + 2 <= q.nq; k += 2) {
+      multiply_rows(q, ta, two, dst, k, m, std::integral_constant<int, 2>());
+#pragma unroll
+      for (int s = 0; s < KS; ++s) ta[s] += 8;
+    }
+    if (k < q.nq) multiply_rows(q, ta, two, dst, k, m, std::integral_constant<int, 1>());
+  };
+  // This wavefront's chunks of a side: ch, ch + nw, ...; m holds the first one's operands.
+  auto side_stage = [&](const Side &q, double *buf, int trow, int n, int m0, int ch, Mops &m) {
+    const int nc = chunks(q, n);
+    if (ch >= nc) return;
+    for (;;) {
+      const int next = ch + nw;
+      if (next >= nc) break;
+      Mops mx;
+      load_m(q, m0, next, mx);
+      multiply(q, buf, trow, n, ch, m);
+      m = mx;
+      ch = next;
+    }
+    multiply(q, buf, trow, n, ch, m);
+  };
+  Mops mg, mh;
+  auto prefetch_m = [&](const ChainStep &st) {
+    if (w < chunks(sg, st.n4)) load_m(sg, st.m4, w, mg);
+    if (nw - 1 - w < chunks(sh, st.n3)) load_m(sh, st.m3, nw - 1 - w, mh);
+  };
+  double u3[SM];  // of the first 16 k3
   const uint32_t uo = g * nK3 + c;
-  auto load_u3 = [&](const ChainStep &st) {
-    const double *base = U3 + st.u3;
+  auto load_u3 = [&](const ChainStep &st, int k3) {
+    const double *base = U3 + st.u3 + k3;
 #pragma unroll
-    for (int s = 0; s < SM; ++s)
-      if (4 * s < st.n4) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) u3[s][q] = ldg_at(base + 4 * s * nK3 + 16 * q, uo);
-      }
+    for (int s = 0; s < SM; ++s) {
+      if (4 * s >= st.n4) break;
+      u3[s] = ldg_at(base, uo + 4 * s * nK3);
+    }
   };
 
   // Zero rows, and finite values wherever an operand read can run past what has been written.
@@ -442,8 +466,8 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
     ChainStep st = step_at(sp);
     while (st.n4 > 0 && st.more && core0 + st.o34 * nd < core_lo) st = step_at(++sp);
     if (st.n4 == 0 || core0 + st.o34 * nd < core_lo || core0 + st.o34 * nd >= core_hi) continue;
-    load_m(st, w, ma);
-    load_u3(st);
+    prefetch_m(st);
+    load_u3(st, 0);
     __syncthreads();  // every wavefront is past the previous unit's steps
     {
       const double *src = T5 + (int64_t)k5 * d1 * t5n;
@@ -458,86 +482,66 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
     }
     __syncthreads();
     for (;;) {
-      // ---- G and H, a chunk's booster entries read during the products of the one before
-      bool h;
-      int pos;
-      if (chunk_of(st, w, h, pos)) {
-        for (int ch = w;; ch += 2 * nw) {
-          load_m(st, ch + nw, mb);
-          multiply(st, ch, ma);
-          if (!chunk_of(st, ch + nw, h, pos)) break;
-          load_m(st, ch + 2 * nw, ma);
-          multiply(st, ch + nw, mb);
-          if (!chunk_of(st, ch + 2 * nw, h, pos)) break;
-        }
-      }
+      // ---- G and H, the wavefronts' chunks of G from the first on, of H from the last
+      side_stage(sg, Gs, st.t5, st.n4, st.m4, w, mg);
+      side_stage(sh, Hs, t5n + st.t2, st.n3, st.m3, nw - 1 - w, mh);
       ChainStep sn = st;
       bool more = st.more != 0;
       if (more) {
         sn = step_at(++sp);
         more = core0 + sn.o34 * nd < core_hi;
-        if (more) load_m(sn, w, ma);
+        if (more) prefetch_m(sn);
       }
       __syncthreads();
-      const int s4 = (st.n4 + 3) >> 2, s3 = (st.n3 + 3) >> 2;
-      const d2v *gp = reinterpret_cast<const d2v *>(Gs) + g * GW + w * RT * 16 + c;
-      const d2v *hp = reinterpret_cast<const d2v *>(Hs) + g * C + c;
+      const int s4 = (st.n4 + 3) >> 2;
+      const d2v *gp = reinterpret_cast<const d2v *>(Gs) + g * R + w * RT * 16 + c;
+      const d2v *hp = reinterpret_cast<const d2v *>(Hs) + g * CW + c;
+      // Sixteen k3 at a time (more than sixteen are rare, and the rows of U3 are then read in place).
+      for (int k3 = 0;; k3 += 16) {
+        // ---- P transposed: rows k3, columns (i5, i4)
+        d4v pt[RT];
 #pragma unroll
-      for (int r0 = 0; r0 < RT; r0 += 2) {
-        // ---- P of two row tiles, transposed: rows k3, columns (i5, i4)
-        constexpr int NR = 2;
-        d4v pt[NR][NQ];
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) pt[r][q] = d4v{0.0, 0.0, 0.0, 0.0};
+        for (int r = 0; r < RT; ++r) pt[r] = d4v{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int s = 0; s < SM / 2; ++s) {
-          if (2 * s < s4) {
-            d2v gv[NR];
+          if (2 * s >= s4) break;
+          d2v gv[RT];
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-              if (r0 + r < RT) gv[r] = gp[s * 4 * GW + (r0 + r) * 16];
+          for (int r = 0; r < RT; ++r) gv[r] = gp[s * 4 * R + r * 16];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
+          for (int r = 0; r < RT; ++r) pt[r] = mfma(u3[2 * s], gv[r].x, pt[r]);
+          if (2 * s + 1 >= s4) break;
 #pragma unroll
-              for (int r = 0; r < NR; ++r)
-                if (r0 + r < RT) pt[r][q] = mfma(u3[2 * s][q], gv[r].x, pt[r][q]);
-            if (2 * s + 1 < s4) {
-#pragma unroll
-              for (int q = 0; q < NQ; ++q)
-#pragma unroll
-                for (int r = 0; r < NR; ++r)
-                  if (r0 + r < RT) pt[r][q] = mfma(u3[2 * s + 1][q], gv[r].y, pt[r][q]);
-            }
-          }
+          for (int r = 0; r < RT; ++r) pt[r] = mfma(u3[2 * s + 1], gv[r].y, pt[r]);
         }
-        if (r0 + 2 >= RT && more) load_u3(sn);
+        const bool last = k3 + 16 >= st.n3;
+        if (!last) load_u3(st, k3 + 16);
+        else if (more) load_u3(sn, 0);
         // ---- A(i1) += P H
+        const int s3 = (st.n3 - k3 + 3) >> 2;
 #pragma unroll
-        for (int s = 0; s < SM / 2; ++s) {
-          if (2 * s < s3) {
-            const bool both = 2 * s + 1 < s3;
+        for (int s = 0; s < 2; ++s) {
+          if (2 * s >= s3) break;
+          const bool both = 2 * s + 1 < s3;
 #pragma unroll
-            for (int t0 = 0; t0 < CT; t0 += 4) {
-              d2v hv[4];
+          for (int t0 = 0; t0 < CT; t0 += 4) {
+            d2v hv[4];
 #pragma unroll
-              for (int t = t0; t < t0 + 4 && t < CT; ++t) hv[t - t0] = hp[s * 4 * C + t * 16];
+            for (int t = t0; t < t0 + 4 && t < CT; ++t) hv[t - t0] = hp[s * 4 * CW + t * 16];
+#pragma unroll
+            for (int t = t0; t < t0 + 4 && t < CT; ++t)
+#pragma unroll
+              for (int r = 0; r < RT; ++r) acc[r][t] = mfma(pt[r][2 * s], hv[t - t0].x, acc[r][t]);
+            if (both) {
 #pragma unroll
               for (int t = t0; t < t0 + 4 && t < CT; ++t)
 #pragma unroll
-                for (int r = 0; r < NR; ++r)
-                  if (r0 + r < RT) acc[r0 + r][t] = mfma(pt[r][s >> 1][(2 * s) & 3], hv[t - t0].x, acc[r0 + r][t]);
-              if (both) {
-#pragma unroll
-                for (int t = t0; t < t0 + 4 && t < CT; ++t)
-#pragma unroll
-                  for (int r = 0; r < NR; ++r)
-                    if (r0 + r < RT) acc[r0 + r][t] = mfma(pt[r][s >> 1][(2 * s + 1) & 3], hv[t - t0].y, acc[r0 + r][t]);
-              }
+                for (int r = 0; r < RT; ++r) acc[r][t] = mfma(pt[r][2 * s + 1], hv[t - t0].y, acc[r][t]);
             }
           }
         }
+        if (last) break;
+        hp += 8 * CW;
       }
       if (!more) break;  // (the next unit begins with a barrier)
       __syncthreads();
@@ -549,29 +553,30 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
   const FastDiv by_d2(d2), by_d4(d4);
 #pragma unroll
   for (int t = 0; t < CT; ++t) {
-    const int sig = t * 16 + c, i3 = by_d2(sig), i2 = sig - i3 * d2;
+    const int sl = t * 16 + c, sig = sig0 + sl, i3 = by_d2(sig), i2 = sig - i3 * d2;
 #pragma unroll
     for (int r0 = 0; r0 < RT; ++r0)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int rl = (w * RT + r0) * 16 + g + 4 * r, rho = rho0 + rl, i5 = by_d4(rho), i4 = rho - i5 * d4;
-        if (rl < GW && sig < C) stg(out + ((i2 * d3 + i3) * d4 + i4) * d5 + i5, acc[r0][t][r]);
+        const int rho = (w * RT + r0) * 16 + g + 4 * r, i5 = by_d4(rho), i4 = rho - i5 * d4;
+        if (rho < R && sl < CW) stg(out + ((i2 * d3 + i3) * d4 + i4) * d5 + i5, acc[r0][t][r]);
       }
   }
 }
 
 // Wavefronts per SIMD the registers are budgeted for, and the most wavefronts of a workgroup.
-template <int RT, int CT, int NQ>
+template <int RT, int CT, int KS>
 constexpr int chain_waves() {
-  constexpr int need = 8 * RT * CT + 8 * RT * NQ + (NQ == 2 ? 144 : 128);  // accumulators, P, operands in flight
+  // accumulators and P; booster operands; U3, addresses, operands in flight
+  constexpr int need = 8 * RT * CT + 8 * RT + (RT * CT >= 14 ? 12 : 24) * KS + 104;
   return need <= 128 ? 4 : need <= 176 ? 3 : 2;
 }
-constexpr int kChainWg = 12;  // wavefronts of a workgroup
+constexpr int kChainWg = 8;  // wavefronts of a workgroup
 
-// Block b runs item b of the list (configuration, chunk, i1, row block), or, without a list,
-// configuration 0's chunk b / (d1 nrb), i1 and row block from b % (d1 nrb).
-template <int RT, int CT, int NQ>
-__global__ __launch_bounds__((chain_waves<RT, CT, NQ>() >= 3 ? kChainWg : 8) * 64, (chain_waves<RT, CT, NQ>()))
+// Block b runs item b of the list (configuration, chunk, i1, column block), or, without a list,
+// configuration 0's chunk b / (d1 nrb), i1 and column block from b % (d1 nrb).
+template <int RT, int CT, int KS>
+__global__ __launch_bounds__(kChainWg * 64, (chain_waves<RT, CT, KS>()))
 void chain_kernel(const RingParams *__restrict__ cfgs, const int *__restrict__ items) {
   extern __shared__ double smem[];
   int q0 = 0, q1, q2, q3;
@@ -587,37 +592,30 @@ void chain_kernel(const RingParams *__restrict__ cfgs, const int *__restrict__ i
     q2 = r / cfgs[0].nrb;
     q3 = r % cfgs[0].nrb;
   }
-  chain_item<RT, CT, NQ>(cfgs[q0], q1, q2, q3, smem);
+  chain_item<RT, CT, KS>(cfgs[q0], q1, q2, q3, smem);
 }
 
-// Kernel variants: row tiles per wavefront, column tiles, window class.
-constexpr int chain_key(int rt, int ct, int nq) { return (rt - 1) * 64 + ct * 2 + nq - 1; }
+// Kernel variants: row tiles per wavefront, column tiles, groups of four spin values.
+constexpr int kChainCT = 10;  // most column tiles of a workgroup
+constexpr int chain_key(int rt, int ct, int ks) { return ((rt - 1) * 16 + ct) * 4 + ks - 1; }
 constexpr int kChainKeys = 2 * 64;
 
 template <typename F>
 hipError_t chain_dispatch(int key, F &&f) {
-#define EPRL_RC(r, c)                                        \
-  case chain_key(r, c, 1): return f(chain_kernel<r, c, 1>); \
-  case chain_key(r, c, 2): return f(chain_kernel<r, c, 2>);
-#define EPRL_C(c) EPRL_RC(1, c) EPRL_RC(2, c)
+#define EPRL_K(r, c, k) \
+  case chain_key(r, c, k): return f(chain_kernel<r, c, k>);
+#define EPRL_C(c)                                         \
+  EPRL_K(1, c, 1) EPRL_K(1, c, 2) EPRL_K(1, c, 3) EPRL_K(1, c, 4) \
+  EPRL_K(2, c, 1) EPRL_K(2, c, 2) EPRL_K(2, c, 3) EPRL_K(2, c, 4)
   switch (key) {
     EPRL_C(1) EPRL_C(2) EPRL_C(3) EPRL_C(4) EPRL_C(5) EPRL_C(6) EPRL_C(7) EPRL_C(8) EPRL_C(9) EPRL_C(10)
-    EPRL_RC(1, 11) EPRL_RC(1, 12) EPRL_RC(1, 13) EPRL_RC(1, 14) EPRL_RC(1, 16)
     default: return hipErrorInvalidValue;
   }
-#undef EPRL_RC
+#undef EPRL_K
 #undef EPRL_C
 }
 
 }  // namespace
-
-// Row tiles per wavefront (rt) and row blocks (nrb) of A(i1) for RT x ct tiles.
-static void chain_split(int RT, int ct, int nq, ChainGeom &g) {
-  g.rt = RT >= 2 && ct <= 10 ? 2 : 1;
-  g.nrb = 1;
-  const int maxw = 8;
-  while ((((RT + g.nrb - 1) / g.nrb) + g.rt - 1) / g.rt > maxw) ++g.nrb;
-}
 
 bool chain_plan(Plan &p) {
   const int nd = p.nd;
@@ -642,33 +640,34 @@ bool chain_plan(Plan &p) {
   }
   if (w > 32) return false;
   const int R = d5 * d4, C = d3 * d2, RT = (R + 15) / 16;
-  g.ct = (C + 15) / 16;
-  g.smax = (w + 3) / 4;
   g.wm = w;
   // Rows that row offsets reach before the first T5 row and past the last T2 row (positions run up to
-  // three past a window's end).
+  // fifteen past a window's end).
   g.tpre = g.tpost = 0;
   const int wlo[2] = {p.K[1].lo2, p.K[2].lo2}, whi[2] = {hi2(p.K[1]), hi2(p.K[2])};
   for (int o = 0; o < nd; ++o) {
     g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, false, o) - wlo[1]) / 2 - o * g.n4t);
-    g.tpost = std::max(g.tpost, (whi[0] + 6 - chain_klo(J, wlo, whi, true, o)) / 2 + 1 - (nd - o) * g.n3t + 1);
+    g.tpost = std::max(g.tpost, (whi[0] + 30 - chain_klo(J, wlo, whi, true, o)) / 2 + 1 - (nd - o) * g.n3t + 1);
     // T5's offsets past its rows and T2's before them stay inside the T rows.
-    g.tpost = std::max(g.tpost, (whi[1] + 6 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t - nd * g.n3t + 1);
+    g.tpost = std::max(g.tpost, (whi[1] + 30 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t - nd * g.n3t + 1);
     g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, true, o) - wlo[0]) / 2 - o * g.n3t - nd * g.n4t);
   }
-  const int nq = g.smax > 4 ? 2 : 1;
-  if (g.ct == 15) g.ct = 16;
   g.ts = (std::max(d5, d2) + 1) & ~1;
   g.mr4 = chain_mrow(nd, d4);
   g.mr3 = chain_mrow(nd, d3);
-  chain_split(RT, g.ct, nq, g);
+  g.sp = (w + 7) / 8;
+  if (std::min(d3, d4) <= 4) g.sp = (g.sp + 1) & ~1;  // chunks of sixteen positions
+  // Two row tiles per wavefront (each H operand serves both), all rows in one workgroup, as many
+  // column blocks as keep the tiles of a wavefront and the LDS in bounds.
+  const int CT = (C + 15) / 16, rt = RT > 1 ? 2 : 1;
+  g.nrb = (CT + kChainCT - 1) / kChainCT;
   for (;; ++g.nrb) {
-    if (g.nrb > RT) return false;
-    g.rtb = (RT + g.nrb - 1) / g.nrb;
+    if (g.nrb > CT) return false;
+    g.ctb = (CT + g.nrb - 1) / g.nrb;
     if (chain_smem_bytes(p) <= kChainMaxLds) break;
   }
-  g.waves = (g.rtb + g.rt - 1) / g.rt;
-  g.key = chain_key(g.rt, g.ct, nq);
+  g.waves = (RT + rt - 1) / rt;
+  g.key = chain_key(rt, g.ctb, (nd + 3) / 4);
   g.lds = (int)(chain_smem_bytes(p) / sizeof(double));
   const int64_t nx = p.X.n, d1 = p.i[0].n;
   auto pad = [](int64_t v) { return (v + 31) / 32 * 32; };
@@ -679,18 +678,19 @@ bool chain_plan(Plan &p) {
   g.m4 = pad(nd * nd * rows * g.mr4 + 16 * g.mr4);
   g.m3 = pad(nd * nd * rows * g.mr3 + 16 * g.mr3);
   g.steps = pad((int64_t)nd * nx * nd * nd * (int64_t)(sizeof(ChainStep) / sizeof(double)));
-  // The steps hold 32-bit offsets into U3, M4 and M3.
-  if (p.tsize[2] > INT32_MAX || g.m4 > INT32_MAX || g.m3 > INT32_MAX) return false;
+  // The steps hold 32-bit offsets into U3, M4 and M3; those into M4 and M3 are used in bytes.
+  constexpr int64_t kMax = UINT32_MAX / 8;
+  if (p.tsize[2] > INT32_MAX || g.m4 > kMax || g.m3 > kMax) return false;
   p.chain = true;
   return true;
 }
 
 size_t chain_smem_bytes(const Plan &p) {
   const ChainGeom &g = p.ch;
-  const int R = p.i[4].n * p.i[3].n, C = p.i[2].n * p.i[1].n, SP = (g.smax + 1) / 2;
-  const int GW = std::min(R, g.rtb * 16);
+  const int R = p.i[4].n * p.i[3].n, C = p.i[2].n * p.i[1].n;
+  const int CW = std::min(C, g.ctb * 16);
   // The last row of G or H is read past its end by up to 31 columns (results never used).
-  return sizeof(double) * ((size_t)(p.nd * (g.n4t + g.n3t) + g.tpre + g.tpost) * g.ts + (size_t)SP * 8 * (GW + C) + 64);
+  return sizeof(double) * ((size_t)(p.nd * (g.n4t + g.n3t) + g.tpre + g.tpost) * g.ts + (size_t)g.sp * 8 * (R + CW) + 64);
 }
 
 hipError_t chain_init_attributes() {
@@ -713,14 +713,14 @@ void chain_params(const Plan &p, double *derived, RingParams &rp) {
   rp.n4t = g.n4t;
   rp.n3t = g.n3t;
   rp.ts = g.ts;
-  rp.smax = g.smax;
+  rp.sp = g.sp;
   rp.wm = g.wm;
   rp.tpre = g.tpre;
   rp.tpost = g.tpost;
   rp.lds = g.lds;
   rp.mr4 = g.mr4;
   rp.mr3 = g.mr3;
-  rp.rtb = g.rtb;
+  rp.ctb = g.ctb;
   rp.nrb = g.nrb;
   rp.nx = p.X.n;
   for (int q = 0; q < 2; ++q) {

@@ -24,12 +24,10 @@ enum Link { L12 = 0, L13, L14, L15, L23, L24, L25, L34, L35, L45 };
 struct ChainGeom {
   int n4t = 0, n3t = 0;   // k4 (k3) values per l45 (l23) of its derived tables
   int ts = 0;             // entries of a row of those tables (i5 or i2, padded)
-  int wm = 0, smax = 0;   // widest k4 or k3 window: positions, steps of four
+  int wm = 0, sp = 0;     // widest k4 or k3 window; eights of positions of G and H
   int tpre = 0, tpost = 0;  // zero rows before and after the T rows in LDS
-  int ct = 0;             // column tiles of A(i1)
-  int nrb = 1, rtb = 1;   // row blocks, row tiles per block
+  int nrb = 1, ctb = 1;   // column blocks, column tiles per block
   int waves = 1;          // wavefronts per workgroup
-  int rt = 1;             // row tiles per wavefront
   int lds = 0;            // LDS of a workgroup, in doubles
   int mr4 = 0, mr3 = 0;   // entries of a row of M4, M3
   int key = 0;            // kernel variant
@@ -135,12 +133,12 @@ struct RingParams {
   double *partial;        // [nchunk][i1][i2][i3][i4][i5]
   const int *bounds;      // [i1][nchunk + 1]: first core of each chunk of that i1
   int nchunk;
-  int nrb;                // row blocks of A(i1)
+  int nrb;                // row (x-outer kernel: column) blocks of A(i1)
   // x-outer kernel: derived tables and their shape (ChainGeom), own x count, own windows of k3
   // (0) and k4 (1), range of cores; bounds then holds units (l24, l25, x, l35).
   double *T5, *T2, *M4, *M3;
   ChainStep *steps;
-  int n4t, n3t, ts, wm, smax, tpre, tpost, rtb, nx, lds, mr4, mr3;
+  int n4t, n3t, ts, wm, sp, tpre, tpost, ctb, nx, lds, mr4, mr3;
   int wlo[2], whi[2];
   int core_lo, core_hi;
 };
@@ -176,8 +174,8 @@ size_t chain_smem_bytes(const Plan &p);
 hipError_t chain_init_attributes();
 void chain_params(const Plan &p, double *derived, RingParams &rp);
 hipError_t launch_chain_prep(const RingParams &rp, hipStream_t s);
-// items: (configuration, chunk, i1, row block) in device memory, or null for every item of
-// configuration 0; waves: wavefronts per workgroup (the largest rtb of the items).
+// items: (configuration, chunk, i1, column block) in device memory, or null for every item of
+// configuration 0; waves: wavefronts per workgroup.
 hipError_t launch_chain(const RingParams *cfgs_dev, const int *items_dev, int nitems, int key, int waves,
                         size_t smem, hipStream_t s);
 // Chunks of units (l24, l25, x, l35) of equal estimated cost for each i1, as ring_schedule does

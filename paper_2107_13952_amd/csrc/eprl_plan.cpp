@@ -317,7 +317,7 @@ int chain_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
     if (a4 > std::min(std::min(l24 + l34, l35 + x), w4hi) || a3 > std::min(std::min(l34 + l35, l24 + x), w3hi))
       return 0.0;
     const int s4 = (n4 + 3) / 4, s3 = (n3 + 3) / 4, nq = (n3 + 15) / 16;
-    return 30.0 + g.ct * s3 + nq * s4;
+    return 30.0 + g.ctb * s3 + nq * s4;
   };
   std::vector<double> unit((size_t)nd * nx * nd, 0.0);  // [o24][x][o35], every l34
   for (int o24 = 0; o24 < nd; ++o24)
@@ -513,7 +513,7 @@ void count_work(const Plan &p, double out[5]) {
                 // 16x16x4 matrix-core steps (2048 flops each) of P and the update; T and G / H run
                 // on the vector ALUs.
                 const int RT = (d5 * d4 + 15) / 16, q4 = (na4 + 3) / 4, q3 = (na3 + 3) / 4;
-                executed += 2048.0 * RT * ((p.ch.smax > 4 ? 2 : 1) * q4 + p.ch.ct * q3);
+                executed += 2048.0 * RT * p.ch.nrb * ((q3 + 3) / 4 * q4 + p.ch.ctb * q3);
               } else {
                 executed += 2.0 * rows * KW * 4 * s4 + 2.0 * rows * cols * 4 * s3;
               }
