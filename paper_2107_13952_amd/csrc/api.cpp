@@ -29,13 +29,11 @@ struct BatchEntry {
   std::vector<double> ccost;    // estimated cost of each (i1, chunk), in x iterations
 };
 
-// The launch sequence of a laid-out batch (host data): replayed from a captured graph, or
-// enqueued directly when per-kernel timing is on.
+// A laid-out batch (host data): everything that follows from the spins, shell counts and tuning, and
+// where the parameters that change from call to call (pointers) sit in the workspace.
 struct BatchSeq {
   std::vector<BatchEntry> ent;
   std::vector<RingParams> params;  // of the factorised configurations (BatchEntry::index)
-  std::vector<const double *> B;
-  std::vector<double *> A;
   int nring = 0, ncu = 256;
   // One launch per group of items [begin, end) of the work list, estimated cost (sum of item costs):
   // a variant and workgroup size of the x-outer kernel within a pass, one workgroup per item; or a
@@ -50,11 +48,20 @@ struct BatchSeq {
   };
   std::vector<Group> groups;
   int npass = 1;
-  size_t params_off = 0, items_off = 0, counters_off = 0;
+  // Launches over several configurations: [begin, end) of the job list, blocks.
+  struct Jobs {
+    int begin = 0, end = 0;
+    int64_t blocks = 0;
+  };
+  Jobs tables, reduce;
+  std::vector<Jobs> prep;  // per pass
+  // Workspace offsets: from dyn_off on RingParams, TableParams, ReduceParams, uploaded on each call;
+  // items, jobs and the plans' metadata with a new layout.
+  size_t items_off = 0, jobs_off = 0, counters_off = 0, dyn_off = 0, tables_off = 0, reduce_off = 0, dyn_end = 0;
 };
 
-// Streams beside the capture stream on which the batch's persistent launches run concurrently
-// inside the captured graph (all at the default priority).
+// Streams beside the context's on which a batch's groups run concurrently (all at the default
+// priority).
 constexpr int kBatchSide = 3;
 
 struct eprl_ctx {
@@ -94,7 +101,6 @@ struct eprl_ctx {
     hipEvent_t start, stop;
   };
   std::vector<Rec> recs;
-  bool capturing = false;
   // Schedule per tile class of the factorised path (set by eprl_autotune or eprl_set_tuning):
   // workgroup target of the cost schedule (0: default) and booster staging level (-1: the
   // most that fits).
@@ -108,14 +114,11 @@ struct eprl_ctx {
   // Plan of the last configuration asked for (host data only, keyed by spins and dl).
   std::vector<int> plan_key;
   Plan plan_last;
-  // Batched path: a dedicated workspace and the instantiated graph of the last batch.
+  // Batched path: a dedicated workspace and the layout of the last batch.
   struct Batch {
-    std::vector<int64_t> key;
+    std::vector<int64_t> key;  // empty: no layout
     char *ws = nullptr;
     size_t ws_size = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipStream_t cap = nullptr;  // private stream the graph is captured on (default priority)
     hipStream_t side[kBatchSide] = {};
     hipEvent_t fork = nullptr, join[kBatchSide] = {};
     BatchSeq seq;
@@ -163,7 +166,7 @@ struct TimedLaunch {
   int kernel;
   hipEvent_t start = nullptr, stop = nullptr;
   TimedLaunch(eprl_ctx *c_, int k) : c(c_), kernel(k) {
-    if (!c->timing || c->capturing) return;
+    if (!c->timing) return;
     if (hipEventCreate(&start) != hipSuccess || hipEventCreate(&stop) != hipSuccess) {
       (void)hipGetLastError();
       start = stop = nullptr;
@@ -244,23 +247,11 @@ int upload(eprl_ctx *c, void *dst, size_t bytes) {
   return EPRL_OK;
 }
 
-// Forgets the instantiated graph of the last batch (it holds device pointers of the context,
-// such as the factorial table, that are about to change).
-void drop_batch_graph(eprl_ctx *c) {
-  if (c->batch.exec) (void)hipGraphExecDestroy(c->batch.exec);
-  if (c->batch.graph) (void)hipGraphDestroy(c->batch.graph);
-  c->batch.exec = nullptr;
-  c->batch.graph = nullptr;
-  c->batch.key.clear();
-}
-
 int ensure_fexp(eprl_ctx *c, int fact_max) {
   if (fact_max <= c->fact_max) return EPRL_OK;
   fact_max = std::max(fact_max, 256);
   std::vector<int> pr = primes_upto(fact_max);
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  // A captured batch reads the table through its old address: it must be captured again.
-  drop_batch_graph(c);
   if (c->fexp) HIP_TRY(c, hipFree(c->fexp));
   if (c->primes) HIP_TRY(c, hipFree(c->primes));
   c->fexp = nullptr;
@@ -702,11 +693,12 @@ void booster_r_nodes(int n, const std::vector<double> (&gx)[2], const std::vecto
 // All configurations of a batch share one dedicated workspace laid out once per batch shape:
 // for each configuration its 6j tables, booster offsets and k ranges, and its per-chunk partial
 // sums; then the RingParams array and the work list of the persistent ring kernel.  The
-// device work (table builds, one persistent ring launch for every configuration the
-// factorised path handles, per-shell launches for the others, reductions) is captured once
-// into a hipGraph and replayed while the batch (spins, shell counts, pointers, algorithm)
-// stays the same.  Chunking per configuration equals the single-configuration path, so every
-// tensor is bitwise identical to a separate eprl_vertex_tensor call.
+// device work (one launch each for the 6j tables, the derived tables and the reductions of every
+// configuration, one per group of work items) is enqueued on each call; the layout is kept while the
+// shape of the batch (spins, shell counts, algorithm, tuning) stays the same, the pointers are uploaded
+// with each call.  (A captured graph held the pointers: a call with other buffers planned and captured
+// again, host work of 39 ms for 64 irregular configurations.)  Chunking per configuration equals the
+// single-configuration path, so every tensor is bitwise identical to a separate eprl_vertex_tensor call.
 
 
 // Most memory the derived tables of a batch's x-outer configurations take at a time.
@@ -747,43 +739,46 @@ TableParams table_params(const Plan &p, double *tables, const eprl_ctx *c) {
   return tp;
 }
 
-// Enqueues the device work of the laid-out batch on c->stream: the 6j tables of every
-// configuration, the work-queue counters (reset by a kernel, so that graph replays start from
-// 0), one persistent ring launch per tile class, per-shell launches for configurations the
-// factorised order does not handle, and the reductions.  Outside a capture each launch is
-// bracketed by the timing events when timing is on.
-hipError_t enqueue_batch(eprl_ctx *c) {
+// Enqueues the device work of the laid-out batch on c->stream: the 6j tables of every configuration
+// (one launch), the work-queue counters, per pass the derived tables (one launch) and one launch per
+// group, per-shell launches for configurations the factorised order does not handle, and the
+// reductions (one launch).
+hipError_t enqueue_batch(eprl_ctx *c, const double *const *B) {
   const BatchSeq &seq = c->batch.seq;
   char *ws = c->batch.ws;
   const int n = (int)seq.ent.size();
+  const RingParams *params = reinterpret_cast<const RingParams *>(ws + seq.dyn_off);
+  const BatchJob *jobs = reinterpret_cast<const BatchJob *>(ws + seq.jobs_off);
   hipError_t e = hipSuccess;
+  {
+    TimedLaunch tl(c, 0);
+    e = launch_ring_tables_batch(reinterpret_cast<const TableParams *>(ws + seq.tables_off), jobs + seq.tables.begin,
+                                 seq.tables.end - seq.tables.begin, seq.tables.blocks, c->stream);
+  }
   for (int q = 0; q < n && e == hipSuccess; ++q) {
     const BatchEntry &b = seq.ent[q];
-    if (b.towner != q) continue;  // reads another configuration's tables
-    TableParams tp = table_params(b.plan, reinterpret_cast<double *>(ws + b.tables), c);
+    if (b.ring) continue;
     TimedLaunch tl(c, 0);
-    e = b.ring ? launch_ring_tables(tp, b.plan.toff[5], c->stream)
-               : launch_sixj_tables(tp, b.plan.toff[5], c->stream);
+    e = launch_sixj_tables(table_params(b.plan, reinterpret_cast<double *>(ws + b.tables), c), b.plan.toff[5], c->stream);
   }
   int *counters = reinterpret_cast<int *>(ws + seq.counters_off);
   const int ngroup = (int)seq.groups.size();
-  if (e == hipSuccess && ngroup > 0) e = launch_reset_counters(counters, ngroup, c->stream);
-  const RingParams *params = reinterpret_cast<const RingParams *>(ws + seq.params_off);
+  bool queues = false;
+  for (const BatchSeq::Group &g : seq.groups) queues = queues || !g.chain;
+  if (e == hipSuccess && queues) e = launch_reset_counters(counters, ngroup, c->stream);
   hipStream_t main = c->stream;
   for (int pass = 0; pass < seq.npass && e == hipSuccess; ++pass) {
-    for (int q = 0; q < n && e == hipSuccess; ++q) {
-      const BatchEntry &b = seq.ent[q];
-      if (!b.ring || !b.plan.chain || b.pass != pass) continue;
+    {
+      const BatchSeq::Jobs &j = seq.prep[pass];
       TimedLaunch tl(c, 0);
-      e = launch_chain_prep(seq.params[b.index], c->stream);
+      e = launch_chain_prep_batch(params, jobs + j.begin, j.end - j.begin, j.blocks, c->stream);
     }
-    // Inside a capture the groups run on up to 1 + kBatchSide streams (graph branches), the
-    // costliest group first, each on the stream with the least work so far; outside a capture
-    // (timed launches) they run one after the other on the context's stream.
+    // The groups run on up to 1 + kBatchSide streams, the costliest group first, each on the stream
+    // with the least work so far; with per-kernel timing on, one after the other on the context's.
     std::vector<int> order;
     for (int g = 0; g < ngroup; ++g)
       if (seq.groups[g].pass == pass) order.push_back(g);
-    const int nstream = c->capturing ? std::min((int)order.size(), 1 + kBatchSide) : 1;
+    const int nstream = c->timing ? 1 : std::min((int)order.size(), 1 + kBatchSide);
     std::vector<hipStream_t> streams(std::max(nstream, 1), main);
     if (e == hipSuccess && nstream > 1) {
       e = hipEventRecord(c->batch.fork, main);
@@ -816,9 +811,10 @@ hipError_t enqueue_batch(eprl_ctx *c) {
       }
     }
     c->stream = main;
-    for (int q = 1; q < nstream && e == hipSuccess; ++q) {
-      e = hipEventRecord(c->batch.join[q - 1], streams[q]);
-      if (e == hipSuccess) e = hipStreamWaitEvent(main, c->batch.join[q - 1], 0);
+    for (int q = 1; q < nstream; ++q) {  // (joined after an error too: the caller may free its buffers)
+      hipError_t ej = hipEventRecord(c->batch.join[q - 1], c->batch.side[q - 1]);
+      if (ej == hipSuccess) ej = hipStreamWaitEvent(main, c->batch.join[q - 1], 0);
+      if (e == hipSuccess) e = ej;
     }
   }
   for (int q = 0; q < n && e == hipSuccess; ++q) {
@@ -829,7 +825,7 @@ hipError_t enqueue_batch(eprl_ctx *c) {
     prep.tables = reinterpret_cast<double *>(ws + b.tables);
     prep.boff = reinterpret_cast<int64_t *>(ws + b.boff);
     prep.kr = reinterpret_cast<int *>(ws + b.kr);
-    VertexParams vp = vertex_params(prep, seq.B[q]);
+    VertexParams vp = vertex_params(prep, B[q]);
     vp.partial = reinterpret_cast<double *>(ws + b.partial);
     vp.shell_begin = 0;
     vp.shell_end = b.plan.nshell;
@@ -838,25 +834,43 @@ hipError_t enqueue_batch(eprl_ctx *c) {
     TimedLaunch tl(c, 1);
     e = launch_assemble(vp, b.plan.D, c->stream);
   }
-  for (int q = 0; q < n && e == hipSuccess; ++q) {
-    const BatchEntry &b = seq.ent[q];
-    ReduceParams red = reduce_params(b.plan, reinterpret_cast<double *>(ws + b.partial), b.nchunk,
-                                     seq.A[q], 0);
+  if (e == hipSuccess) {
     TimedLaunch tl(c, 2);
-    e = launch_reduce(red, c->stream);
+    e = launch_reduce_batch(reinterpret_cast<const ReduceParams *>(ws + seq.reduce_off), jobs + seq.reduce.begin,
+                            seq.reduce.end - seq.reduce.begin, seq.reduce.blocks, c->stream);
   }
   return e;
 }
 
-// Runs the current batch: a replay of its graph, or, with per-kernel timing on, the same
-// launch sequence enqueued directly so that every launch can be timed.
-int run_batch(eprl_ctx *c) {
-  if (c->timing) {
-    hipError_t e = enqueue_batch(c);
-    if (e != hipSuccess) return hip_fail(c, e, "batched launch sequence");
-    return EPRL_OK;
+// Writes the parameters that change from call to call, and runs the laid-out batch.  st: pinned
+// staging whose first `head` bytes are uploaded to the workspace's start with them (0: none).
+int run_batch(eprl_ctx *c, const double *const *boosters, double *const *A, char *st, size_t head) {
+  BatchSeq &seq = c->batch.seq;
+  char *ws = c->batch.ws;
+  const int n = (int)seq.ent.size();
+  const size_t dyn = seq.dyn_end - seq.dyn_off;
+  if (!st) {
+    int rc = staging(c, dyn, &st);
+    if (rc) return rc;
   }
-  HIP_TRY(c, hipGraphLaunch(c->batch.exec, c->stream));
+  RingParams *rp = reinterpret_cast<RingParams *>(st + head);
+  TableParams *tp = reinterpret_cast<TableParams *>(st + head + (seq.tables_off - seq.dyn_off));
+  ReduceParams *red = reinterpret_cast<ReduceParams *>(st + head + (seq.reduce_off - seq.dyn_off));
+  for (int q = 0; q < n; ++q) {
+    const BatchEntry &b = seq.ent[q];
+    if (b.ring) {
+      rp[b.index] = seq.params[b.index];
+      rp[b.index].B = boosters[q];
+    }
+    tp[q] = table_params(b.plan, reinterpret_cast<double *>(ws + b.tables), c);
+    red[q] = reduce_params(b.plan, reinterpret_cast<double *>(ws + b.partial), b.nchunk, A[q], 0);
+  }
+  if (head) HIP_TRY(c, hipMemcpyAsync(ws, st, head, hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(ws + seq.dyn_off, st + head, dyn, hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipEventRecord(c->stage_done[c->stage_cur], c->stream));
+  c->stage_pending[c->stage_cur] = true;
+  hipError_t e = enqueue_batch(c, boosters);
+  if (e != hipSuccess) return hip_fail(c, e, "batched launch sequence");
   return EPRL_OK;
 }
 
@@ -878,11 +892,14 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
   for (int q = 0; q < n; ++q) {
     for (int t = 0; t < 10; ++t) key.push_back(two_j[10 * q + t]);
     key.push_back(dl[q]);
-    key.push_back((int64_t)(uintptr_t)boosters[q]);
-    key.push_back((int64_t)(uintptr_t)A[q]);
     if (!boosters[q] || !A[q]) return fail(c, EPRL_EINVAL, "null booster or output pointer");
   }
-  if (c->batch.exec && key == c->batch.key) return run_batch(c);
+  // The call uploads from host buffers that are used again: it cannot become part of a graph.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t ec = hipStreamIsCapturing(c->stream, &capture);
+  if (ec != hipSuccess) return hip_fail(c, ec, "hipStreamIsCapturing");
+  if (capture != hipStreamCaptureStatusNone) return hip_fail(c, hipErrorStreamCaptureUnsupported, "batched call");
+  if (!c->batch.key.empty() && key == c->batch.key) return run_batch(c, boosters, A, nullptr, 0);
   // New batch shape: plan every configuration and lay out the workspace.
   std::vector<BatchEntry> ent(n);
   size_t off = 0;
@@ -927,8 +944,6 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     off += align_up(p.kr.size() * sizeof(int), 256);
     b.sched = off;
     off += align_up(b.bounds.size() * sizeof(int), 256);
-    b.partial = off;
-    off += align_up((size_t)b.nchunk * p.a_size * sizeof(double), 256);
   }
   // 6j tables: a factorised configuration whose table index ranges (virtual spins, x, spin
   // offsets) lie inside those of another of the same spins reads that one's tables, the one with
@@ -947,20 +962,8 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     while (ent[t].towner != t) t = ent[t].towner;
     ent[q].towner = t;
   }
-  for (int q = 0; q < n; ++q)
-    if (ent[q].towner == q) {
-      ent[q].tables = off;
-      off += align_up((size_t)ent[q].plan.toff[5] * sizeof(double), 256);
-    }
-  for (int q = 0; q < n; ++q) ent[q].tables = ent[ent[q].towner].tables;
-  // Work lists of the persistent kernels, one per group: (configuration, chunk, i1, row block),
-  // longest first.
-  struct Item {
-    double cost;
-    int cfg, chunk, n1, rb;
-  };
-  // Derived tables of the x-outer kernel: as many configurations at a time (a pass) as keep them
-  // within kDerivedBytes; the passes run one after the other on the same memory.
+  // Passes: as many configurations at a time as keep their derived tables within kDerivedBytes; the
+  // passes run one after the other on the same memory (offsets from its start for now).
   size_t dmax = 0, dsum = 0;
   int npass = 1;
   for (int q = 0; q < n; ++q) {
@@ -971,11 +974,16 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
       dsum = 0;
     }
     ent[q].pass = npass - 1;
-    ent[q].derived = off + dsum;
+    ent[q].derived = dsum;
     dsum += need;
     dmax = std::max(dmax, dsum);
   }
-  off += dmax;
+  // Work lists of the kernels, one per group: (configuration, chunk, i1, row block),
+  // longest first.
+  struct Item {
+    double cost;
+    int cfg, chunk, n1, rb;
+  };
   // Groups of items that one launch can take.
   std::map<std::tuple<int, int, int, int>, std::vector<Item>> grouped;
   std::vector<int> ring_index(n, -1);
@@ -1020,18 +1028,73 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     g.end = (int)items.size();
     groups.push_back(g);
   }
-  const size_t params_off = off;
-  off += align_up((size_t)std::max(nring, 1) * sizeof(RingParams), 256);
+  // Launches over several configurations.
+  std::vector<BatchJob> jobs;
+  auto job_list = [&](auto &&blocks_of) {  // blocks_of(q, index): blocks of configuration q (0: none)
+    BatchSeq::Jobs j;
+    j.begin = (int)jobs.size();
+    for (int q = 0; q < n; ++q) {
+      int index = q;
+      const int64_t nb = blocks_of(q, index);
+      if (nb <= 0) continue;
+      jobs.push_back({(int)j.blocks, index});
+      j.blocks += nb;
+    }
+    j.end = (int)jobs.size();
+    return j;
+  };
+  const auto chain_blocks = [&](int q) {  // (the counts only)
+    RingParams rp;
+    rp.nd = ent[q].plan.nd;
+    chain_params(ent[q].plan, nullptr, rp);
+    return chain_prep_blocks(rp);
+  };
+  const BatchSeq::Jobs jtables = job_list([&](int q, int &) -> int64_t {
+    return ent[q].ring && ent[q].towner == q ? ring_table_blocks(ent[q].plan.toff[5]) : 0;
+  });
+  const BatchSeq::Jobs jreduce = job_list([&](int q, int &) -> int64_t { return reduce_blocks(ent[q].plan.a_size); });
+  std::vector<BatchSeq::Jobs> jprep;
+  for (int pass = 0; pass < npass; ++pass)
+    jprep.push_back(job_list([&](int q, int &index) -> int64_t {
+      index = ent[q].index;
+      return ent[q].ring && ent[q].plan.chain && ent[q].pass == pass ? chain_blocks(q) : 0;
+    }));
+  for (const BatchSeq::Jobs *j : {&jtables, &jreduce})
+    if (j->blocks > INT32_MAX) return fail(c, EPRL_ERANGE, "batch too large for one launch");
+  for (const BatchSeq::Jobs &j : jprep)
+    if (j.blocks > INT32_MAX) return fail(c, EPRL_ERANGE, "batch too large for one launch");
   const size_t items_off = off;
   off += align_up(std::max<size_t>(items.size(), 1) * 4 * sizeof(int), 256);
+  const size_t jobs_off = off;
+  off += align_up(std::max<size_t>(jobs.size(), 1) * sizeof(BatchJob), 256);
+  const size_t dyn_off = off;
+  off += align_up((size_t)std::max(nring, 1) * sizeof(RingParams), 256);
+  const size_t tables_off = off;
+  off += align_up((size_t)n * sizeof(TableParams), 256);
+  const size_t reduce_off = off;
+  off += align_up((size_t)n * sizeof(ReduceParams), 256);
+  const size_t dyn_end = off;
   const size_t counters_off = off;  // one work-queue counter per group
   off += align_up(std::max<size_t>(groups.size(), 1) * sizeof(int), 256);
+  for (int q = 0; q < n; ++q) {
+    ent[q].partial = off;
+    off += align_up((size_t)ent[q].nchunk * ent[q].plan.a_size * sizeof(double), 256);
+  }
+  for (int q = 0; q < n; ++q)
+    if (ent[q].towner == q) {
+      ent[q].tables = off;
+      off += align_up((size_t)ent[q].plan.toff[5] * sizeof(double), 256);
+    }
+  for (int q = 0; q < n; ++q) ent[q].tables = ent[ent[q].towner].tables;
+  for (int q = 0; q < n; ++q) ent[q].derived += off;
+  off += dmax;
   int rc = ensure_fexp(c, fact_max);
   if (rc) return rc;
-  // Drop the previous graph and workspace.
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  drop_batch_graph(c);
+  // The workspace is laid out anew (in stream order, after the previous batch); a larger one first
+  // waits for the work on the old one.
+  c->batch.key.clear();
   if (off > c->batch.ws_size) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (c->batch.ws) (void)hipFree(c->batch.ws);
     c->batch.ws = nullptr;
     c->batch.ws_size = 0;
@@ -1043,7 +1106,6 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     c->batch.ws_size = off;
   }
   char *ws = c->batch.ws;
-  // Metadata upload (outside the graph; the workspace belongs to this batch only).
   std::vector<RingParams> params(std::max(nring, 1));
   for (int q = 0; q < n; ++q) {
     if (!ent[q].ring) continue;
@@ -1072,7 +1134,6 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     rp.U3 = tab + tp.toff[2];
     rp.U4 = tab + tp.toff[3];
     rp.U5 = tab + tp.toff[4];
-    rp.B = boosters[q];
     rp.boff = reinterpret_cast<const int64_t *>(ws + ent[q].boff);
     rp.kr = reinterpret_cast<const int *>(ws + ent[q].kr);
     rp.partial = reinterpret_cast<double *>(ws + ent[q].partial);
@@ -1081,96 +1142,51 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     rp.nrb = ring_row_blocks(p);
     if (p.chain) chain_params(p, reinterpret_cast<double *>(ws + ent[q].derived), rp);
   }
-  // Compact staging of the metadata blocks: (workspace offset, bytes) in staging order.
-  std::vector<std::pair<size_t, size_t>> blocks;
-  size_t sbytes = 0;
-  for (int q = 0; q < n; ++q) {
-    blocks.push_back({ent[q].boff, ent[q].partial - ent[q].boff});  // boff and kr
-    sbytes += ent[q].partial - ent[q].boff;
-  }
-  blocks.push_back({params_off, off - params_off});                  // params and items
-  sbytes += off - params_off;
   char *st;
-  rc = staging(c, sbytes, &st);
+  rc = staging(c, dyn_end, &st);
   if (rc) return rc;
+  for (int q = 0; q < n; ++q) {
+    const Plan &p = ent[q].plan;
+    std::memcpy(st + ent[q].boff, p.boff.data(), p.boff.size() * sizeof(int64_t));
+    std::memcpy(st + ent[q].kr, p.kr.data(), p.kr.size() * sizeof(int));
+    if (!ent[q].bounds.empty())
+      std::memcpy(st + ent[q].sched, ent[q].bounds.data(), ent[q].bounds.size() * sizeof(int));
+  }
   {
-    size_t so = 0;
-    for (int q = 0; q < n; ++q) {
-      const Plan &p = ent[q].plan;
-      std::memcpy(st + so, p.boff.data(), p.boff.size() * sizeof(int64_t));
-      std::memcpy(st + so + (ent[q].kr - ent[q].boff), p.kr.data(), p.kr.size() * sizeof(int));
-      if (!ent[q].bounds.empty())
-        std::memcpy(st + so + (ent[q].sched - ent[q].boff), ent[q].bounds.data(),
-                    ent[q].bounds.size() * sizeof(int));
-      so += ent[q].partial - ent[q].boff;
-    }
-    std::memcpy(st + so, params.data(), params.size() * sizeof(RingParams));
-    std::vector<int> flat(std::max<size_t>(items.size(), 1) * 4, 0);
+    int *flat = reinterpret_cast<int *>(st + items_off);
     for (size_t k = 0; k < items.size(); ++k) {
       flat[4 * k] = items[k].cfg;
       flat[4 * k + 1] = items[k].chunk;
       flat[4 * k + 2] = items[k].n1;
       flat[4 * k + 3] = items[k].rb;
     }
-    std::memcpy(st + so + (items_off - params_off), flat.data(), flat.size() * sizeof(int));
-    so = 0;
-    for (auto &b : blocks) {
-      HIP_TRY(c, hipMemcpyAsync(ws + b.first, st + so, b.second, hipMemcpyHostToDevice, c->stream));
-      so += b.second;
-    }
   }
-  HIP_TRY(c, hipEventRecord(c->stage_done[c->stage_cur], c->stream));
-  c->stage_pending[c->stage_cur] = true;
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  std::memcpy(st + jobs_off, jobs.data(), jobs.size() * sizeof(BatchJob));
   BatchSeq &seq = c->batch.seq;
   seq.ent = std::move(ent);
-  seq.B.assign(boosters, boosters + n);
-  seq.A.assign(A, A + n);
   seq.params = std::move(params);
   seq.npass = npass;
   seq.nring = nring;
   seq.groups = std::move(groups);
-  seq.params_off = params_off;
+  seq.tables = jtables;
+  seq.reduce = jreduce;
+  seq.prep = std::move(jprep);
   seq.items_off = items_off;
+  seq.jobs_off = jobs_off;
+  seq.dyn_off = dyn_off;
+  seq.tables_off = tables_off;
+  seq.reduce_off = reduce_off;
+  seq.dyn_end = dyn_end;
   seq.counters_off = counters_off;
-  seq.ncu = 256;
-  (void)hipDeviceGetAttribute(&seq.ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  // Capture the device work on a private stream (the caller's stream may be the null stream,
-  // which cannot be captured); the graph is then launched on the caller's stream.
-  if (!c->batch.cap) HIP_TRY(c, hipStreamCreateWithFlags(&c->batch.cap, hipStreamNonBlocking));
+  seq.ncu = c->ncu;
   if (!c->batch.fork) HIP_TRY(c, hipEventCreateWithFlags(&c->batch.fork, hipEventDisableTiming));
   for (int q = 0; q < kBatchSide; ++q) {
     if (!c->batch.side[q]) HIP_TRY(c, hipStreamCreateWithFlags(&c->batch.side[q], hipStreamNonBlocking));
     if (!c->batch.join[q]) HIP_TRY(c, hipEventCreateWithFlags(&c->batch.join[q], hipEventDisableTiming));
   }
-  hipStream_t user = c->stream;
-  c->stream = c->batch.cap;
-  hipError_t eb = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
-  if (eb != hipSuccess) {
-    c->stream = user;
-    return hip_fail(c, eb, "hipStreamBeginCapture");
-  }
-  c->capturing = true;
-  hipError_t e = enqueue_batch(c);
-  hipGraph_t graph = nullptr;
-  hipError_t e2 = hipStreamEndCapture(c->stream, &graph);
-  c->capturing = false;
-  c->stream = user;
-  if (e != hipSuccess) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return hip_fail(c, e, "batched launch sequence");
-  }
-  if (e2 != hipSuccess) return hip_fail(c, e2, "hipStreamEndCapture");
-  hipGraphExec_t exec = nullptr;
-  e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(graph);
-    return hip_fail(c, e, "hipGraphInstantiate");
-  }
-  c->batch.graph = graph;
-  c->batch.exec = exec;
-  c->batch.key = key;
-  return run_batch(c);
+  rc = run_batch(c, boosters, A, st, dyn_off);
+  if (rc == EPRL_OK) c->batch.key = std::move(key);
+  return rc;
 }
 
 }  // namespace
@@ -1215,10 +1231,7 @@ void eprl_destroy(eprl_ctx *c) {
   if (c->handoff) (void)hipEventDestroy(c->handoff);
   if (c->fexp) (void)hipFree(c->fexp);
   if (c->primes) (void)hipFree(c->primes);
-  if (c->batch.exec) (void)hipGraphExecDestroy(c->batch.exec);
-  if (c->batch.graph) (void)hipGraphDestroy(c->batch.graph);
   if (c->batch.ws) (void)hipFree(c->batch.ws);
-  if (c->batch.cap) (void)hipStreamDestroy(c->batch.cap);
   for (int q = 0; q < kBatchSide; ++q) {
     if (c->batch.side[q]) (void)hipStreamDestroy(c->batch.side[q]);
     if (c->batch.join[q]) (void)hipEventDestroy(c->batch.join[q]);

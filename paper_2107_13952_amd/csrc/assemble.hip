@@ -256,10 +256,10 @@ __global__ __launch_bounds__(NT) void assemble_kernel(VertexParams vp) {
 // chunks in chunk order, then the RW run sums are added in run order: a fixed order for a given
 // chunk count, with enough loads in flight to stream the partials at HBM rate.
 constexpr int RW = 16;
-__global__ __launch_bounds__(64 * RW) void reduce_kernel(ReduceParams rp) {
+__device__ __forceinline__ void reduce_block(const ReduceParams &rp, int block) {
   __shared__ double run[RW][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t idx = (int64_t)block * 64 + lane;
   const bool in = idx < rp.a_size;
   const int c0 = (int)((int64_t)rp.nchunk * w / RW), c1 = (int)((int64_t)rp.nchunk * (w + 1) / RW);
   double s = 0.0;
@@ -290,6 +290,16 @@ __global__ __launch_bounds__(64 * RW) void reduce_kernel(ReduceParams rp) {
   }
   const double v = t * norm;
   rp.A[idx] = rp.accumulate ? rp.A[idx] + v : v;
+}
+
+__global__ __launch_bounds__(64 * RW) void reduce_kernel(ReduceParams rp) { reduce_block(rp, blockIdx.x); }
+
+// Several tensors in one launch.
+__global__ __launch_bounds__(64 * RW) void reduce_batch_kernel(const ReduceParams *__restrict__ rps,
+                                                               const BatchJob *__restrict__ jobs, int njobs) {
+  int b = blockIdx.x;
+  const ReduceParams rp = rps[batch_job(jobs, njobs, b)];
+  reduce_block(rp, b);
 }
 
 template <int D>
@@ -379,8 +389,15 @@ hipError_t launch_assemble(const VertexParams &vp, int D, hipStream_t s) {
 }
 
 hipError_t launch_reduce(const ReduceParams &rp, hipStream_t s) {
-  const int64_t blocks = (rp.a_size + 63) / 64;
-  reduce_kernel<<<(unsigned)blocks, 64 * RW, 0, s>>>(rp);
+  reduce_kernel<<<(unsigned)reduce_blocks(rp.a_size), 64 * RW, 0, s>>>(rp);
+  return hipGetLastError();
+}
+
+int64_t reduce_blocks(int64_t a_size) { return (a_size + 63) / 64; }
+
+hipError_t launch_reduce_batch(const ReduceParams *rps, const BatchJob *jobs, int njobs, int64_t blocks, hipStream_t s) {
+  if (njobs <= 0) return hipSuccess;
+  reduce_batch_kernel<<<(unsigned)blocks, 64 * RW, 0, s>>>(rps, jobs, njobs);
   return hipGetLastError();
 }
 

@@ -101,12 +101,12 @@ constexpr int kPrepThreads = 256;
 // (x over the configuration's own range; entries outside a booster block or a triad are zeros; the
 // (x, i1) that do not close (i1 l25 x) are not written).  One block per T5 (o25, x, o35), per T2
 // (o24, o25, x), then the boosters.
-__global__ __launch_bounds__(kPrepThreads) void chain_prep_kernel(RingParams rp, int nb5, int nb2, int nbs) {
+__device__ __forceinline__ void chain_prep_block(const RingParams &rp, int b) {
   const int nd = rp.nd, nd3 = nd * nd * nd, nx = rp.nx, d1 = rp.i_n[0];
+  const int nb5 = nd * nx * nd, nb2 = nd * nd * nx, nbs = (nd * nx * nd + kPrepThreads - 1) / kPrepThreads;
   const int *J = rp.two_j;
   const int NX = rp.NX, nK2 = rp.K_n[0], nK3 = rp.K_n[1], nK4 = rp.K_n[2], nK5 = rp.K_n[3];
   const int S = rp.ts;
-  int b = blockIdx.x;
   if (b < nb5 + nb2) {
     const bool five = b < nb5;
     if (!five) b -= nb5;
@@ -242,6 +242,16 @@ __global__ __launch_bounds__(kPrepThreads) void chain_prep_kernel(RingParams rp,
     if (k >= klb && kk < kn) v = rp.B[rp.boff[e * nd3 + t] + (int64_t)i * kn + kk] * (double)(k + 1);
   }
   *out = v;
+}
+
+__global__ __launch_bounds__(kPrepThreads) void chain_prep_kernel(RingParams rp) { chain_prep_block(rp, blockIdx.x); }
+
+// The derived tables of several configurations in one launch.
+__global__ __launch_bounds__(kPrepThreads) void chain_prep_batch_kernel(const RingParams *__restrict__ cfgs,
+                                                                        const BatchJob *__restrict__ jobs, int njobs) {
+  int b = blockIdx.x;
+  const RingParams &rp = cfgs[batch_job(jobs, njobs, b)];
+  chain_prep_block(rp, b);
 }
 
 typedef int i8v __attribute__((ext_vector_type(8)));
@@ -731,12 +741,21 @@ void chain_params(const Plan &p, double *derived, RingParams &rp) {
   rp.core_hi = p.nd * p.nd * p.nd * p.nd;
 }
 
+int64_t chain_prep_blocks(const RingParams &rp) {
+  const int64_t nd = rp.nd, m = nd * nd * (rp.wm + 3) * (rp.mr4 + rp.mr3);
+  return nd * rp.nx * nd + nd * nd * rp.nx + (nd * rp.nx * nd + kPrepThreads - 1) / kPrepThreads +
+         (m + kPrepThreads - 1) / kPrepThreads;
+}
+
 hipError_t launch_chain_prep(const RingParams &rp, hipStream_t s) {
-  const int nd = rp.nd, nb5 = nd * rp.nx * nd, nb2 = nd * nd * rp.nx;
-  const int64_t m = (int64_t)nd * nd * (rp.wm + 3) * (rp.mr4 + rp.mr3);
-  const int nbs = (nd * rp.nx * nd + kPrepThreads - 1) / kPrepThreads;
-  const int64_t blocks = nb5 + nb2 + nbs + (m + kPrepThreads - 1) / kPrepThreads;
-  chain_prep_kernel<<<(unsigned)blocks, kPrepThreads, 0, s>>>(rp, nb5, nb2, nbs);
+  chain_prep_kernel<<<(unsigned)chain_prep_blocks(rp), kPrepThreads, 0, s>>>(rp);
+  return hipGetLastError();
+}
+
+hipError_t launch_chain_prep_batch(const RingParams *cfgs, const BatchJob *jobs, int njobs, int64_t blocks,
+                                   hipStream_t s) {
+  if (njobs <= 0) return hipSuccess;
+  chain_prep_batch_kernel<<<(unsigned)blocks, kPrepThreads, 0, s>>>(cfgs, jobs, njobs);
   return hipGetLastError();
 }
 

@@ -143,6 +143,26 @@ struct RingParams {
   int core_lo, core_hi;
 };
 
+// One launch over several configurations: job q has the blocks from jobs[q].first to the next job's
+// first, and works on entry jobs[q].index of the launch's parameter array.
+struct BatchJob {
+  int first, index;
+};
+
+#ifdef __HIPCC__
+// The job of block b (the last whose first block is not past it); b becomes the block within the job.
+__device__ __forceinline__ int batch_job(const BatchJob *jobs, int njobs, int &b) {
+  int lo = 0, hi = njobs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (jobs[mid].first <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  b -= jobs[lo].first;
+  return __builtin_amdgcn_readfirstlane(jobs[lo].index);
+}
+#endif
+
 struct ReduceParams {
   const double *partial;
   int nchunk;
@@ -157,10 +177,16 @@ hipError_t launch_fexp_table(uint16_t *fexp, int fact_max, const int *primes, in
                              hipStream_t s);
 hipError_t launch_sixj_tables(const TableParams &tp, int64_t total, hipStream_t s);
 hipError_t launch_ring_tables(const TableParams &tp, int64_t total, hipStream_t s);
+int64_t ring_table_blocks(int64_t total);
+hipError_t launch_ring_tables_batch(const TableParams *tps_dev, const BatchJob *jobs_dev, int njobs, int64_t blocks,
+                                    hipStream_t s);
 hipError_t launch_sixj_batch(const int *args, int n, double *out, const uint16_t *fexp,
                              const int *primes, int nprime, int fact_max, hipStream_t s);
 hipError_t launch_assemble(const VertexParams &vp, int D, hipStream_t s);
 hipError_t launch_reduce(const ReduceParams &rp, hipStream_t s);
+int64_t reduce_blocks(int64_t a_size);
+hipError_t launch_reduce_batch(const ReduceParams *rps_dev, const BatchJob *jobs_dev, int njobs, int64_t blocks,
+                               hipStream_t s);
 int ring_class(int DI, int DK, int KW);
 // Tile classes: 0..7 by the padded tiles of ring.hip's kernels, kWideClass a boundary dimension
 // above 8 in the x-outer kernel of chain.hip (which also runs classes 0..3).
@@ -174,6 +200,9 @@ size_t chain_smem_bytes(const Plan &p);
 hipError_t chain_init_attributes();
 void chain_params(const Plan &p, double *derived, RingParams &rp);
 hipError_t launch_chain_prep(const RingParams &rp, hipStream_t s);
+int64_t chain_prep_blocks(const RingParams &rp);
+hipError_t launch_chain_prep_batch(const RingParams *cfgs_dev, const BatchJob *jobs_dev, int njobs, int64_t blocks,
+                                   hipStream_t s);
 // items: (configuration, chunk, i1, column block) in device memory, or null for every item of
 // configuration 0; waves: wavefronts per workgroup.
 hipError_t launch_chain(const RingParams *cfgs_dev, const int *items_dev, int nitems, int key, int waves,

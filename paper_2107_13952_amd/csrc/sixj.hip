@@ -365,9 +365,8 @@ __global__ void sixj_table_kernel(TableParams tp, int64_t total) {
 //   U4[o23][o24][x][k3][k2] = (-1)^{r2} {l24 k3 x; j13 k2 l23}
 //   U5[o25][x][k2][i1]  = {k2 j13 x; i1 l25 j12}
 // so that W(i1, k2..k5) = sum_x U1 U2 U3 U4 U5 exactly.
-__global__ void ring_table_kernel(TableParams tp, int64_t total) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= total) return;
+__device__ __forceinline__ void ring_table_entry(const TableParams &tp, int64_t g) {
+  if (g >= tp.toff[5]) return;
   int t = 0;
   while (t < 4 && g >= tp.toff[t + 1]) ++t;
   int64_t idx = g - tp.toff[t];
@@ -433,6 +432,18 @@ __global__ void ring_table_kernel(TableParams tp, int64_t total) {
   tp.tables[g] = (ph & 1) ? -v : v;
 }
 
+__global__ __launch_bounds__(256) void ring_table_kernel(TableParams tp) {
+  ring_table_entry(tp, (int64_t)blockIdx.x * 256 + threadIdx.x);
+}
+
+// The tables of several configurations in one launch.
+__global__ __launch_bounds__(256) void ring_table_batch_kernel(const TableParams *__restrict__ tps,
+                                                               const BatchJob *__restrict__ jobs, int njobs) {
+  int b = blockIdx.x;
+  const TableParams &tp = tps[batch_job(jobs, njobs, b)];
+  ring_table_entry(tp, (int64_t)b * 256 + threadIdx.x);
+}
+
 __global__ void sixj_batch_kernel(const int *args, int n, double *out, const uint16_t *fexp,
                                   const int *primes, int nprime, int fact_max) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -464,8 +475,16 @@ hipError_t launch_sixj_tables(const TableParams &tp, int64_t total, hipStream_t 
 }
 
 hipError_t launch_ring_tables(const TableParams &tp, int64_t total, hipStream_t s) {
-  int64_t blocks = (total + 255) / 256;
-  ring_table_kernel<<<(unsigned)blocks, 256, 0, s>>>(tp, total);
+  ring_table_kernel<<<(unsigned)ring_table_blocks(total), 256, 0, s>>>(tp);
+  return hipGetLastError();
+}
+
+int64_t ring_table_blocks(int64_t total) { return (total + 255) / 256; }
+
+hipError_t launch_ring_tables_batch(const TableParams *tps, const BatchJob *jobs, int njobs, int64_t blocks,
+                                    hipStream_t s) {
+  if (njobs <= 0) return hipSuccess;
+  ring_table_batch_kernel<<<(unsigned)blocks, 256, 0, s>>>(tps, jobs, njobs);
   return hipGetLastError();
 }
 

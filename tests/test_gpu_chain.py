@@ -72,3 +72,26 @@ def test_tile_edges(lib, torch, two_j, dl, cores, dims):
     scale = np.abs(ref).max()
     assert scale > 0
     assert np.abs(a.cpu().numpy() - ref).max() <= TOL * scale
+
+
+# A layout kept from call to call must follow the buffers of each call: two batches of one shape
+# (factorised configurations of both kinds of tables and a per-shell one), called in turn with other
+# boosters and outputs, on the default and on a side stream, equal the plain calls bit by bit.
+@pytest.mark.parametrize("shape", [[([2] * 10, 2), ([4, 4, 5, 3, 5, 5, 6, 4, 3, 6], 1), ([1] * 10, 16)],
+                                   [([3, 2, 3, 2, 4, 3, 4, 3, 3, 3], 3), ([2] * 10, 2)]])
+def test_batch_follows_its_buffers(lib, torch, shape):
+    sets = [[torch.from_numpy(workloads.synthetic_boosters(500 + 10 * k + q, R.block_shapes(j, d))).cuda()
+             for q, (j, d) in enumerate(shape)] for k in range(3)]
+    plain = [[lib.vertex_tensor(j, d, 1.2, b) for (j, d), b in zip(shape, s)] for s in sets]
+    side = torch.cuda.Stream()
+    for k in (0, 1, 2, 1, 0):
+        print("batch buffers", k, flush=True)
+        if k == 2:
+            side.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(side):
+                out = lib.vertex_tensor_batched(shape, 1.2, sets[k])
+            torch.cuda.current_stream().wait_stream(side)
+        else:
+            out = lib.vertex_tensor_batched(shape, 1.2, sets[k])
+        for a, p in zip(out, plain[k]):
+            assert torch.equal(a, p)
