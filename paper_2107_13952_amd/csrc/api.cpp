@@ -88,10 +88,9 @@ struct eprl_ctx {
   // work enqueued earlier still uses the workspace that later calls reuse.
   hipEvent_t handoff = nullptr;
   // factorial prime-exponent table (device), valid for arguments <= fact_max
-  uint16_t *fexp = nullptr;
-  int *primes = nullptr;
+  double4 *fact = nullptr;  // factorial table, its exponents behind it
   int fact_max = -1;
-  int nprime = 0;
+  FactTables ft;
   // algorithm: EPRL_ALGO_AUTO, EPRL_ALGO_SHELL or EPRL_ALGO_RING
   int algo = 0;
   // optional per-kernel timing
@@ -247,30 +246,23 @@ int upload(eprl_ctx *c, void *dst, size_t bytes) {
   return EPRL_OK;
 }
 
-int ensure_fexp(eprl_ctx *c, int fact_max) {
+int ensure_fact(eprl_ctx *c, int fact_max) {
   if (fact_max <= c->fact_max) return EPRL_OK;
   fact_max = std::max(fact_max, 256);
-  std::vector<int> pr = primes_upto(fact_max);
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  if (c->fexp) HIP_TRY(c, hipFree(c->fexp));
-  if (c->primes) HIP_TRY(c, hipFree(c->primes));
-  c->fexp = nullptr;
-  c->primes = nullptr;
+  if (c->fact) HIP_TRY(c, hipFree(c->fact));
+  c->fact = nullptr;
   c->fact_max = -1;
-  if (hipMalloc(&c->primes, pr.size() * sizeof(int)) != hipSuccess ||
-      hipMalloc(&c->fexp, (size_t)(fact_max + 1) * pr.size() * sizeof(uint16_t)) != hipSuccess) {
+  if (hipMalloc(&c->fact, (size_t)(fact_max + 1) * (sizeof(double4) + sizeof(int))) != hipSuccess) {
     (void)hipGetLastError();
+    c->fact = nullptr;
     return fail(c, EPRL_ENOMEM, "factorial table allocation failed");
   }
-  char *st;
-  int rc = staging(c, pr.size() * sizeof(int), &st);
-  if (rc) return rc;
-  std::memcpy(st, pr.data(), pr.size() * sizeof(int));
-  rc = upload(c, c->primes, pr.size() * sizeof(int));
-  if (rc) return rc;
-  HIP_TRY(c, launch_fexp_table(c->fexp, fact_max, c->primes, (int)pr.size(), c->stream));
+  int *exps = reinterpret_cast<int *>(c->fact + fact_max + 1);
+  HIP_TRY(c, launch_fact_table(c->fact, exps, fact_max, c->stream));
+  c->ft.f = c->fact;
+  c->ft.e = exps;
   c->fact_max = fact_max;
-  c->nprime = (int)pr.size();
   return EPRL_OK;
 }
 
@@ -322,7 +314,7 @@ int prepare(eprl_ctx *c, const int two_j[10], int dl, size_t extra, Prepared &pr
   Plan &p = prep.plan;
   if (!any_dims && (p.D == 0 || p.kmax > 16))
     return fail(c, EPRL_ERANGE, "intertwiner dimensions above 16 are not supported");
-  rc = ensure_fexp(c, p.fact_max);
+  rc = ensure_fact(c, p.fact_max);
   if (rc) return rc;
   const size_t tbytes = align_up((size_t)p.toff[5] * sizeof(double), 256);
   const size_t bbytes = align_up(p.boff.size() * sizeof(int64_t), 256);
@@ -357,13 +349,11 @@ int prepare(eprl_ctx *c, const int two_j[10], int dl, size_t extra, Prepared &pr
   tp.NX = p.X.n;
   for (int t = 0; t < 6; ++t) tp.toff[t] = p.toff[t];
   tp.tables = prep.tables;
-  tp.fexp = c->fexp;
-  tp.primes = c->primes;
-  tp.nprime = c->nprime;
+  tp.fact = c->ft;
   {
     TimedLaunch tl(c, 0);
     if (ring_tables)
-      HIP_TRY(c, launch_ring_tables(tp, p.toff[5], c->stream));
+      HIP_TRY(c, launch_ring_tables(tp, c->stream));
     else
       HIP_TRY(c, launch_sixj_tables(tp, p.toff[5], c->stream));
   }
@@ -733,9 +723,7 @@ TableParams table_params(const Plan &p, double *tables, const eprl_ctx *c) {
   tp.NX = p.X.n;
   for (int t = 0; t < 6; ++t) tp.toff[t] = p.toff[t];
   tp.tables = tables;
-  tp.fexp = c->fexp;
-  tp.primes = c->primes;
-  tp.nprime = c->nprime;
+  tp.fact = c->ft;
   return tp;
 }
 
@@ -1050,7 +1038,7 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     return chain_prep_blocks(rp);
   };
   const BatchSeq::Jobs jtables = job_list([&](int q, int &) -> int64_t {
-    return ent[q].ring && ent[q].towner == q ? ring_table_blocks(ent[q].plan.toff[5]) : 0;
+    return ent[q].ring && ent[q].towner == q ? ring_table_blocks(ent[q].plan.nd, ent[q].plan.X.n) : 0;
   });
   const BatchSeq::Jobs jreduce = job_list([&](int q, int &) -> int64_t { return reduce_blocks(ent[q].plan.a_size); });
   std::vector<BatchSeq::Jobs> jprep;
@@ -1088,7 +1076,7 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
   for (int q = 0; q < n; ++q) ent[q].tables = ent[ent[q].towner].tables;
   for (int q = 0; q < n; ++q) ent[q].derived += off;
   off += dmax;
-  int rc = ensure_fexp(c, fact_max);
+  int rc = ensure_fact(c, fact_max);
   if (rc) return rc;
   // The workspace is laid out anew (in stream order, after the previous batch); a larger one first
   // waits for the work on the old one.
@@ -1229,8 +1217,7 @@ void eprl_destroy(eprl_ctx *c) {
     if (c->stage_done[k]) (void)hipEventDestroy(c->stage_done[k]);
   }
   if (c->handoff) (void)hipEventDestroy(c->handoff);
-  if (c->fexp) (void)hipFree(c->fexp);
-  if (c->primes) (void)hipFree(c->primes);
+  if (c->fact) (void)hipFree(c->fact);
   if (c->batch.ws) (void)hipFree(c->batch.ws);
   for (int q = 0; q < kBatchSide; ++q) {
     if (c->batch.side[q]) (void)hipStreamDestroy(c->batch.side[q]);
@@ -1640,7 +1627,7 @@ int eprl_threejm_batch(eprl_ctx *c, int n, const int *args, double *out) {
         return fail(c, EPRL_ERANGE, "3jm argument outside |two_j| <= 200");
       if (a < 3) big = std::max(big, v);
     }
-  int rc = ensure_fexp(c, 2 * big + 2);
+  int rc = ensure_fact(c, 2 * big + 2);
   if (rc) return rc;
   const size_t bytes = (size_t)n * 6 * sizeof(int);
   rc = ensure_workspace(c, bytes);
@@ -1651,8 +1638,7 @@ int eprl_threejm_batch(eprl_ctx *c, int n, const int *args, double *out) {
   std::memcpy(st, args, bytes);
   rc = upload(c, c->ws, bytes);
   if (rc) return rc;
-  HIP_TRY(c, launch_threejm_batch(reinterpret_cast<int *>(c->ws), n, out, c->fexp, c->primes,
-                                  c->nprime, c->fact_max, c->stream));
+  HIP_TRY(c, launch_threejm_batch(reinterpret_cast<int *>(c->ws), n, out, c->ft, c->fact_max, c->stream));
   return EPRL_OK;
 }
 
@@ -1774,7 +1760,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     fact = std::max(fact, std::max(b.lb[0] + b.lb[1], b.lb[2] + b.lb[3]) + kmax);
   }
   if (fact / 2 + 2 > 2 * kSixjMaxTwo + 2) return fail(c, EPRL_ERANGE, "spins beyond the 3jm range");
-  rc = ensure_fexp(c, fact / 2 + 2);
+  rc = ensure_fact(c, fact / 2 + 2);
   if (rc) return rc;
   const int ns = 256;
   std::vector<double> sx, sw, gx[2], gw[2];
@@ -1832,8 +1818,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
       if (rc) return rc;
       HIP_TRY(c, launch_fourjm_tables(reinterpret_cast<const FourjmSet *>(ws + o_sets), (int)sets.size(),
                                       max_entries, reinterpret_cast<const int *>(ws + o_mt),
-                                      reinterpret_cast<double *>(ws + o_coef), c->fexp, c->primes,
-                                      c->nprime, c->stream));
+                                      reinterpret_cast<double *>(ws + o_coef), c->ft, c->stream));
       ws_seen = ws;
     }
     {
@@ -1898,7 +1883,7 @@ int eprl_sixj_batch(eprl_ctx *c, int n, const int *args, double *out) {
       return fail(c, EPRL_ERANGE, "6j argument outside 0..200 (two_j)");
     big = std::max(big, args[q]);
   }
-  int rc = ensure_fexp(c, 2 * big + 2);
+  int rc = ensure_fact(c, 2 * big + 2);
   if (rc) return rc;
   const size_t bytes = (size_t)n * 6 * sizeof(int);
   rc = ensure_workspace(c, bytes);
@@ -1909,8 +1894,7 @@ int eprl_sixj_batch(eprl_ctx *c, int n, const int *args, double *out) {
   std::memcpy(st, args, bytes);
   rc = upload(c, c->ws, bytes);
   if (rc) return rc;
-  HIP_TRY(c, launch_sixj_batch(reinterpret_cast<int *>(c->ws), n, out, c->fexp, c->primes,
-                               c->nprime, c->fact_max, c->stream));
+  HIP_TRY(c, launch_sixj_batch(reinterpret_cast<int *>(c->ws), n, out, c->ft, c->fact_max, c->stream));
   return EPRL_OK;
 }
 

@@ -75,10 +75,14 @@ int make_plan(const int two_j[10], int dl, Plan &p, std::string &err);
 void count_terms(const Plan &p, int64_t &live, double &terms);
 // Exact work counts: terms, per-shell-order flops, factorised-order useful and executed flops.
 void count_work(const Plan &p, double out[5]);
-// Primes up to n.
-std::vector<int> primes_upto(int n);
 
 // ---- kernel-side parameter blocks (passed by value) ----
+
+// sqrt(n!) and its inverse, n <= fact_max: (f.x + f.y) 2^e and (f.z + f.w) 2^-e.
+struct FactTables {
+  const double4 *f = nullptr;
+  const int *e = nullptr;
+};
 
 struct TableParams {
   int two_j[10];
@@ -88,9 +92,7 @@ struct TableParams {
   int X_lo2, NX;
   int64_t toff[6];
   double *tables;
-  const uint16_t *fexp;  // [fact_max + 1][nprime]
-  const int *primes;
-  int nprime;
+  FactTables fact;
 };
 
 struct VertexParams {
@@ -173,15 +175,13 @@ struct ReduceParams {
 };
 
 // Kernel launchers (defined in the .hip files).  They return hipSuccess or the launch error.
-hipError_t launch_fexp_table(uint16_t *fexp, int fact_max, const int *primes, int nprime,
-                             hipStream_t s);
+hipError_t launch_fact_table(double4 *f, int *e, int fact_max, hipStream_t s);
 hipError_t launch_sixj_tables(const TableParams &tp, int64_t total, hipStream_t s);
-hipError_t launch_ring_tables(const TableParams &tp, int64_t total, hipStream_t s);
-int64_t ring_table_blocks(int64_t total);
+hipError_t launch_ring_tables(const TableParams &tp, hipStream_t s);
+int64_t ring_table_blocks(int64_t nd, int64_t nx);
 hipError_t launch_ring_tables_batch(const TableParams *tps_dev, const BatchJob *jobs_dev, int njobs, int64_t blocks,
                                     hipStream_t s);
-hipError_t launch_sixj_batch(const int *args, int n, double *out, const uint16_t *fexp,
-                             const int *primes, int nprime, int fact_max, hipStream_t s);
+hipError_t launch_sixj_batch(const int *args, int n, double *out, FactTables fact, int fact_max, hipStream_t s);
 hipError_t launch_assemble(const VertexParams &vp, int D, hipStream_t s);
 hipError_t launch_reduce(const ReduceParams &rp, hipStream_t s);
 int64_t reduce_blocks(int64_t a_size);
@@ -274,10 +274,8 @@ struct FourjmSet {
   int64_t out;
 };
 hipError_t launch_fourjm_tables(const FourjmSet *sets_dev, int nsets, int max_entries,
-                                const int *mtuples_dev, double *out, const uint16_t *fexp,
-                                const int *primes, int nprime, hipStream_t s);
-hipError_t launch_threejm_batch(const int *args, int n, double *out, const uint16_t *fexp,
-                                const int *primes, int nprime, int fact_max, hipStream_t s);
+                                const int *mtuples_dev, double *out, FactTables fact, hipStream_t s);
+hipError_t launch_threejm_batch(const int *args, int n, double *out, FactTables fact, int fact_max, hipStream_t s);
 // A boost matrix element d^{(rho, k = j)}_{j l m}(r): spins, the Y-map rho = gamma (j + 1), the
 // phase factor of the basis convention, and the Jacobi-form constants of the two SU(2) d
 // functions it integrates, d^j_{j m} and d^l_{j m}.

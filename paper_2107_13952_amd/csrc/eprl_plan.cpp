@@ -40,17 +40,6 @@ int min_gap(Range ra, int b) {
 
 }  // namespace
 
-std::vector<int> primes_upto(int n) {
-  std::vector<char> sieve(std::max(n + 1, 2), 1);
-  std::vector<int> out;
-  for (int q = 2; q <= n; ++q) {
-    if (!sieve[q]) continue;
-    out.push_back(q);
-    for (int m = 2 * q; m <= n; m += q) sieve[m] = 0;
-  }
-  return out;
-}
-
 int make_plan(const int two_j[10], int dl, Plan &p, std::string &err) {
   std::ostringstream msg;
   if (!two_j) {

@@ -7,10 +7,11 @@
 //   P = prod over the four triads (x y z) of (x+y-z)! (x-y+z)! (-x+y+z)! / (x+y+z+1)!.
 //
 // Evaluation, designed so that the result is within a few ulp of the exact value:
-//  * The common factor sqrt(P) * T0 (T0 = |first term|) is an exact rational square root.
-//    Its prime factorisation is assembled from a table of prime exponents of n! (Legendre's
-//    formula), and the product prod_p sqrt(p)^{E_p} is formed in double-double arithmetic
-//    with a separate binary exponent, so no factorial is ever rounded.
+//  * The common factor sqrt(P) * T0 (T0 = |first term|) is a product of sqrt(n!) and 1 / sqrt(n!),
+//    squared for T0, from a table of both in double-double with a separate binary exponent.  The
+//    table's error grows by 2^-104 per factor of n!, so 24 factors of n <= 400 stay within 2^-90.
+//    (Assembling the factor from prime exponents took a loop over all primes, 23 exponent
+//    reads and a power for each: 224 us for the tables at two_j = 6, 8 shells, now 50 us with the slices of ring_table_slice.)
 //  * The remaining sum is 1 + r_0 + r_0 r_1 + ... with exact integer ratios
 //    r_t = -(t+2) prod_j (beta_j - t) / prod_i (t + 1 - alpha_i); the ratios and the running
 //    products and sum are carried in double-double, which removes the effect of the
@@ -61,30 +62,10 @@ __device__ __forceinline__ dd dd_mul(dd a, dd b) {
 
 // Quotient of two exactly representable integers as a double-double.
 __device__ __forceinline__ dd dd_ratio(double num, double den) {
-  double q = num / den;
+  double inv = 1.0 / den;
+  double q = num * inv;                    // within two ulp
   double r = __builtin_fma(-q, den, num);  // exact remainder
-  return fast_two_sum(q, r / den);
-}
-
-// Double-double with a separate power-of-two exponent: value = (hi + lo) * 2^e.
-struct dde {
-  double hi, lo;
-  int e;
-};
-
-__device__ __forceinline__ void normalise(dde &v) {
-  int k;
-  double h = __builtin_frexp(v.hi, &k);
-  v.lo = __builtin_ldexp(v.lo, -k);
-  v.hi = h;
-  v.e += k;
-}
-
-__device__ __forceinline__ dde dde_mul(dde a, dde b) {
-  dd m = dd_mul({a.hi, a.lo}, {b.hi, b.lo});
-  dde r{m.hi, m.lo, a.e + b.e};
-  normalise(r);
-  return r;
+  return fast_two_sum(q, r * inv);
 }
 
 // sqrt(q) of a small integer q as a double-double.
@@ -94,26 +75,35 @@ __device__ __forceinline__ dd dd_sqrt_int(double q) {
   return fast_two_sum(s, r / (2.0 * s));
 }
 
-// base^n, n >= 0, by binary powering.
-__device__ dde dde_pow(dd base, int n) {
-  dde result{1.0, 0.0, 0};
-  dde b{base.hi, base.lo, 0};
-  normalise(b);
-  while (n > 0) {
-    if (n & 1) result = dde_mul(result, b);
-    n >>= 1;
-    if (n) b = dde_mul(b, b);
+// Running product of factors sqrt(n!) and 1 / sqrt(n!): m * 2^e.
+struct FactProduct {
+  dd m{1.0, 0.0};
+  int e = 0;
+  __device__ __forceinline__ void times(const FactTables &ft, int n) {
+    const double4 f = ft.f[n];
+    m = dd_mul(m, {f.x, f.y});
+    e += ft.e[n];
   }
-  return result;
-}
+  __device__ __forceinline__ void over(const FactTables &ft, int n) {
+    const double4 f = ft.f[n];
+    m = dd_mul(m, {f.z, f.w});
+    e -= ft.e[n];
+  }
+  __device__ __forceinline__ void triad(const FactTables &ft, int x, int y, int z) {
+    times(ft, (x + y - z) / 2);
+    times(ft, (x - y + z) / 2);
+    times(ft, (-x + y + z) / 2);
+    over(ft, (x + y + z) / 2 + 1);
+    __builtin_amdgcn_sched_barrier(0);  // (the table reads of all factors at once spill)
+  }
+};
 
 __device__ __forceinline__ bool triad_ok(int a, int b, int c) {
   return ((a + b + c) & 1) == 0 && c >= (a > b ? a - b : b - a) && c <= a + b;
 }
 
-// {a b c; d e f}, all arguments in two-units.  `fexp` holds v_p(n!) for n <= fact_max.
-__device__ double sixj_device(int a, int b, int c, int d, int e, int f, const uint16_t *fexp,
-                              const int *primes, int nprime) {
+// {a b c; d e f}, all arguments in two-units.
+__device__ __forceinline__ double sixj_device(int a, int b, int c, int d, int e, int f, FactTables ft) {
   if (!(triad_ok(a, b, c) && triad_ok(a, e, f) && triad_ok(d, b, f) && triad_ok(d, e, c)))
     return 0.0;
   const int al[4] = {(a + b + c) / 2, (a + e + f) / 2, (d + b + f) / 2, (d + e + c) / 2};
@@ -121,40 +111,21 @@ __device__ double sixj_device(int a, int b, int c, int d, int e, int f, const ui
   int tmin = al[0], tmax = be[0];
   for (int q = 1; q < 4; ++q) tmin = al[q] > tmin ? al[q] : tmin;
   for (int q = 1; q < 3; ++q) tmax = be[q] < tmax ? be[q] : tmax;
-  // Factorial arguments with their exponent in P * T0^2.
-  const int tri[4][3] = {{a, b, c}, {a, e, f}, {d, b, f}, {d, e, c}};
-  int arg[24], coef[24];
-  int na = 0, top = tmin + 1;
-  for (int q = 0; q < 4; ++q) {
-    const int x = tri[q][0], y = tri[q][1], z = tri[q][2];
-    arg[na] = (x + y - z) / 2; coef[na++] = 1;
-    arg[na] = (x - y + z) / 2; coef[na++] = 1;
-    arg[na] = (-x + y + z) / 2; coef[na++] = 1;
-    arg[na] = (x + y + z) / 2 + 1; coef[na++] = -1;
-    if ((x + y + z) / 2 + 1 > top) top = (x + y + z) / 2 + 1;
-  }
-  arg[na] = tmin + 1; coef[na++] = 2;
-  for (int q = 0; q < 4; ++q) { arg[na] = tmin - al[q]; coef[na++] = -2; }
-  for (int q = 0; q < 3; ++q) { arg[na] = be[q] - tmin; coef[na++] = -2; }
-  // prod_p sqrt(p)^{E_p}: numerator and denominator powers kept apart.
-  dde num{0.5, 0.0, 1}, den{0.5, 0.0, 1};
-  for (int ip = 0; ip < nprime; ++ip) {
-    const int pr = primes[ip];
-    if (pr > top) break;
-    int E = 0;
-    for (int q = 0; q < na; ++q) E += coef[q] * (int)fexp[arg[q] * nprime + ip];
-    if (E == 0) continue;
-    dd sp = dd_sqrt_int((double)pr);
-    if (E > 0)
-      num = dde_mul(num, dde_pow(sp, E));
-    else
-      den = dde_mul(den, dde_pow(sp, -E));
-  }
+  FactProduct pref, first;  // sqrt(P), sqrt(T0)
+  pref.triad(ft, a, b, c);
+  pref.triad(ft, a, e, f);
+  pref.triad(ft, d, b, f);
+  pref.triad(ft, d, e, c);
+  first.times(ft, tmin + 1);
+  for (int q = 0; q < 4; ++q) first.over(ft, tmin - al[q]);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int q = 0; q < 3; ++q) first.over(ft, be[q] - tmin);
   // Series in double-double.  Terms can grow far beyond the first one before they fall off:
   // the running term and sum are scaled down together by 2^-768 (exact) whenever the term
   // passes 2^768, and the scale is put back at the end.
   dd rho{1.0, 0.0}, sum{1.0, 0.0};
   int sexp = 0;
+#pragma unroll 1
   for (int t = tmin; t < tmax; ++t) {
     double nu = -(double)(t + 2) * (double)(be[0] - t) * (double)(be[1] - t) * (double)(be[2] - t);
     double de = (double)(t + 1 - al[0]) * (double)(t + 1 - al[1]) * (double)(t + 1 - al[2]) *
@@ -167,17 +138,9 @@ __device__ double sixj_device(int a, int b, int c, int d, int e, int f, const ui
       sexp += 768;
     }
   }
-  // value = (-1)^tmin * num / den * sum
-  dd q;
-  {
-    // num / den in double-double: q = num.hi / den.hi, then one correction step.
-    double qh = num.hi / den.hi;
-    dd prod = dd_mul({qh, 0.0}, {den.hi, den.lo});
-    dd diff = dd_add({num.hi, num.lo}, {-prod.hi, -prod.lo});
-    q = fast_two_sum(qh, diff.hi / den.hi);
-  }
-  dd v = dd_mul(q, sum);
-  double r = __builtin_ldexp(v.hi + v.lo, num.e - den.e + sexp);
+  // value = (-1)^tmin * sqrt(P) * T0 * sum
+  dd v = dd_mul(dd_mul(pref.m, dd_mul(first.m, first.m)), sum);
+  double r = __builtin_ldexp(v.hi + v.lo, pref.e + 2 * first.e + sexp);
   return (tmin & 1) ? -r : r;
 }
 
@@ -185,10 +148,9 @@ __device__ double sixj_device(int a, int b, int c, int d, int e, int f, const ui
 //   (-1)^(j1-j2-m3) sqrt(D(j1 j2 j3) prod_a (j_a+m_a)! (j_a-m_a)!)
 //     * sum_t (-1)^t / [t! (j3-j2+t+m1)! (j3-j1+t-m2)! (j1+j2-j3-t)! (j1-t-m1)! (j2-t+m2)!],
 // D(abc) = (a+b-c)! (a-b+c)! (-a+b+c)! / (a+b+c+1)!, evaluated like the 6j symbol above: the
-// common factor sqrt(D prod (j +- m)!) T0 as an exact square root from prime exponents, the
+// common factor sqrt(D prod (j +- m)!) T0 from the factorial table, the
 // series 1 + r_0 + r_0 r_1 + ... with exact integer ratios in double-double.
-__device__ double threejm_device(int j1, int j2, int j3, int m1, int m2, int m3, const uint16_t *fexp,
-                                 const int *primes, int nprime) {
+__device__ __forceinline__ double threejm_device(int j1, int j2, int j3, int m1, int m2, int m3, FactTables ft) {
   if (m1 + m2 + m3 != 0 || !triad_ok(j1, j2, j3)) return 0.0;
   const int jj[3] = {j1, j2, j3}, mm[3] = {m1, m2, m3};
   for (int q = 0; q < 3; ++q)
@@ -202,96 +164,80 @@ __device__ double threejm_device(int j1, int j2, int j3, int m1, int m2, int m3,
   if (a2 < tmax) tmax = a2;
   if (a3 < tmax) tmax = a3;
   if (tmin > tmax) return 0.0;
-  int arg[16], coef[16];
-  int na = 0;
-  arg[na] = (j1 + j2 - j3) / 2; coef[na++] = 1;
-  arg[na] = (j1 - j2 + j3) / 2; coef[na++] = 1;
-  arg[na] = (-j1 + j2 + j3) / 2; coef[na++] = 1;
-  arg[na] = (j1 + j2 + j3) / 2 + 1; coef[na++] = -1;
+  FactProduct pref, first;  // sqrt(D prod (j +- m)!), sqrt(T0)
+  pref.triad(ft, j1, j2, j3);
   for (int q = 0; q < 3; ++q) {
-    arg[na] = (jj[q] + mm[q]) / 2; coef[na++] = 1;
-    arg[na] = (jj[q] - mm[q]) / 2; coef[na++] = 1;
+    pref.times(ft, (jj[q] + mm[q]) / 2);
+    pref.times(ft, (jj[q] - mm[q]) / 2);
   }
-  arg[na] = tmin; coef[na++] = -2;
-  arg[na] = b1 + tmin; coef[na++] = -2;
-  arg[na] = b2 + tmin; coef[na++] = -2;
-  arg[na] = a1 - tmin; coef[na++] = -2;
-  arg[na] = a2 - tmin; coef[na++] = -2;
-  arg[na] = a3 - tmin; coef[na++] = -2;
-  const int top = (j1 + j2 + j3) / 2 + 1;
-  dde num{0.5, 0.0, 1}, den{0.5, 0.0, 1};
-  for (int ip = 0; ip < nprime; ++ip) {
-    const int pr = primes[ip];
-    if (pr > top) break;
-    int E = 0;
-    for (int q = 0; q < na; ++q) E += coef[q] * (int)fexp[arg[q] * nprime + ip];
-    if (E == 0) continue;
-    dd sp = dd_sqrt_int((double)pr);
-    if (E > 0)
-      num = dde_mul(num, dde_pow(sp, E));
-    else
-      den = dde_mul(den, dde_pow(sp, -E));
-  }
+  first.over(ft, tmin);
+  first.over(ft, b1 + tmin);
+  first.over(ft, b2 + tmin);
+  first.over(ft, a1 - tmin);
+  first.over(ft, a2 - tmin);
+  first.over(ft, a3 - tmin);
   // term(t+1) / term(t) = -(a1 - t)(a2 - t)(a3 - t) / ((t + 1)(b1 + t + 1)(b2 + t + 1))
   dd rho{1.0, 0.0}, sum{1.0, 0.0};
+#pragma unroll 1
   for (int t = tmin; t < tmax; ++t) {
     const double nu = -(double)(a1 - t) * (double)(a2 - t) * (double)(a3 - t);
     const double de = (double)(t + 1) * (double)(b1 + t + 1) * (double)(b2 + t + 1);
     rho = dd_mul(rho, dd_ratio(nu, de));
     sum = dd_add(sum, rho);
   }
-  dd q;
-  {
-    double qh = num.hi / den.hi;
-    dd prod = dd_mul({qh, 0.0}, {den.hi, den.lo});
-    dd diff = dd_add({num.hi, num.lo}, {-prod.hi, -prod.lo});
-    q = fast_two_sum(qh, diff.hi / den.hi);
-  }
-  dd v = dd_mul(q, sum);
-  const double r = __builtin_ldexp(v.hi + v.lo, num.e - den.e);
+  dd v = dd_mul(dd_mul(pref.m, dd_mul(first.m, first.m)), sum);
+  const double r = __builtin_ldexp(v.hi + v.lo, pref.e + 2 * first.e);
   const int ph = (j1 - j2 - m3) / 2 + tmin;
   return (ph & 1) ? -r : r;
 }
 
 // 4jm(j1 j2 j3 j4; m1 m2 m3 m4)^(i): (j1 j2) coupled to i, then i with (j3 j4),
 //   (-1)^(i - mi) (j1 j2 i; m1 m2 mi) (i j3 j4; -mi m3 m4),  mi = -(m1 + m2).
-__device__ double fourjm_device(const int *j, const int *m, int i, const uint16_t *fexp,
-                                const int *primes, int nprime) {
+__device__ double fourjm_device(const int *j, const int *m, int i, FactTables ft) {
   const int mi = -(m[0] + m[1]);
   if (mi - m[2] - m[3] != 0) return 0.0;
-  const double v = threejm_device(j[0], j[1], i, m[0], m[1], mi, fexp, primes, nprime) *
-                   threejm_device(i, j[2], j[3], -mi, m[2], m[3], fexp, primes, nprime);
+  const double v = threejm_device(j[0], j[1], i, m[0], m[1], mi, ft) *
+                   threejm_device(i, j[2], j[3], -mi, m[2], m[3], ft);
   return (((i - mi) / 2) & 1) ? -v : v;
 }
 
 // Coefficient tables of the booster contraction: set s (blockIdx.y), entry (m, i) of its
 // M x n table = 4jm(j; m-tuple m; two_lo + 2 i).
 __global__ void fourjm_table_kernel(const FourjmSet *sets, const int *mtuples, double *out,
-                                    const uint16_t *fexp, const int *primes, int nprime) {
+                                    FactTables ft) {
   const FourjmSet st = sets[blockIdx.y];
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= st.M * st.n) return;
   const int m = idx / st.n, i = idx % st.n;
-  out[st.out + idx] = fourjm_device(st.j, mtuples + st.mt + 4 * m, st.two_lo + 2 * i, fexp, primes,
-                                    nprime);
+  out[st.out + idx] = fourjm_device(st.j, mtuples + st.mt + 4 * m, st.two_lo + 2 * i, ft);
 }
 
-__global__ void threejm_batch_kernel(const int *args, int n, double *out, const uint16_t *fexp,
-                                     const int *primes, int nprime, int fact_max) {
+__global__ void threejm_batch_kernel(const int *args, int n, double *out, FactTables ft, int fact_max) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n) return;
   const int *a = args + 6 * idx;
-  out[idx] = threejm_device(a[0], a[1], a[2], a[3], a[4], a[5], fexp, primes, nprime);
+  out[idx] = threejm_device(a[0], a[1], a[2], a[3], a[4], a[5], ft);
 }
 
-__global__ void fexp_kernel(uint16_t *fexp, int fact_max, const int *primes, int nprime) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (fact_max + 1) * nprime) return;
-  const int n = idx / nprime, p = primes[idx % nprime];
-  // Legendre: v_p(n!) = sum_k floor(n / p^k)
-  int v = 0;
-  for (long long pk = p; pk <= n; pk *= p) v += (int)(n / pk);
-  fexp[idx] = (uint16_t)v;
+// sqrt(n!) = (x + y) 2^e with x in [0.5, 1), 1 / sqrt(n!) = (z + w) 2^-e for n <= fact_max (one thread:
+// each entry is the one before times sqrt(n); once per context and growth).
+__global__ void fact_kernel(double4 *f, int *e, int fact_max) {
+  if (threadIdx.x || blockIdx.x) return;
+  dd s{1.0, 0.0};
+  int es = 0;
+  for (int n = 0; n <= fact_max; ++n) {
+    if (n > 1) s = dd_mul(s, dd_sqrt_int((double)n));
+    int k;
+    const double h = __builtin_frexp(s.hi, &k);
+    s = {h, __builtin_ldexp(s.lo, -k)};
+    es += k;
+    const double q = 1.0 / s.hi;
+    const dd p = dd_mul({q, 0.0}, s);
+    const dd r = dd_add({1.0, 0.0}, {-p.hi, -p.lo});
+    const dd g = fast_two_sum(q, r.hi / s.hi);
+    f[n] = {s.hi, s.lo, g.hi, g.lo};
+    e[n] = es;
+  }
 }
 
 // One thread per table entry.  Table t (0..4), its linear index decomposed row-major.
@@ -351,8 +297,7 @@ __global__ void sixj_table_kernel(TableParams tp, int64_t total) {
     int a6[6] = {k2, J[L13], x, i1, l25, J[L12]};
     for (int q = 0; q < 6; ++q) args[q] = a6[q];
   }
-  tp.tables[g] = sixj_device(args[0], args[1], args[2], args[3], args[4], args[5], tp.fexp,
-                             tp.primes, tp.nprime);
+  tp.tables[g] = sixj_device(args[0], args[1], args[2], args[3], args[4], args[5], tp.fact);
 }
 
 // Signed, x-major tables for the factorised (ring) assembly.  The phase (-1)^R of eq. (15j)
@@ -365,75 +310,103 @@ __global__ void sixj_table_kernel(TableParams tp, int64_t total) {
 //   U4[o23][o24][x][k3][k2] = (-1)^{r2} {l24 k3 x; j13 k2 l23}
 //   U5[o25][x][k2][i1]  = {k2 j13 x; i1 l25 j12}
 // so that W(i1, k2..k5) = sum_x U1 U2 U3 U4 U5 exactly.
-__device__ __forceinline__ void ring_table_entry(const TableParams &tp, int64_t g) {
-  if (g >= tp.toff[5]) return;
-  int t = 0;
-  while (t < 4 && g >= tp.toff[t + 1]) ++t;
-  int64_t idx = g - tp.toff[t];
-  const int nd = tp.nd;
+// One slice of a table (all but its last two indices fixed) per wavefront: the two indices' triads do not
+// couple them, so the entries that are not zero are a window of rows times a window of columns; the
+// lanes take those densely, after writing the zeros of the rest.  (A thread per entry spent its time
+// on the 64-bit index divisions of entries that are mostly zero: 224 us for two_j = 6, 8 shells with
+// 3.6 M entries, 0.5 M of them not zero; this 134 us, and 50 us with the factorial table.)
+__device__ __forceinline__ void ring_table_slice(const TableParams &tp, int slice) {
+  const int nd = tp.nd, NX = tp.NX;
   const int *J = tp.two_j;
-  const int NX = tp.NX;
-  const int n1 = tp.i1_n, nK2 = tp.K_n[0], nK3 = tp.K_n[1], nK4 = tp.K_n[2], nK5 = tp.K_n[3];
-  int64_t size;
-  switch (t) {
-    case 0: size = (int64_t)nd * NX * n1 * nK5; break;
-    case 1: size = (int64_t)nd * nd * NX * nK5 * nK4; break;
-    case 2: size = (int64_t)nd * nd * nd * NX * nK4 * nK3; break;
-    case 3: size = (int64_t)nd * nd * NX * nK3 * nK2; break;
-    default: size = (int64_t)nd * NX * nK2 * n1; break;
+  const int lane = threadIdx.x & 63;
+  const int n1 = nd * NX, n2 = nd * n1, n3 = nd * n2;
+  int t, s = slice;
+  if (s < n3) t = 2;
+  else if ((s -= n3) < n2) t = 1;
+  else if ((s -= n2) < n2) t = 3;
+  else if ((s -= n2) < n1) t = 0;
+  else if ((s -= n1) < n1) t = 4;
+  else return;
+  const bool last = s == (t == 2 ? n3 : t == 1 || t == 3 ? n2 : n1) - 1;
+  const int x = tp.X_lo2 + 2 * (s % NX);
+  const int o0 = s / NX % nd, o1 = s / NX / nd % nd, o2 = s / NX / nd / nd;  // innermost spin offset first
+  // Row and column ranges (lowest, count) of the table and the two pairs of spins that close a triad
+  // with each.
+  int rlo, rn, clo, cn, r0, r1, r2, r3, c0, c1, c2, c3;
+  auto set = [&](int a, int b, int c, int d, int e, int f, int g, int h) {
+    r0 = a; r1 = b; r2 = c; r3 = d; c0 = e; c1 = f; c2 = g; c3 = h;
+  };
+  int la, lb, lc = 0;
+  if (t == 0) {         // {i1 l25 x; k5 j14 j15}
+    la = J[L25] + 2 * o0; lb = 0;
+    rlo = tp.i1_lo2; rn = tp.i1_n; clo = tp.K_lo2[3]; cn = tp.K_n[3];
+    set(la, x, J[L14], J[L15], la, J[L15], J[L14], x);
+  } else if (t == 1) {  // {j14 k5 x; l35 k4 l45}
+    lb = J[L45] + 2 * o0; la = J[L35] + 2 * o1;
+    rlo = tp.K_lo2[3]; rn = tp.K_n[3]; clo = tp.K_lo2[2]; cn = tp.K_n[2];
+    set(J[L14], x, la, lb, J[L14], lb, la, x);
+  } else if (t == 2) {  // {k4 l35 x; k3 l24 l34}
+    lc = J[L35] + 2 * o0; lb = J[L34] + 2 * o1; la = J[L24] + 2 * o2;
+    rlo = tp.K_lo2[2]; rn = tp.K_n[2]; clo = tp.K_lo2[1]; cn = tp.K_n[1];
+    set(lc, x, la, lb, lc, lb, la, x);
+  } else if (t == 3) {  // {l24 k3 x; j13 k2 l23}
+    la = J[L24] + 2 * o0; lb = J[L23] + 2 * o1;
+    rlo = tp.K_lo2[1]; rn = tp.K_n[1]; clo = tp.K_lo2[0]; cn = tp.K_n[0];
+    set(la, x, J[L13], lb, la, lb, J[L13], x);
+  } else {              // {k2 j13 x; i1 l25 j12}
+    la = J[L25] + 2 * o0; lb = 0;
+    rlo = tp.K_lo2[0]; rn = tp.K_n[0]; clo = tp.i1_lo2; cn = tp.i1_n;
+    set(J[L13], x, la, J[L12], J[L13], J[L12], la, x);
   }
-  if (idx >= size) {  // padding: read (times zero) by operand reads that run past a table's end
-    tp.tables[g] = 0.0;
-    return;
+  // Windows [w, w + n) of positions; empty when a parity or a range does not fit.
+  auto window = [](int lo, int n, int a, int b, int c, int d, int &w) {
+    const int ab = a > b ? a - b : b - a, cd = c > d ? c - d : d - c;
+    int kl = ab > cd ? ab : cd, kh = a + b < c + d ? a + b : c + d;
+    if (((a + b + lo) & 1) || ((c + d + lo) & 1)) return 0;
+    kl = kl > lo ? kl : lo;
+    kh = kh < lo + 2 * (n - 1) ? kh : lo + 2 * (n - 1);
+    w = (kl - lo) / 2;
+    return kh < kl ? 0 : (kh - kl) / 2 + 1;
+  };
+  int rw = 0, cw = 0;
+  int nr = window(rlo, rn, r0, r1, r2, r3, rw), nc = window(clo, cn, c0, c1, c2, c3, cw);
+  if (nr == 0 || nc == 0) nr = nc = 0;
+  double *out = tp.tables + tp.toff[t] + (int64_t)s * rn * cn;
+  for (int q = lane; q < rn * cn; q += 64) {
+    const int r = q / cn, c = q - r * cn;
+    if ((unsigned)(r - rw) >= (unsigned)nr || (unsigned)(c - cw) >= (unsigned)nc) out[q] = 0.0;
   }
-  int64_t r = idx;
-  double v = 0.0;
-  int ph = 0;  // exponent of -1 (two-units, halved below)
-  if (t == 0) {
-    const int k5 = tp.K_lo2[3] + 2 * (int)(r % nK5); r /= nK5;
-    const int i1 = tp.i1_lo2 + 2 * (int)(r % n1); r /= n1;
-    const int x = tp.X_lo2 + 2 * (int)(r % NX); r /= NX;
-    const int l25 = J[L25] + 2 * (int)r;
-    v = (double)(x + 1) * sixj_device(i1, l25, x, k5, J[L14], J[L15], tp.fexp, tp.primes, tp.nprime);
-    ph = (i1 + J[L12] + J[L13]) / 2 + (k5 + J[L15] + l25) / 2;
-  } else if (t == 1) {
-    const int k4 = tp.K_lo2[2] + 2 * (int)(r % nK4); r /= nK4;
-    const int k5 = tp.K_lo2[3] + 2 * (int)(r % nK5); r /= nK5;
-    const int x = tp.X_lo2 + 2 * (int)(r % NX); r /= NX;
-    const int l45 = J[L45] + 2 * (int)(r % nd); r /= nd;
-    const int l35 = J[L35] + 2 * (int)r;
-    v = sixj_device(J[L14], k5, x, l35, k4, l45, tp.fexp, tp.primes, tp.nprime);
-    ph = (k4 + J[L14] + l45) / 2;
-  } else if (t == 2) {
-    const int k3 = tp.K_lo2[1] + 2 * (int)(r % nK3); r /= nK3;
-    const int k4 = tp.K_lo2[2] + 2 * (int)(r % nK4); r /= nK4;
-    const int x = tp.X_lo2 + 2 * (int)(r % NX); r /= NX;
-    const int l35 = J[L35] + 2 * (int)(r % nd); r /= nd;
-    const int l34 = J[L34] + 2 * (int)(r % nd); r /= nd;
-    const int l24 = J[L24] + 2 * (int)r;
-    v = sixj_device(k4, l35, x, k3, l24, l34, tp.fexp, tp.primes, tp.nprime);
-    ph = (k3 + l34 + l35) / 2;
-  } else if (t == 3) {
-    const int k2 = tp.K_lo2[0] + 2 * (int)(r % nK2); r /= nK2;
-    const int k3 = tp.K_lo2[1] + 2 * (int)(r % nK3); r /= nK3;
-    const int x = tp.X_lo2 + 2 * (int)(r % NX); r /= NX;
-    const int l24 = J[L24] + 2 * (int)(r % nd); r /= nd;
-    const int l23 = J[L23] + 2 * (int)r;
-    v = sixj_device(l24, k3, x, J[L13], k2, l23, tp.fexp, tp.primes, tp.nprime);
-    ph = (k2 + l23 + l24) / 2;
-  } else {
-    const int i1 = tp.i1_lo2 + 2 * (int)(r % n1); r /= n1;
-    const int k2 = tp.K_lo2[0] + 2 * (int)(r % nK2); r /= nK2;
-    const int x = tp.X_lo2 + 2 * (int)(r % NX); r /= NX;
-    const int l25 = J[L25] + 2 * (int)r;
-    v = sixj_device(k2, J[L13], x, i1, l25, J[L12], tp.fexp, tp.primes, tp.nprime);
-    ph = 0;
+  // Padding: read (times zero) by operand reads that run past a table's end.
+  if (last)
+    for (int64_t q = tp.toff[t] + (int64_t)(s + 1) * rn * cn + lane; q < tp.toff[t + 1]; q += 64) tp.tables[q] = 0.0;
+  for (int q = lane; q < nr * nc; q += 64) {
+    const int r = q / nc, row = rlo + 2 * (rw + r), col = clo + 2 * (cw + q - r * nc);
+    int a, b, d, e, f;  // {a b x; d e f}
+    int ph;             // exponent of -1
+    if (t == 0) {
+      a = row; b = la; d = col; e = J[L14]; f = J[L15];
+      ph = (row + J[L12] + J[L13]) / 2 + (col + J[L15] + la) / 2;
+    } else if (t == 1) {
+      a = J[L14]; b = row; d = la; e = col; f = lb;
+      ph = (col + J[L14] + lb) / 2;
+    } else if (t == 2) {
+      a = row; b = lc; d = col; e = la; f = lb;
+      ph = (col + lb + lc) / 2;
+    } else if (t == 3) {
+      a = la; b = row; d = J[L13]; e = col; f = lb;
+      ph = (col + lb + la) / 2;
+    } else {
+      a = row; b = J[L13]; d = col; e = la; f = J[L12];
+      ph = 0;
+    }
+    double v = sixj_device(a, b, x, d, e, f, tp.fact);
+    if (t == 0) v *= (double)(x + 1);
+    out[(rw + r) * cn + cw + q - r * nc] = (ph & 1) ? -v : v;
   }
-  tp.tables[g] = (ph & 1) ? -v : v;
 }
 
 __global__ __launch_bounds__(256) void ring_table_kernel(TableParams tp) {
-  ring_table_entry(tp, (int64_t)blockIdx.x * 256 + threadIdx.x);
+  ring_table_slice(tp, __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)));
 }
 
 // The tables of several configurations in one launch.
@@ -441,11 +414,10 @@ __global__ __launch_bounds__(256) void ring_table_batch_kernel(const TableParams
                                                                const BatchJob *__restrict__ jobs, int njobs) {
   int b = blockIdx.x;
   const TableParams &tp = tps[batch_job(jobs, njobs, b)];
-  ring_table_entry(tp, (int64_t)b * 256 + threadIdx.x);
+  ring_table_slice(tp, __builtin_amdgcn_readfirstlane(b * 4 + (threadIdx.x >> 6)));
 }
 
-__global__ void sixj_batch_kernel(const int *args, int n, double *out, const uint16_t *fexp,
-                                  const int *primes, int nprime, int fact_max) {
+__global__ void sixj_batch_kernel(const int *args, int n, double *out, FactTables ft, int fact_max) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int *a = args + 6 * i;
@@ -456,15 +428,13 @@ __global__ void sixj_batch_kernel(const int *args, int n, double *out, const uin
     out[i] = __builtin_nan("");
     return;
   }
-  out[i] = sixj_device(a[0], a[1], a[2], a[3], a[4], a[5], fexp, primes, nprime);
+  out[i] = sixj_device(a[0], a[1], a[2], a[3], a[4], a[5], ft);
 }
 
 }  // namespace
 
-hipError_t launch_fexp_table(uint16_t *fexp, int fact_max, const int *primes, int nprime,
-                             hipStream_t s) {
-  int total = (fact_max + 1) * nprime;
-  fexp_kernel<<<(total + 255) / 256, 256, 0, s>>>(fexp, fact_max, primes, nprime);
+hipError_t launch_fact_table(double4 *f, int *e, int fact_max, hipStream_t s) {
+  fact_kernel<<<1, 64, 0, s>>>(f, e, fact_max);
   return hipGetLastError();
 }
 
@@ -474,12 +444,13 @@ hipError_t launch_sixj_tables(const TableParams &tp, int64_t total, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_ring_tables(const TableParams &tp, int64_t total, hipStream_t s) {
-  ring_table_kernel<<<(unsigned)ring_table_blocks(total), 256, 0, s>>>(tp);
+hipError_t launch_ring_tables(const TableParams &tp, hipStream_t s) {
+  ring_table_kernel<<<(unsigned)ring_table_blocks(tp.nd, tp.NX), 256, 0, s>>>(tp);
   return hipGetLastError();
 }
 
-int64_t ring_table_blocks(int64_t total) { return (total + 255) / 256; }
+// Four slices to a workgroup.
+int64_t ring_table_blocks(int64_t nd, int64_t nx) { return (nd * nx * (nd * nd + 2 * nd + 2) + 3) / 4; }
 
 hipError_t launch_ring_tables_batch(const TableParams *tps, const BatchJob *jobs, int njobs, int64_t blocks,
                                     hipStream_t s) {
@@ -489,25 +460,22 @@ hipError_t launch_ring_tables_batch(const TableParams *tps, const BatchJob *jobs
 }
 
 hipError_t launch_fourjm_tables(const FourjmSet *sets_dev, int nsets, int max_entries,
-                                const int *mtuples_dev, double *out, const uint16_t *fexp,
-                                const int *primes, int nprime, hipStream_t s) {
+                                const int *mtuples_dev, double *out, FactTables ft, hipStream_t s) {
   if (nsets <= 0 || max_entries <= 0) return hipSuccess;
   dim3 grid((unsigned)((max_entries + 255) / 256), (unsigned)nsets);
-  fourjm_table_kernel<<<grid, 256, 0, s>>>(sets_dev, mtuples_dev, out, fexp, primes, nprime);
+  fourjm_table_kernel<<<grid, 256, 0, s>>>(sets_dev, mtuples_dev, out, ft);
   return hipGetLastError();
 }
 
-hipError_t launch_threejm_batch(const int *args, int n, double *out, const uint16_t *fexp,
-                                const int *primes, int nprime, int fact_max, hipStream_t s) {
+hipError_t launch_threejm_batch(const int *args, int n, double *out, FactTables ft, int fact_max, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  threejm_batch_kernel<<<(n + 255) / 256, 256, 0, s>>>(args, n, out, fexp, primes, nprime, fact_max);
+  threejm_batch_kernel<<<(n + 255) / 256, 256, 0, s>>>(args, n, out, ft, fact_max);
   return hipGetLastError();
 }
 
-hipError_t launch_sixj_batch(const int *args, int n, double *out, const uint16_t *fexp,
-                             const int *primes, int nprime, int fact_max, hipStream_t s) {
+hipError_t launch_sixj_batch(const int *args, int n, double *out, FactTables ft, int fact_max, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  sixj_batch_kernel<<<(n + 255) / 256, 256, 0, s>>>(args, n, out, fexp, primes, nprime,
+  sixj_batch_kernel<<<(n + 255) / 256, 256, 0, s>>>(args, n, out, ft,
                                                     fact_max);
   return hipGetLastError();
 }
