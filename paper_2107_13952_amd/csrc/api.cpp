@@ -1685,11 +1685,13 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
   // d-function keys: for each (j, l) met on a link, the rows m = -j..j.
   std::map<std::pair<int, int>, int> key_base;
   std::vector<DKey> keys;
+  std::vector<int> groups;
   auto key_of = [&](int j2, int l2) {
     auto it = key_base.find({j2, l2});
     if (it != key_base.end()) return it->second;
     const int base = (int)keys.size();
     key_base[{j2, l2}] = base;
+    groups.push_back(base);
     const double rho = gamma * (j2 / 2.0 + 1.0);
     double phase = 0.0;
     for (int n2 = j2 + 2; n2 <= l2; n2 += 2) phase += std::atan2(rho, n2 / 2.0);
@@ -1759,6 +1761,43 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     const int kmax = b.two_klo + 2 * (b.kdim - 1);
     fact = std::max(fact, std::max(b.lb[0] + b.lb[1], b.lb[2] + b.lb[3]) + kmax);
   }
+  groups.push_back((int)keys.size());
+  // The blocks of each edge as a matrix over pairs of key bases.
+  BoosterGrid grid[4];
+  std::vector<int> pairs, bmap, tiles;
+  for (int e = 0; e < 4; ++e) {
+    std::map<std::pair<int, int>, int> id[2];
+    std::vector<int> list[2], cell;  // (row, column, offset in I) of each block
+    for (int q = 0; q < nb; ++q) {
+      const int *bi = &binfo[9 * (size_t)q];
+      if (bi[0] != e || bi[3] == 0) continue;
+      for (int h = 0; h < 2; ++h) {
+        const std::pair<int, int> k(bi[5 + 2 * h], bi[6 + 2 * h]);
+        auto it = id[h].emplace(k, (int)id[h].size());
+        if (it.second) list[h].insert(list[h].end(), {k.first, k.second});
+        cell.push_back(it.first->second);
+      }
+      cell.push_back(bi[4]);
+    }
+    BoosterGrid &g = grid[e];
+    g.M = M_edge[e];
+    g.nrow = (int)id[0].size();
+    g.ncol = (int)id[1].size();
+    g.rows = (int)pairs.size();
+    pairs.insert(pairs.end(), list[0].begin(), list[0].end());
+    g.cols = (int)pairs.size();
+    pairs.insert(pairs.end(), list[1].begin(), list[1].end());
+    g.map = (int)bmap.size();
+    bmap.resize(bmap.size() + (size_t)g.nrow * g.ncol, -1);
+    for (size_t k = 0; k < cell.size(); k += 3) bmap[g.map + (size_t)cell[k] * g.ncol + cell[k + 1]] = cell[k + 2];
+    for (int r = 0; r < g.nrow; r += 16)
+      for (int cl = 0; cl < g.ncol; cl += 16) {
+        bool any = false;
+        for (int i = r; i < std::min(r + 16, g.nrow) && !any; ++i)
+          for (int j = cl; j < std::min(cl + 16, g.ncol) && !any; ++j) any = bmap[g.map + (size_t)i * g.ncol + j] >= 0;
+        if (any) tiles.insert(tiles.end(), {e, r, cl, 0});
+      }
+  }
   if (fact / 2 + 2 > 2 * kSixjMaxTwo + 2) return fail(c, EPRL_ERANGE, "spins beyond the 3jm range");
   rc = ensure_fact(c, fact / 2 + 2);
   if (rc) return rc;
@@ -1782,6 +1821,9 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
   const size_t o_boffs = take(boffs.size() * sizeof(int64_t));
   const size_t o_mt = take(mtup.size() * sizeof(int));
   const size_t o_sets = take(sets.size() * sizeof(FourjmSet));
+  const size_t o_groups = take(groups.size() * sizeof(int));
+  const size_t o_pairs = take(pairs.size() * sizeof(int)), o_bmap = take(bmap.size() * sizeof(int));
+  const size_t o_tiles = take(tiles.size() * sizeof(int));
   const size_t static_bytes = off;
   const size_t o_coef = take((size_t)(ci_total + ck_total) * sizeof(double));
   const size_t o_I = take((size_t)I_total * 4 * sizeof(double));
@@ -1814,6 +1856,10 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
       std::memcpy(stg + o_boffs, boffs.data(), boffs.size() * sizeof(int64_t));
       if (!mtup.empty()) std::memcpy(stg + o_mt, mtup.data(), mtup.size() * sizeof(int));
       if (!sets.empty()) std::memcpy(stg + o_sets, sets.data(), sets.size() * sizeof(FourjmSet));
+      std::memcpy(stg + o_groups, groups.data(), groups.size() * sizeof(int));
+      if (!pairs.empty()) std::memcpy(stg + o_pairs, pairs.data(), pairs.size() * sizeof(int));
+      if (!bmap.empty()) std::memcpy(stg + o_bmap, bmap.data(), bmap.size() * sizeof(int));
+      if (!tiles.empty()) std::memcpy(stg + o_tiles, tiles.data(), tiles.size() * sizeof(int));
       rc = upload(c, ws, static_bytes);
       if (rc) return rc;
       HIP_TRY(c, launch_fourjm_tables(reinterpret_cast<const FourjmSet *>(ws + o_sets), (int)sets.size(),
@@ -1857,6 +1903,13 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     bp.stat = reinterpret_cast<double *>(ws + o_stat);
     bp.nblocks = nb;
     bp.Mmax = Mmax;
+    bp.groups = reinterpret_cast<const int *>(ws + o_groups);
+    bp.ngroups = (int)groups.size() - 1;
+    for (int e = 0; e < 4; ++e) bp.grid[e] = grid[e];
+    bp.pairs = reinterpret_cast<const int *>(ws + o_pairs);
+    bp.bmap = reinterpret_cast<const int *>(ws + o_bmap);
+    bp.tiles = reinterpret_cast<const int *>(ws + o_tiles);
+    bp.ntiles = (int)tiles.size() / 4;
     HIP_TRY(c, launch_booster_dfun(bp, c->stream));
     HIP_TRY(c, launch_booster_integrals(bp, c->stream));
     HIP_TRY(c, launch_booster_assemble(bp, reinterpret_cast<double *>(ws + o_stat3), c->stream));

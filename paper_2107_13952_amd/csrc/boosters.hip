@@ -27,11 +27,11 @@
 // subintervals growing linearly from u = 0; each gets a 30- and a 61-point Gauss-Legendre rule
 // (the host builds the nodes); the 61-point sum is the value and |61 - 30| the error estimate.
 //
-// Kernels: (1) d on every (j, l, m) and r node (one wavefront per pair, lanes over the s
-// nodes); (2) per booster block and m-tuple the r integral of the product of its four d
-// (one wavefront each, lanes over the r nodes); (3) per block the contraction with the 4jm
-// coefficient tables (sixj.hip) and the error and magnitude statistics.  All sums run in a fixed
-// order.
+// Kernels: (1) d on every (j, l, m) and r node (one wavefront per (j, l) and r, lanes over the s
+// nodes, everything that does not depend on m made once); (2) the r integrals of the products of
+// four d as matrix products over the r nodes, on the matrix cores; (3) per block the contraction
+// with the 4jm coefficient tables (sixj.hip) and the error and magnitude statistics.  All sums run
+// in a fixed order.
 #include "eprl_internal.hpp"
 
 namespace eprl {
@@ -61,10 +61,9 @@ __device__ double jacobi(int n, int a, int b, double x) {
   return p1;
 }
 
-// SU(2) d in Jacobi form from cos^2 and sin^2 of the half angle.
-__device__ __forceinline__ double dsu2(double norm, int mu, int nu, int s, double c2, double s2) {
-  const double sh = __builtin_sqrt(s2 > 0.0 ? s2 : 0.0), ch = __builtin_sqrt(c2 > 0.0 ? c2 : 0.0);
-  return norm * ipow(sh, mu) * ipow(ch, nu) * jacobi(s, mu, nu, c2 - s2);
+// SU(2) d in Jacobi form from sin and cos of the half angle and cos of the angle.
+__device__ __forceinline__ double dsu2(double norm, int mu, int nu, int s, double sh, double ch, double cb) {
+  return norm * ipow(sh, mu) * ipow(ch, nu) * jacobi(s, mu, nu, cb);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -72,76 +71,132 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// (1) d_{jlm}(r) for key `key` and r node `ir`: one wavefront, lanes over the s nodes.
+// (1) d_{jlm}(r) for the keys of group `grp` (one (j, l), m = -j..j) at r node `ir`: one wavefront,
+// lanes over the s nodes.  The exponentials, the half-angle functions and the phase do not depend
+// on m: a wavefront per key made them 2 j + 1 times (484 us for two_j = 6, 8 shells, now 216 us).
 __global__ __launch_bounds__(256) void booster_dfun_kernel(BoosterParams bp) {
+  constexpr int kS = 4;  // s nodes of a lane held at a time
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
-  if (wave >= (int64_t)bp.nkeys * bp.nr) return;  // uniform over the wavefront
-  const int key = (int)(wave / bp.nr), ir = (int)(wave % bp.nr);
-  const DKey K = bp.keys[key];
+  if (wave >= (int64_t)bp.ngroups * bp.nr) return;  // uniform over the wavefront
+  const int grp = __builtin_amdgcn_readfirstlane((int)(wave / bp.nr)), ir = (int)(wave % bp.nr);
+  const int k0 = bp.groups[grp], k1 = bp.groups[grp + 1];
+  const double rho = bp.keys[k0].rho;
   const double r = bp.r[ir];
   const double sh2 = 2.0 * sinh(r), emr = exp(-r);
-  double re = 0.0, im = 0.0;
-  for (int q = lane; q < bp.ns; q += 64) {
-    const double x = bp.sx[q], w = bp.sw[q];
-    const double s = r * x;
-    // e^s - e^-r = e^-r expm1(r (1 + x)) and e^r - e^s = e^s expm1(r (1 - x)): no cancellation
-    // at small r.
-    const double ep = expm1(r * (1.0 + x)), em = expm1(r * (1.0 - x));
-    const double es = exp(s), ems = exp(-s);
-    const double c2 = emr * ep / sh2, s2 = es * em / sh2;
-    const double c2p = ems * ep / sh2, s2p = emr * em / sh2;
-    const double f = w * dsu2(K.nj, K.muj, K.nuj, K.sj, c2, s2) * dsu2(K.nl, K.mul, K.nul, K.sl, c2p, s2p);
-    double sn, cs;
-    sincos(K.rho * s, &sn, &cs);
-    re += f * cs;
-    im += f * sn;
-  }
-  re = wave_sum(re);
-  im = wave_sum(im);
-  if (lane == 0) {
-    const double scale = K.pre * r / sh2;
-    bp.dtab[2 * wave] = scale * (re * K.ph_re - im * K.ph_im);
-    bp.dtab[2 * wave + 1] = scale * (re * K.ph_im + im * K.ph_re);
+  for (int q0 = lane; q0 < bp.ns; q0 += 64 * kS) {
+    double sh[kS], ch[kS], cb[kS], shp[kS], chp[kS], cbp[kS], wc[kS], wn[kS];
+#pragma unroll
+    for (int i = 0; i < kS; ++i) {
+      const int q = q0 + 64 * i;
+      const double x = q < bp.ns ? bp.sx[q] : 0.0, w = q < bp.ns ? bp.sw[q] : 0.0;
+      const double s = r * x;
+      // e^s - e^-r = e^-r expm1(r (1 + x)) and e^r - e^s = e^s expm1(r (1 - x)): no cancellation
+      // at small r.
+      const double ep = expm1(r * (1.0 + x)), em = expm1(r * (1.0 - x));
+      const double es = exp(s), ems = exp(-s);
+      const double c2 = emr * ep / sh2, s2 = es * em / sh2;
+      const double c2p = ems * ep / sh2, s2p = emr * em / sh2;
+      sh[i] = __builtin_sqrt(s2 > 0.0 ? s2 : 0.0);
+      ch[i] = __builtin_sqrt(c2 > 0.0 ? c2 : 0.0);
+      shp[i] = __builtin_sqrt(s2p > 0.0 ? s2p : 0.0);
+      chp[i] = __builtin_sqrt(c2p > 0.0 ? c2p : 0.0);
+      cb[i] = c2 - s2;
+      cbp[i] = c2p - s2p;
+      double sn, cs;
+      sincos(rho * s, &sn, &cs);
+      wc[i] = w * cs;
+      wn[i] = w * sn;
+    }
+    for (int key = k0; key < k1; ++key) {
+      const DKey &K = bp.keys[key];
+      const double nj = K.nj, nl = K.nl;
+      const int muj = K.muj, nuj = K.nuj, sj = K.sj, mul = K.mul, nul = K.nul, sl = K.sl;
+      double re = 0.0, im = 0.0;
+#pragma unroll
+      for (int i = 0; i < kS; ++i) {
+        const double f = dsu2(nj, muj, nuj, sj, sh[i], ch[i], cb[i]) * dsu2(nl, mul, nul, sl, shp[i], chp[i], cbp[i]);
+        re += f * wc[i];
+        im += f * wn[i];
+      }
+      re = wave_sum(re);
+      im = wave_sum(im);
+      if (lane == 0) {
+        const double scale = K.pre * r / sh2;
+        const int64_t at = 2 * ((int64_t)key * bp.nr + ir);
+        const double vr = scale * (re * K.ph_re - im * K.ph_im), vi = scale * (re * K.ph_im + im * K.ph_re);
+        bp.dtab[at] = q0 == 0 ? vr : bp.dtab[at] + vr;
+        bp.dtab[at + 1] = q0 == 0 ? vi : bp.dtab[at + 1] + vi;
+      }
+    }
   }
 }
 
-// (2) Per block (blockIdx.y) and m-tuple (one wavefront each): the two rules' integrals of the
-// product of the block's four d functions.
-__global__ __launch_bounds__(256) void booster_integrals_kernel(BoosterParams bp) {
-  const int b = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int mi = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const int *bi = bp.binfo + 9 * b;
-  const int e = bi[0], M = bi[3], moff = bi[4];
-  if (mi >= M) return;
+typedef double d4v __attribute__((ext_vector_type(4)));
+typedef double d2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ d2v cmul(d2v a, d2v b) { return d2v{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
+
+// (2) The two rules' integrals of the products of four d, sum_r w(r) X(r) Y(r) with X = d_1 d_2 of the
+// first two links and Y = d_3 d_4 of the others: for one edge and m-tuple a complex matrix product of
+// the edge's distinct X (rows) and Y (columns) over the r nodes.  One workgroup per m-tuple and 16 x 16
+// tile of (row, column) pairs; its eight wavefronts share the r nodes, three the 30-point rule, five
+// the 61-point rule, and their sums are added in order.  Bound by the matrix instructions (four per
+// four r nodes) and the reads of d from L2 about evenly; a wavefront per (block, m-tuple) read four
+// complex d for every product and took 2490 us for two_j = 6, 8 shells, this 573 us.
+constexpr int kIntWaves = 8, kInt30 = 3;
+__global__ __launch_bounds__(64 * kIntWaves) void booster_integrals_kernel(BoosterParams bp) {
+  __shared__ d2v part[kIntWaves][4][64];
+  const int *tl = bp.tiles + 4 * blockIdx.y;
+  const int e = tl[0], row0 = tl[1], col0 = tl[2];
+  const int mi = blockIdx.x;
+  const BoosterGrid &gr = bp.grid[e];
+  if (mi >= gr.M) return;
   const int *mt = bp.mtuples + bp.mt_edge[e] + 4 * mi;
-  const double *d[4];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  // This lane's row and column (padding: the last one, results unused).
+  const int row = row0 + c < gr.nrow ? row0 + c : gr.nrow - 1, col = col0 + c < gr.ncol ? col0 + c : gr.ncol - 1;
+  const d2v *d[4];
+#pragma unroll
   for (int a = 0; a < 4; ++a) {
-    // row of (j_a, l_a, m_a): the key base of (j_a, l_a) at m = -j_a, plus (m_a + j_a) / 2
-    const int row = bi[5 + a] + (mt[a] + bp.jb_edge[e][a]) / 2;
-    d[a] = bp.dtab + 2 * (int64_t)row * bp.nr;
+    const int base = bp.pairs[(a < 2 ? gr.rows + 2 * row : gr.cols + 2 * col) + (a & 1)];
+    d[a] = reinterpret_cast<const d2v *>(bp.dtab) + (int64_t)(base + (mt[a] + bp.jb_edge[e][a]) / 2) * bp.nr;
   }
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int rule = 0; rule < 2; ++rule) {
-    const int q0 = rule ? bp.nr30 : 0, q1 = rule ? bp.nr : bp.nr30;
-    double re = 0.0, im = 0.0;
-    for (int q = q0 + lane; q < q1; q += 64) {
-      double pr = d[0][2 * q], pi = d[0][2 * q + 1];
-      for (int a = 1; a < 4; ++a) {
-        const double xr = d[a][2 * q], xi = d[a][2 * q + 1];
-        const double t = pr * xr - pi * xi;
-        pi = pr * xi + pi * xr;
-        pr = t;
-      }
-      re += bp.rw[q] * pr;
-      im += bp.rw[q] * pi;
-    }
-    acc[2 * rule] = wave_sum(re);
-    acc[2 * rule + 1] = wave_sum(im);
+  // Groups of four nodes of this wavefront.
+  const bool r61 = w >= kInt30;
+  const int q0 = r61 ? bp.nr30 : 0, q1 = r61 ? bp.nr : bp.nr30, ng = (q1 - q0 + 3) / 4;
+  const int part_n = r61 ? kIntWaves - kInt30 : kInt30, part_i = r61 ? w - kInt30 : w;
+  const int b0 = ng * part_i / part_n, b1 = ng * (part_i + 1) / part_n;
+  d4v re = {0.0, 0.0, 0.0, 0.0}, im = re, im2 = re, re2 = re;
+#pragma unroll 4
+  for (int b = b0; b < b1; ++b) {
+    const int q = q0 + 4 * b + g;
+    const bool in = q < q1;
+    const int qq = in ? q : q1 - 1;
+    const d2v x = cmul(d[0][qq], d[1][qq]), y = cmul(d[2][qq], d[3][qq]);
+    const double wt = in ? bp.rw[qq] : 0.0;
+    const double xr = wt * x.x, xi = wt * x.y;
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, y.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, y.y, im, 0, 0, 0);
+    re2 = __builtin_amdgcn_mfma_f64_16x16x4f64(xi, y.y, re2, 0, 0, 0);
+    im2 = __builtin_amdgcn_mfma_f64_16x16x4f64(xi, y.x, im2, 0, 0, 0);
   }
-  if (lane == 0)
-    for (int q = 0; q < 4; ++q) bp.I[4 * (int64_t)(moff + mi) + q] = acc[q];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[w][r][lane] = d2v{re[r] - re2[r], im[r] + im2[r]};
+  __syncthreads();
+  // Thread (w < 4): register w of every lane: entry (row g + 4 w, column c).
+  if (w >= 4) return;
+  const int rr = row0 + g + 4 * w, cc = col0 + c;
+  if (rr >= gr.nrow || cc >= gr.ncol) return;
+  const int moff = bp.bmap[gr.map + rr * gr.ncol + cc];
+  if (moff < 0) return;
+  d2v v[2] = {d2v{0.0, 0.0}, d2v{0.0, 0.0}};
+  for (int q = 0; q < kIntWaves; ++q) v[q >= kInt30] += part[q][w][lane];
+  double *out = bp.I + 4 * (int64_t)(moff + mi);
+  out[0] = v[0].x;
+  out[1] = v[0].y;
+  out[2] = v[1].x;
+  out[3] = v[1].y;
 }
 
 // (3) One workgroup per block: entry (i, k) = sum over the m-tuples of 4jm(j; m; i) 4jm(l; m; k)
@@ -202,16 +257,16 @@ __global__ __launch_bounds__(256) void booster_stat_kernel(const double *stat, i
 }  // namespace
 
 hipError_t launch_booster_dfun(const BoosterParams &bp, hipStream_t s) {
-  const int64_t waves = (int64_t)bp.nkeys * bp.nr;
+  const int64_t waves = (int64_t)bp.ngroups * bp.nr;
   if (waves == 0) return hipSuccess;
   booster_dfun_kernel<<<(unsigned)((waves + 3) / 4), 256, 0, s>>>(bp);
   return hipGetLastError();
 }
 
 hipError_t launch_booster_integrals(const BoosterParams &bp, hipStream_t s) {
-  if (bp.nblocks == 0 || bp.Mmax == 0) return hipSuccess;
-  dim3 grid((unsigned)((bp.Mmax + 3) / 4), (unsigned)bp.nblocks);
-  booster_integrals_kernel<<<grid, 256, 0, s>>>(bp);
+  if (bp.ntiles == 0 || bp.Mmax == 0) return hipSuccess;
+  dim3 grid((unsigned)bp.Mmax, (unsigned)bp.ntiles);
+  booster_integrals_kernel<<<grid, 64 * kIntWaves, 0, s>>>(bp);
   return hipGetLastError();
 }
 

@@ -284,6 +284,13 @@ struct DKey {
   double nj, nl;                      // xi * sqrt(s! (s+mu+nu)! / ((s+mu)! (s+nu)!)) of each d
   int muj, nuj, sj, mul, nul, sl;     // Jacobi parameters of each d
 };
+// The blocks of one edge as a matrix: rows, the distinct pairs of key bases of the first two links;
+// columns, those of the other two.
+struct BoosterGrid {
+  int M, nrow, ncol;       // m-tuples, rows, columns
+  int rows, cols, map;     // offsets in pairs (two key bases each) and bmap
+};
+
 struct BoosterParams {
   const DKey *keys;
   int nkeys;
@@ -305,6 +312,14 @@ struct BoosterParams {
   double *B;               // packed boosters (real parts of the 61-point values)
   double *stat;            // per block: max |G61 - G30|, max |G61|, max |Im G61|
   int nblocks, Mmax;
+  // grouped for the kernels: keys of one (j, l) together, group g from groups[g]; the blocks' matrices,
+  // bmap[row][column] the block's offset in I (-1: no block), and their 16 x 16 tiles (edge, row,
+  // column, 0)
+  const int *groups;
+  int ngroups;
+  BoosterGrid grid[4];
+  const int *pairs, *bmap, *tiles;
+  int ntiles;
 };
 hipError_t launch_booster_dfun(const BoosterParams &bp, hipStream_t s);
 hipError_t launch_booster_integrals(const BoosterParams &bp, hipStream_t s);

@@ -121,3 +121,13 @@ def test_boosters_invalid_arguments(lib):
         lib.boosters([2] * 10, 1, -1.0)
     with pytest.raises(lib.EprlError):
         lib.boosters([2] * 10, 1, 1.2, tol=0.0)
+
+
+# The r integrals run as matrix products over 16 x 16 tiles of link pairs: edges with fewer, exactly and
+# more than sixteen pairs on either side, unequal spins (m-tuples differ from edge to edge).
+@pytest.mark.parametrize("two_j,dl", [([1, 1, 2, 0, 1, 2, 2, 2, 2, 2], 3), ([1, 1, 2, 2, 1, 0, 2, 2, 2, 2], 1),
+                                      ([0] * 10, 4)])
+def test_booster_integral_tiles(lib, two_j, dl):
+    ref, imag, err = Bo.boosters(two_j, dl, 1.2)
+    note(f"booster tiles {two_j} dl={dl}")
+    _check(lib, two_j, dl, ref)
