@@ -151,6 +151,32 @@ struct BatchJob {
   int first, index;
 };
 
+// Division of 32-bit indices by a divisor that is the same for the whole launch: floor(n m / 2^32) with
+// m = floor((2^32 - 1) / d) is the quotient or one less.
+struct IndexDiv {
+  uint32_t m = 0, d = 1;
+  __host__ __device__ IndexDiv() {}
+  __host__ __device__ explicit IndexDiv(int d_) : m(0xffffffffu / (uint32_t)d_), d((uint32_t)d_) {}
+#ifdef __HIPCC__
+  // r becomes r / d; returns the remainder.
+  __device__ __forceinline__ int take(uint32_t &r) const {
+    uint32_t q = __umulhi(r, m), rest = r - q * d;
+    if (rest >= d) {
+      ++q;
+      rest -= d;
+    }
+    r = q;
+    return (int)rest;
+  }
+  // (indices past 32 bits)
+  __device__ __forceinline__ int take(int64_t &r) const {
+    const int rest = (int)(r % d);
+    r /= d;
+    return rest;
+  }
+#endif
+};
+
 #ifdef __HIPCC__
 // The job of block b (the last whose first block is not past it); b becomes the block within the job.
 __device__ __forceinline__ int batch_job(const BatchJob *jobs, int njobs, int &b) {
@@ -243,6 +269,7 @@ struct ContractParams {
   const double *psi[5];
   double *partial;  // complex partial sums
   int nblocks;
+  IndexDiv by[5];   // by n (set by the launchers)
 };
 struct GradPsiOut {
   double *p[5];
@@ -335,6 +362,7 @@ struct TrailParams {
   int nsplit;             // blocks per leading row
   double *T;              // complex [lead]
   double *partial;        // complex [lead][nsplit] when nsplit > 1
+  IndexDiv by[5];         // by n (set by the launcher)
 };
 hipError_t launch_contract_vertices(const double *A, const double *B, int64_t total, int nblocks,
                                     double *partial, double *F, hipStream_t s);

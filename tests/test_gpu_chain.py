@@ -95,3 +95,22 @@ def test_batch_follows_its_buffers(lib, torch, shape):
             out = lib.vertex_tensor_batched(shape, 1.2, sets[k])
         for a, p in zip(out, plain[k]):
             assert torch.equal(a, p)
+
+
+# Index arithmetic of the contractions at its edges: dimensions of one, powers of two, primes, and one
+# past 2^16.  A complex product is within sqrt(8) 2^-53, so either side's sum of N products of up to six
+# factors is within (N + 15) 2^-53 of the sum of their moduli.
+@pytest.mark.parametrize("dims", [(1, 1, 1, 1, 1), (3, 5, 7, 2, 11), (16, 8, 1, 4, 32), (1, 2, 65537, 1, 3), (13, 1, 1, 17, 1)])
+def test_contraction_indices(lib, torch, dims):
+    gen = torch.Generator().manual_seed(sum(dims))
+    a = torch.randn(dims, dtype=torch.float64, generator=gen)
+    psi = [torch.randn(n, dtype=torch.complex128, generator=gen) for n in dims]
+    print("contraction", dims, flush=True)
+    ad, pd = a.cuda(), [p.cuda() for p in psi]
+    for m in range(1, 6):
+        got = lib.contract_trailing(ad, pd[5 - m:]) if m < 5 else lib.contract_boundary(ad, pd)
+        ref, mod = a.to(torch.complex128), a.abs()
+        for p in reversed(psi[5 - m:]):
+            ref, mod = ref @ p, mod @ p.abs()
+        bound = (2 * int(np.prod(dims[5 - m:])) + 30) * 2.0 ** -53 * mod
+        assert ((got.cpu().reshape(ref.shape) - ref).abs() <= bound).all()
