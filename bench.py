@@ -3,7 +3,7 @@
 One step = the whole hot path over the large-spin batch: 16 seeded irregular 4-simplices with
 spins j in {5, 5.5, 6, 6.5, 7}, dl = 6 (intertwiner dimensions 10..14, 4.9e11 {15j} x booster
 terms), gamma = 1.2: the 16 vertex tensors in one batched call (6j tables, the factorised shell
-sum in one persistent launch, reductions and normalisation, replayed from a captured graph),
+sum, reductions and normalisation),
 then for every configuration the boundary contraction with five seeded unit complex vectors and
 its adjoint (gradients with respect to the vectors and to every booster entry).  Inputs
 (seeded synthetic boosters of the exact packed shape) are resident in HBM before the timed
@@ -11,7 +11,7 @@ region.
 
 Prints one JSON line:
   value        {15j} x booster terms of the 16 vertex tensors per second of step
-  roofline     the persistent factorised kernel: its useful FP64 flops (exact count of the
+  roofline     the factorised kernel: its useful FP64 flops (exact count of the
                multiply-adds its active index ranges need) per launch divided by its average
                launch duration (HIP events on the library's stream, from a second pass that
                enqueues the batch's launches directly), against the MI355X FP64 peak
@@ -229,7 +229,7 @@ def irregular_batch(lib, torch, dev, reps):
         for c, (tj, d) in enumerate(configs)]
     terms = sum(lib.count_terms(tj, d)[1] for tj, d in configs)
     outs = [torch.empty(lib.layout(tj, d)[0], dtype=torch.float64, device=dev) for tj, d in configs]
-    # First call of a new batch shape: planning, schedules, metadata upload, graph capture and
+    # First call of a new batch shape: planning, schedules, metadata upload and
     # the run itself (host wall clock).
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -431,14 +431,14 @@ def main():
     step_ms = [ev[k].elapsed_time(ev[k + 1]) for k in range(args.steps)]
     ms = ev[0].elapsed_time(ev[-1]) / args.steps
     progress(f"step {ms:.1f} ms (median {statistics.median(step_ms):.1f})")
-    # Forward only, batched graph vs plain calls.
+    # Forward only, batched vs plain calls.
     fb = event_times(torch, lb.forward_batched, 5)
     fp = event_times(torch, lb.forward_plain, 5)
     fa = event_times(torch, lb.adjoint, 3)
     progress(f"forward batched {statistics.median(fb):.1f} ms, plain {statistics.median(fp):.1f} ms, "
              f"contraction + adjoint {statistics.median(fa):.1f} ms")
-    # Second pass with the library's per-launch events on (the batch then enqueues its launches
-    # directly instead of replaying the graph).
+    # Second pass with the library's per-launch events on (the batch then runs its launches
+    # one after the other).
     lib.timing_enable(True)
     for _ in range(3):
         lb.forward_batched()
@@ -457,9 +457,9 @@ def main():
     kernel_ms = kms / max(kn, 1)
     alg_per_launch = useful / max(launches, 1.0)
     achieved = alg_per_launch / (kernel_ms * 1e-3) / 1e12
-    # Every configuration of this batch takes the all-matrix-core factorised kernel (class 8)
-    # unless the planner picked otherwise; the roofline names the kernel that ran.
-    kname, ksrc = ("wide_batch_kernel", "wide.hip") if classes == [8] else ("ring_batch_kernel", "ring.hip")
+    # Every configuration of this batch takes the x-outer factorised kernel (class 8) unless the
+    # planner picked otherwise; the roofline names the kernel that ran.
+    kname, ksrc = ("chain_kernel", "chain.hip") if classes == [8] else ("ring_batch_kernel", "ring.hip")
     progress(f"{kname} {kernel_ms:.2f} ms per launch ({launches:g} launches per step): "
              f"{achieved:.2f} TFLOP/s useful")
 
@@ -483,8 +483,8 @@ def main():
                                "boundary contraction and adjoint of each",
                    "configs": [{"two_j": tj, "dl": d} for tj, d in lb.configs],
                    "terms": lb.terms, "tile_classes": classes,
-                   "algorithm": "factorised shell sum (ring), FP64 matrix-core contractions, one "
-                                "persistent launch per tile class in a captured graph"},
+                   "algorithm": "factorised shell sum (ring), x outside the virtual spins, FP64 "
+                                "matrix-core contractions, one launch per kernel variant"},
         "step_spread": spread(step_ms),
         "batched_vs_plain": {"forward_batched": spread(fb), "forward_plain": spread(fp),
                              "batched_terms_per_s": lb.terms / (statistics.median(fb) * 1e-3),

@@ -81,7 +81,8 @@ int eprl_set_stream(eprl_ctx *ctx, void *hip_stream);
  *  EPRL_ALGO_AUTO   (default) RING where it applies, SHELL otherwise;
  *  EPRL_ALGO_RING_VALU  RING restricted to the kernels that take the l45 / l23 half chains on
  *                   vector ALUs (tile classes 0..7): for boundary dimensions above 8 RING
- *                   otherwise runs every stage on matrix-core tiles (class 8); kept as a
+ *                   otherwise reports class 8 (RING itself takes x outside the virtual spins
+ *                   and runs every product on the matrix cores, for all classes); kept as a
  *                   cross-check and for shell counts above 11 (EPRL_ERANGE where neither
  *                   applies).  Same sum, results agree to rounding. */
 #define EPRL_ALGO_AUTO 0
@@ -91,8 +92,9 @@ int eprl_set_stream(eprl_ctx *ctx, void *hip_stream);
 int eprl_set_algorithm(eprl_ctx *ctx, int algo);
 
 /* Work split of the factorised order per tile class (the class is out[4] of eprl_count_work):
- * the shell sum is cut into chunks of cores of equal estimated cost, about target_workgroups
- * workgroups per launch (0: the default, 8192), and staging_level picks how many booster blocks
+ * the shell sum is cut into chunks of equal estimated cost, about target_workgroups
+ * workgroups per launch (0: the default, 6144 for the kernel with x outside the virtual spins,
+ * 8192 for the others), and, for the others, staging_level picks how many booster blocks
  * of a core are held in LDS (2: all four, 1: the two of the second stage, 0: none, -1: the
  * most that fits; a level that does not fit falls back to the next lower one).  The paper
  * adapts the split of its loops to the machine in the same spirit (Sec. 3.1,
@@ -133,7 +135,7 @@ int eprl_count_terms(const int two_j[10], int dl, int64_t *live_shells, double *
  *            + 6 per (term, allowed x) for the {15j} sums;
  *   out[2] = useful FP64 flops of the factorised order (active index ranges only);
  *   out[3] = FP64 flops its matrix-core tiles execute (16x16x4 tiles, padding included);
- *   out[4] = tile class of the factorised kernel for this configuration (0..7), or -1 when
+ *   out[4] = tile class of the factorised kernel for this configuration (0..8), or -1 when
  *            the configuration falls back to the per-shell order. */
 int eprl_count_work(const int two_j[10], int dl, double out[5]);
 
@@ -181,10 +183,10 @@ int eprl_vertex_tensor_cores(eprl_ctx *ctx, const int two_j[10], int dl, double 
                              int accumulate, double *A);
 
 /* n independent vertex tensors (configuration c: two_j[10 c .. 10 c + 9], dl[c],
- * boosters[c], A[c]); the host arrays of pointers hold device pointers.  The 6j tables, one
- * persistent launch per tile class over a longest-first work queue of all configurations and
- * the reductions are captured into a HIP graph, replayed while the configurations, pointers
- * and algorithm are unchanged.  Results are bitwise equal to n calls of eprl_vertex_tensor. */
+ * boosters[c], A[c]); the host arrays of pointers hold device pointers.  One launch builds
+ * the 6j tables of all configurations, one per kernel variant takes their work items longest
+ * first, one reduces; the layout is kept while the configurations and the algorithm stay the
+ * same (boosters and A may change freely).  Not capturable (EPRL_EHIP).  Results are bitwise equal to n calls of eprl_vertex_tensor. */
 int eprl_vertex_tensor_batched(eprl_ctx *ctx, int n, const int *two_j, const int *dl,
                                double gamma, const double *const *boosters, double *const *A);
 
@@ -193,8 +195,7 @@ int eprl_vertex_tensor_batched(eprl_ctx *ctx, int n, const int *two_j, const int
  * A(dl) = A(dl - 1) + the shells whose largest offset is dl).  boosters: device, packed for
  * dl_max (eprl_layout(two_j, dl_max)); each A(dl) reads the blocks of its own shells from it.
  * A: device, (dl_max + 1) prod(dims_i) doubles, A(dl) at offset dl prod(dims_i), overwritten.
- * The dl_max + 1 tensors run as one batch (one graph of table builds, persistent launches and
- * reductions; see eprl_vertex_tensor_batched): every A(dl) has the bits of
+ * The dl_max + 1 tensors run as one batch (see eprl_vertex_tensor_batched): every A(dl) has the bits of
  * eprl_vertex_tensor(two_j, dl) on its own packed boosters.  Errors as eprl_vertex_tensor. */
 int eprl_vertex_tensor_scan(eprl_ctx *ctx, const int two_j[10], int dl_max, double gamma,
                             const double *boosters, double *A);
@@ -300,9 +301,9 @@ int eprl_shell_fifteenj(eprl_ctx *ctx, const int two_j[10], int dl, int64_t shel
 /* Per-kernel timing with HIP events recorded on the context's stream around each launch.
  * kernel ids: 0 = 6j table builder, 1 = per-shell vertex assembly, 2 = shell-sum reduction,
  * 3 = adjoint shell kernel, 4 = factorised (ring) vertex assembly, 5 = BF vertex,
- * 6 = persistent factorised assembly of a batch (one launch per tile class).  While timing is
- * on, eprl_vertex_tensor_batched enqueues its launch sequence directly instead of replaying
- * the captured graph (same kernels, same results), so that each launch can be bracketed.
+ * 6 = factorised assembly of a batch (one launch per kernel variant).  While timing is
+ * on, eprl_vertex_tensor_batched runs its launches one after the other on the context's stream
+ * instead of on several (same kernels, same results), so that each launch can be bracketed.
  * eprl_timing_enable(ctx, 1) starts recording (clearing earlier records), 0 stops.
  * eprl_timing_read synchronises the stream and returns the summed duration in milliseconds and
  * the number of launches recorded for `kernel`. */

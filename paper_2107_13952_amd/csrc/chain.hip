@@ -27,12 +27,15 @@
 //   * the update, one matrix-core step per (four k3, column tile).
 // Operand entries past a window need no masks: k4 (k3) beyond a triad has a zero T row or a zero
 // booster entry, so G and H are zero there and meet finite values of U3.
-// What bounds it: at two_j = 6, 8 shells (7^5 outputs, 258 k steps) the matrix instructions of a
-// step take about a third of its time; the rest are LDS reads of T and of G, H (a 4 x 4 x 4 operand
-// serves one instruction), the two barriers and the scalar work per step, which two to three
-// workgroups per CU hide only in part.  Doubling G and H in LDS (one barrier per step) was no faster
-// (fewer workgroups fit).  Two row tiles per wavefront instead of one: 1800 against 1870 us for that
-// tensor, 6950 against 8360 us at two_j = 10, 6 shells (each H operand is read half as often).
+// What bounds it: at two_j = 6, 8 shells (7^5 outputs, 303 k steps over all i1) a call takes 1.43 ms
+// here (2.61 ms for the kernel with the half chains inside the core loop), at two_j = 10 .. 14, 6
+// shells 5.8 ms (12.3).  The matrix cores are busy 38 % of the cycles; a wavefront spends a third of
+// its time in waits (the LDS operands of the 4 x 4 products, U3, two barriers a step) and issues 230
+// scalar and 260 vector instructions a step around 52 matrix instructions.  The accumulators allow two
+// wavefronts per SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no
+// change, fewer workgroups fit), 16 x 16 tiles for G and H of large dimensions (5.8 -> 6.7 ms), row
+// blocks (each repeats H: 6.3 -> 11.0 ms for two), one wavefront per workgroup without barriers (1.43
+// -> 1.69 ms), rt = 1 (6.95 -> 8.36 ms: each H operand then serves one row tile).
 // Lane layout (lane l = 16 g + c, measured on the device): v_mfma_f64_16x16x4 operand A[c][g],
 // operand B[g][c], result register r = D[g + 4 r][c]; v_mfma_f64_4x4x4 block b = c >> 2, operand
 // A[c & 3][g], operand B[g][c & 3], result D[g][c & 3].
@@ -274,7 +277,10 @@ __host__ __device__ inline int chain_mrow(int nd, int dm) { return 4 * ((nd + 3)
 template <int RT, int CT, int KS>
 __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int n1, int cb, double *smem) {
   constexpr int SM = 8;                      // steps of four window positions
-  constexpr int NB = RT * CT >= 14 ? 2 : 4;  // instructions per T row group in a chunk (registers)
+  // Instructions per T row group in a chunk: more in flight, more registers (two everywhere: 1.36 -> 1.51
+  // ms at two_j = 6, 8 shells; four everywhere: spills from 14 accumulator tiles on, 6.78 -> 6.95 ms at
+  // two_j = 10 .. 14, 6 shells).
+  constexpr int NB = RT * CT >= 14 ? 2 : 4;
   const int tid = threadIdx.x, nthr = blockDim.x, nw = nthr >> 6;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, c = l & 15;
   const int nd = rp.nd, nx = rp.nx;
@@ -577,7 +583,9 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
 // Wavefronts per SIMD the registers are budgeted for, and the most wavefronts of a workgroup.
 template <int RT, int CT, int KS>
 constexpr int chain_waves() {
-  // accumulators and P; booster operands; U3, addresses, operands in flight
+  // Accumulators and P; booster operands; U3, addresses, operands in flight.  The last is what leaves no
+  // spills: 80 (one wavefront more for the small tiles) was slower, 244 against 205 us for spins 3 .. 12 / 2,
+  // 5 shells.
   constexpr int need = 8 * RT * CT + 8 * RT + (RT * CT >= 14 ? 12 : 24) * KS + 104;
   return need <= 128 ? 4 : need <= 176 ? 3 : 2;
 }

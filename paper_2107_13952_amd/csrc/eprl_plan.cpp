@@ -499,8 +499,8 @@ void count_work(const Plan &p, double out[5]) {
               const int s4 = ((b4 - w4lo) / 2) / 4 - ((a4 - w4lo) / 2) / 4 + 1;
               const int s3 = ((b3 - w3lo) / 2) / 4 - ((a3 - w3lo) / 2) / 4 + 1;
               if (p.chain) {
-                // 16x16x4 matrix-core steps (2048 flops each) of P and the update; T and G / H run
-                // on the vector ALUs.
+                // 16x16x4 matrix-core steps (2048 flops each) of P and the update; G and H run on
+                // 4x4x4 tiles and T5, T2 are made once, neither is counted.
                 const int RT = (d5 * d4 + 15) / 16, q4 = (na4 + 3) / 4, q3 = (na3 + 3) / 4;
                 executed += 2048.0 * RT * p.ch.nrb * ((q3 + 3) / 4 * q4 + p.ch.ctb * q3);
               } else {
