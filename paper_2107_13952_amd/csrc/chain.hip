@@ -27,14 +27,14 @@
 //   * the update, one matrix-core step per (four k3, column tile).
 // Operand entries past a window need no masks: k4 (k3) beyond a triad has a zero T row or a zero
 // booster entry, so G and H are zero there and meet finite values of U3.
-// What bounds it: at two_j = 6, 8 shells (7^5 outputs, 303 k steps over all i1) a call takes 1.43 ms
+// What bounds it: at two_j = 6, 8 shells (7^5 outputs, 303 k steps over all i1) a call takes 1.37 ms
 // here (2.61 ms for the kernel with the half chains inside the core loop), at two_j = 10 .. 14, 6
-// shells 5.8 ms (12.3).  The matrix cores are busy 38 % of the cycles; a wavefront spends a third of
+// shells 5.35 ms (12.3).  The matrix cores are busy 38 % of the cycles; a wavefront spends a third of
 // its time in waits (the LDS operands of the 4 x 4 products, U3, two barriers a step) and issues 230
 // scalar and 260 vector instructions a step around 52 matrix instructions.  The accumulators allow two
 // wavefronts per SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no
-// change, fewer workgroups fit), 16 x 16 tiles for G and H of large dimensions (5.8 -> 6.7 ms), row
-// blocks (each repeats H: 6.3 -> 11.0 ms for two), one wavefront per workgroup without barriers (1.43
+// change, fewer workgroups fit), 16 x 16 tiles for G and H of large dimensions (6.3 -> 6.7 ms), row
+// blocks (each repeats H: 6.3 -> 11.0 ms for two), one wavefront per workgroup without barriers (1.49
 // -> 1.69 ms), rt = 1 (6.95 -> 8.36 ms: each H operand then serves one row tile).
 // Lane layout (lane l = 16 g + c, measured on the device): v_mfma_f64_16x16x4 operand A[c][g],
 // operand B[g][c], result register r = D[g + 4 r][c]; v_mfma_f64_4x4x4 block b = c >> 2, operand
@@ -281,6 +281,7 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
   // ms at two_j = 6, 8 shells; four everywhere: spills from 14 accumulator tiles on, 6.78 -> 6.95 ms at
   // two_j = 10 .. 14, 6 shells).
   constexpr int NB = RT * CT >= 14 ? 2 : 4;
+  constexpr int HG = RT * CT >= 18 ? 2 : 4;  // columns of H in flight (registers)
   const int tid = threadIdx.x, nthr = blockDim.x, nw = nthr >> 6;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4, c = l & 15;
   const int nd = rp.nd, nx = rp.nx;
@@ -440,12 +441,14 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
     if (w < chunks(sg, st.n4)) load_m(sg, st.m4, w, mg);
     if (nw - 1 - w < chunks(sh, st.n3)) load_m(sh, st.m3, nw - 1 - w, mh);
   };
-  double u3[SM];  // of the first 16 k3
+  // U3 of the first 16 k4 and k3; the rest, rare, is read where it is used (all 32 k4 a step ahead
+  // spilled: 5.8 -> 5.35 ms at two_j = 10 .. 14, 6 shells).
+  double u3[SM / 2];
   const uint32_t uo = g * nK3 + c;
   auto load_u3 = [&](const ChainStep &st, int k3) {
     const double *base = U3 + st.u3 + k3;
 #pragma unroll
-    for (int s = 0; s < SM; ++s) {
+    for (int s = 0; s < SM / 2; ++s) {
       if (4 * s >= st.n4) break;
       u3[s] = ldg_at(base, uo + 4 * s * nK3);
     }
@@ -521,14 +524,22 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
 #pragma unroll
         for (int s = 0; s < SM / 2; ++s) {
           if (2 * s >= s4) break;
+          double ua, ub;
+          if (s < SM / 4) {
+            ua = u3[2 * s];
+            ub = u3[2 * s + 1];
+          } else {
+            ua = ldg_at(U3 + st.u3 + k3, uo + 8 * s * nK3);
+            ub = ldg_at(U3 + st.u3 + k3, uo + (2 * s + 1 < s4 ? 8 * s + 4 : 8 * s) * nK3);
+          }
           d2v gv[RT];
 #pragma unroll
           for (int r = 0; r < RT; ++r) gv[r] = gp[s * 4 * R + r * 16];
 #pragma unroll
-          for (int r = 0; r < RT; ++r) pt[r] = mfma(u3[2 * s], gv[r].x, pt[r]);
+          for (int r = 0; r < RT; ++r) pt[r] = mfma(ua, gv[r].x, pt[r]);
           if (2 * s + 1 >= s4) break;
 #pragma unroll
-          for (int r = 0; r < RT; ++r) pt[r] = mfma(u3[2 * s + 1], gv[r].y, pt[r]);
+          for (int r = 0; r < RT; ++r) pt[r] = mfma(ub, gv[r].y, pt[r]);
         }
         const bool last = k3 + 16 >= st.n3;
         if (!last) load_u3(st, k3 + 16);
@@ -540,17 +551,17 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
           if (2 * s >= s3) break;
           const bool both = 2 * s + 1 < s3;
 #pragma unroll
-          for (int t0 = 0; t0 < CT; t0 += 4) {
-            d2v hv[4];
+          for (int t0 = 0; t0 < CT; t0 += HG) {
+            d2v hv[HG];
 #pragma unroll
-            for (int t = t0; t < t0 + 4 && t < CT; ++t) hv[t - t0] = hp[s * 4 * CW + t * 16];
+            for (int t = t0; t < t0 + HG && t < CT; ++t) hv[t - t0] = hp[s * 4 * CW + t * 16];
 #pragma unroll
-            for (int t = t0; t < t0 + 4 && t < CT; ++t)
+            for (int t = t0; t < t0 + HG && t < CT; ++t)
 #pragma unroll
               for (int r = 0; r < RT; ++r) acc[r][t] = mfma(pt[r][2 * s], hv[t - t0].x, acc[r][t]);
             if (both) {
 #pragma unroll
-              for (int t = t0; t < t0 + 4 && t < CT; ++t)
+              for (int t = t0; t < t0 + HG && t < CT; ++t)
 #pragma unroll
                 for (int r = 0; r < RT; ++r) acc[r][t] = mfma(pt[r][2 * s + 1], hv[t - t0].y, acc[r][t]);
             }
@@ -614,7 +625,9 @@ void chain_kernel(const RingParams *__restrict__ cfgs, const int *__restrict__ i
 }
 
 // Kernel variants: row tiles per wavefront, column tiles, groups of four spin values.
-constexpr int kChainCT = 10;  // most column tiles of a workgroup
+// Most column tiles of a workgroup: a second column block repeats G; past ten tiles the registers spill
+// (16 large configurations, up to eleven tiles: 189, 169, 161, 159 ms with at most 8, 9, 10, 11).
+constexpr int kChainCT = 11;
 constexpr int chain_key(int rt, int ct, int ks) { return ((rt - 1) * 16 + ct) * 4 + ks - 1; }
 constexpr int kChainKeys = 2 * 64;
 
@@ -626,7 +639,7 @@ hipError_t chain_dispatch(int key, F &&f) {
   EPRL_K(1, c, 1) EPRL_K(1, c, 2) EPRL_K(1, c, 3) EPRL_K(1, c, 4) \
   EPRL_K(2, c, 1) EPRL_K(2, c, 2) EPRL_K(2, c, 3) EPRL_K(2, c, 4)
   switch (key) {
-    EPRL_C(1) EPRL_C(2) EPRL_C(3) EPRL_C(4) EPRL_C(5) EPRL_C(6) EPRL_C(7) EPRL_C(8) EPRL_C(9) EPRL_C(10)
+    EPRL_C(1) EPRL_C(2) EPRL_C(3) EPRL_C(4) EPRL_C(5) EPRL_C(6) EPRL_C(7) EPRL_C(8) EPRL_C(9) EPRL_C(10) EPRL_C(11)
     default: return hipErrorInvalidValue;
   }
 #undef EPRL_K
