@@ -197,8 +197,6 @@ def plain_j3(lib, torch, dev, synthetic, autotune, steps):
     terms = lib.count_terms(two_j, dl)[1]
     work = lib.count_work(two_j, dl)
     tuned = lib.autotune(two_j, dl, b, out) if autotune else None
-    # (target workgroups, staging level) of the work split the timed calls use
-    split = (tuned["target_workgroups"], tuned["staging_level"]) if tuned else (8192, 2)
     ms = event_times(torch, lambda: lib.vertex_tensor(two_j, dl, 1.2, b, out=out), steps, 3)
     lib.timing_enable(True)
     for _ in range(steps):
@@ -216,9 +214,8 @@ def plain_j3(lib, torch, dev, synthetic, autotune, steps):
                             "achieved_tflops": work["ring_useful_flops"] / (ring_ms * 1e-3) / 1e12,
                             "frac": work["ring_useful_flops"] / (ring_ms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS,
                             "mfma_executed_tflops": work["ring_mfma_flops"] / (ring_ms * 1e-3) / 1e12,
-                            "traffic": measured_traffic("ring_kernel_j3_dl8_counters.md",
-                                                        "traffic bytes per launch, split "
-                                                        f"{split[0]} {split[1]}", "ring.hip")}}
+                            "traffic": measured_traffic("chain_kernel_j3_dl8_counters.md",
+                                                        "traffic bytes per launch", "chain.hip")}}
 
 
 def irregular_batch(lib, torch, dev, reps):
