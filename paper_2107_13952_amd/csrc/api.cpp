@@ -87,8 +87,8 @@ struct eprl_ctx {
   // Recorded on the old stream when the context moves to another one, which then waits for it:
   // work enqueued earlier still uses the workspace that later calls reuse.
   hipEvent_t handoff = nullptr;
-  // factorial prime-exponent table (device), valid for arguments <= fact_max
-  double4 *fact = nullptr;  // factorial table, its exponents behind it
+  // factorial table (device), valid for arguments <= fact_max
+  double4 *fact = nullptr;  // its exponents behind it
   int fact_max = -1;
   FactTables ft;
   // algorithm: EPRL_ALGO_AUTO, EPRL_ALGO_SHELL or EPRL_ALGO_RING
@@ -246,21 +246,26 @@ int upload(eprl_ctx *c, void *dst, size_t bytes) {
   return EPRL_OK;
 }
 
+// The factorial table for arguments up to fact_max, in c->ft.  The old one stays until a larger one is
+// in place: the layout of a batch relies on a table at least as large as the one it was made with.
 int ensure_fact(eprl_ctx *c, int fact_max) {
   if (fact_max <= c->fact_max) return EPRL_OK;
   fact_max = std::max(fact_max, 256);
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  if (c->fact) HIP_TRY(c, hipFree(c->fact));
-  c->fact = nullptr;
-  c->fact_max = -1;
-  if (hipMalloc(&c->fact, (size_t)(fact_max + 1) * (sizeof(double4) + sizeof(int))) != hipSuccess) {
+  HIP_TRY(c, hipStreamSynchronize(c->stream));  // (earlier work reads the old table)
+  double4 *f = nullptr;
+  if (hipMalloc(&f, (size_t)(fact_max + 1) * (sizeof(double4) + sizeof(int))) != hipSuccess) {
     (void)hipGetLastError();
-    c->fact = nullptr;
     return fail(c, EPRL_ENOMEM, "factorial table allocation failed");
   }
-  int *exps = reinterpret_cast<int *>(c->fact + fact_max + 1);
-  HIP_TRY(c, launch_fact_table(c->fact, exps, fact_max, c->stream));
-  c->ft.f = c->fact;
+  int *exps = reinterpret_cast<int *>(f + fact_max + 1);
+  hipError_t e = launch_fact_table(f, exps, fact_max, c->stream);
+  if (e != hipSuccess) {
+    (void)hipFree(f);
+    return hip_fail(c, e, "factorial table");
+  }
+  if (c->fact) (void)hipFree(c->fact);
+  c->fact = f;
+  c->ft.f = f;
   c->ft.e = exps;
   c->fact_max = fact_max;
   return EPRL_OK;

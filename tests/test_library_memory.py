@@ -1,0 +1,97 @@
+"""The library's handling of device memory that runs out, on the CPU: its host code runs against a
+runtime without a device (hip_stub.c) whose memory the test bounds.  Each scenario in a process of its
+own, the stub loaded before the library."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+LIB = os.path.join(ROOT, "paper_2107_13952_amd", "libeprl.so")
+OK, ENOMEM, EHIP = 0, -2, -3
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-o", out,
+                    os.path.join(HERE, "hip_stub.c")], check=True)
+    return out
+
+
+class Library:
+    """The library over the stub: one context, calls with buffers of the stub's memory."""
+
+    def __init__(self, path):
+        self.stub = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)
+        for name in ("stub_live", "stub_peak"):
+            getattr(self.stub, name).restype = ctypes.c_size_t
+        self.stub.stub_limit.argtypes = [ctypes.c_size_t]
+        self.lib = ctypes.CDLL(LIB)
+        self.ctx = self.context()
+        self.buf = ctypes.c_void_p()
+        assert self.stub.hipMalloc(ctypes.byref(self.buf), ctypes.c_size_t(1 << 20)) == 0
+        self.stub.stub_peak()
+
+    def context(self):
+        ctx = ctypes.c_void_p()
+        assert self.lib.eprl_create(ctypes.byref(ctx), 0, None) == 0
+        return ctx
+
+    def launches(self, name):
+        return self.stub.stub_launches(name.encode())
+
+    def vertex(self, two_j, dl, ctx=None):
+        return self.lib.eprl_vertex_tensor(ctx or self.ctx, (ctypes.c_int * 10)(*two_j), dl, ctypes.c_double(1.2),
+                                           self.buf, self.buf)
+
+    def batch(self, configs, ctx=None):
+        n = len(configs)
+        js = (ctypes.c_int * (10 * n))(*[s for two_j, _ in configs for s in two_j])
+        dls = (ctypes.c_int * n)(*[dl for _, dl in configs])
+        ptrs = (ctypes.c_void_p * n)(*[self.buf.value] * n)
+        return self.lib.eprl_vertex_tensor_batched(ctx or self.ctx, n, js, dls, ctypes.c_double(1.2), ptrs, ptrs)
+
+    def sixj(self, two_j):
+        return self.lib.eprl_sixj_batch(self.ctx, 1, (ctypes.c_int * 6)(*[two_j] * 6), self.buf)
+
+
+SMALL = [([2] * 10, 2), ([4, 4, 5, 3, 5, 5, 6, 4, 3, 6], 1)]
+
+
+# A table of factorials that cannot grow leaves the old one in place: the batch laid out with it runs
+# on, and never with the address of freed memory.
+def factorial_table_stays_when_it_cannot_grow(lib):
+    for how in ("memory", "launch"):
+        assert lib.batch(SMALL) == OK
+        if how == "memory":
+            lib.stub.stub_limit(lib.stub.stub_live())
+            assert lib.sixj(200) == ENOMEM
+            lib.stub.stub_limit(1 << 40)
+        else:
+            lib.stub.stub_fail(b"fact_kernel")
+            assert lib.sixj(200) == EHIP
+            lib.stub.stub_fail(None)
+        assert lib.batch(SMALL) == OK
+        assert lib.vertex(*SMALL[1]) == OK
+        assert lib.stub.stub_stale() == 0
+    assert lib.sixj(200) == OK
+    assert lib.batch(SMALL) == OK
+    assert lib.stub.stub_stale() == 0
+
+
+SCENARIOS = [factorial_table_stays_when_it_cannot_grow]
+
+
+@pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
+def test_memory(stub, scenario):
+    res = subprocess.run([sys.executable, os.path.abspath(__file__), stub, scenario], capture_output=True, text=True,
+                         timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]](Library(sys.argv[1]))
