@@ -57,8 +57,8 @@ extern "C" {
 typedef struct eprl_ctx eprl_ctx;
 
 /* Create a context bound to HIP device `device` and stream `hip_stream` (a hipStream_t; NULL
- * means the null stream).  The context owns a grow-only device workspace (6j tables,
- * per-chunk partial sums) that is freed by eprl_destroy.  Returns EPRL_EHIP when the device
+ * means the null stream).  The context owns a grow-only device workspace (6j tables, tables
+ * derived from them and the boosters, per-chunk partial sums) that is freed by eprl_destroy.  Returns EPRL_EHIP when the device
  * cannot be selected. */
 int eprl_create(eprl_ctx **out, int device, void *hip_stream);
 void eprl_destroy(eprl_ctx *ctx);
@@ -147,7 +147,10 @@ int eprl_count_work(const int two_j[10], int dl, double out[5]);
  *   A         device, prod(dims_i) doubles, overwritten
  *   gamma     the Barbero-Immirzi parameter the boosters were computed with; it enters A only
  *             through the boosters and is checked to be finite and positive.
- * The shell sum is evaluated in a fixed order: repeated calls give bitwise identical A. */
+ * The shell sum is evaluated in a fixed order: repeated calls give bitwise identical A.  The derived
+ * tables can take several times the memory of the 6j tables (0.1 GB at all spins 3, eight shells,
+ * 2.5 GB at all spins 7, ten shells); where they do not fit, the kernels of EPRL_ALGO_RING_VALU, which
+ * need none, take the call (the same sum in another order). */
 int eprl_vertex_tensor(eprl_ctx *ctx, const int two_j[10], int dl, double gamma,
                        const double *boosters, double *A);
 

@@ -450,8 +450,16 @@ size_t chain_derived_bytes(const Plan &p) {
   return (size_t)(p.ch.t5 + p.ch.t2 + p.ch.m4 + p.ch.m3 + p.ch.steps) * sizeof(double);
 }
 
+// The configuration evaluated by ring.hip's kernels, which need no derived tables.
+Plan without_chain(const Plan &p) {
+  Plan q = p;
+  q.ring_cls = q.ring_cls8;
+  q.chain = false;
+  return q;
+}
+
 // x-outer evaluation over the cores [core_lo, core_hi) (core_hi < 0: all cores): the derived tables,
-// one workgroup per (chunk, i1, row block), then the reduction.
+// one workgroup per (chunk, i1, column block), then the reduction.
 int chain_impl(eprl_ctx *c, const int two_j[10], int dl, const double *B, int accumulate, double *A,
                const Plan &p, int nchunk, int core_lo, int core_hi) {
   const size_t rbytes = align_up(sizeof(RingParams), 256), dbytes = align_up(chain_derived_bytes(p), 256);
@@ -508,7 +516,12 @@ int ring_impl(eprl_ctx *c, const int two_j[10], int dl, const double *B, int acc
   }
   const std::vector<int> &bounds = c->sched_bounds;
   const int nchunk = c->sched_nchunk;
-  if (probe.chain) return chain_impl(c, two_j, dl, B, accumulate, A, probe, nchunk, core_lo, core_hi);
+  if (probe.chain) {
+    const int rc = chain_impl(c, two_j, dl, B, accumulate, A, probe, nchunk, core_lo, core_hi);
+    // Derived tables that do not fit in what is left of the memory (2.5 GB at all spins 7, ten shells,
+    // where the 6j tables take 0.25 GB): the kernels without them.
+    return rc == EPRL_ENOMEM ? ring_impl(c, two_j, dl, B, accumulate, A, without_chain(probe), core_lo, core_hi) : rc;
+  }
   const size_t pbytes = align_up((size_t)nchunk * probe.a_size * sizeof(double), 256);
   Prepared prep;
   int rc = prepare(c, two_j, dl, pbytes, prep, true, &bounds, &probe);
@@ -550,12 +563,8 @@ int vertex_range_impl(eprl_ctx *c, const int two_j[10], int dl, double gamma, co
                 "the factorised path needs the full shell range, i and k ranges <= 16 and core "
                 "windows <= 32");
   if (full && c->algo != EPRL_ALGO_SHELL && probe.ring_KW != 0) {
-    if (c->algo == EPRL_ALGO_RING_VALU && probe.chain) {
-      Plan q = probe;
-      q.ring_cls = q.ring_cls8;
-      q.chain = false;
-      return ring_impl(c, two_j, dl, B, accumulate, A, q);
-    }
+    if (c->algo == EPRL_ALGO_RING_VALU && probe.chain)
+      return ring_impl(c, two_j, dl, B, accumulate, A, without_chain(probe));
     return ring_impl(c, two_j, dl, B, accumulate, A, probe);
   }
   const int64_t nrange = std::max<int64_t>(se - sb, 1);
@@ -612,12 +621,8 @@ int vertex_cores_impl(eprl_ctx *c, const int two_j[10], int dl, double gamma, co
   if (probe.ring_KW == 0)
     return fail(c, EPRL_ERANGE,
                 "the factorised path needs i and k ranges <= 16 and core windows <= 32");
-  if (c->algo == EPRL_ALGO_RING_VALU && probe.chain) {
-    Plan q = probe;
-    q.ring_cls = q.ring_cls8;
-    q.chain = false;
-    return ring_impl(c, two_j, dl, B, accumulate, A, q, (int)cb, (int)ce);
-  }
+  if (c->algo == EPRL_ALGO_RING_VALU && probe.chain)
+    return ring_impl(c, two_j, dl, B, accumulate, A, without_chain(probe), (int)cb, (int)ce);
   return ring_impl(c, two_j, dl, B, accumulate, A, probe, (int)cb, (int)ce);
 }
 

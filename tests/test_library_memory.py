@@ -83,7 +83,47 @@ def factorial_table_stays_when_it_cannot_grow(lib):
     assert lib.stub.stub_stale() == 0
 
 
-SCENARIOS = [factorial_table_stays_when_it_cannot_grow]
+RING_VALU = 3
+# Spins, dl: 8-wide tiles, 16-wide tiles.
+LARGE = [([6] * 10, 8), ([13, 10, 11, 12, 10, 14, 11, 13, 13, 10], 6)]
+
+
+def needed(lib, call, algorithm):
+    """Device memory that `call` takes on a fresh context."""
+    ctx = lib.context()
+    assert lib.lib.eprl_set_algorithm(ctx, algorithm) == OK
+    before = lib.stub.stub_live()
+    lib.stub.stub_peak()
+    assert call(ctx) == OK
+    need = lib.stub.stub_peak() - before
+    lib.lib.eprl_destroy(ctx)
+    return need
+
+
+# Memory for the kernels without derived tables, and no more, is enough for a vertex tensor and for a
+# core range; with memory the x-outer kernel takes over again.
+def vertex_runs_without_memory_for_derived_tables(lib):
+    for two_j, dl in LARGE:
+        def cores(ctx):
+            return lib.lib.eprl_vertex_tensor_cores(ctx, (ctypes.c_int * 10)(*two_j), dl, ctypes.c_double(1.2), lib.buf,
+                                                    ctypes.c_int64(0), ctypes.c_int64((dl + 1) ** 3), 0, lib.buf)
+        for call in (lambda ctx: lib.vertex(two_j, dl, ctx), cores):
+            need = needed(lib, call, RING_VALU)
+            assert needed(lib, call, 0) > need
+            ctx = lib.context()
+            lib.stub.stub_limit(lib.stub.stub_live() + need)
+            for _ in range(2):
+                lib.stub.stub_clear()
+                assert call(ctx) == OK
+                assert lib.launches("chain_kernel") == 0 and lib.launches("ring_kernel") == 1
+            lib.stub.stub_limit(1 << 40)
+            lib.stub.stub_clear()
+            assert call(ctx) == OK
+            assert lib.launches("chain_kernel") == 1 and lib.launches("ring_kernel") == 0
+            lib.lib.eprl_destroy(ctx)
+
+
+SCENARIOS = [vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
