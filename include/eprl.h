@@ -189,7 +189,11 @@ int eprl_vertex_tensor_cores(eprl_ctx *ctx, const int two_j[10], int dl, double 
  * boosters[c], A[c]); the host arrays of pointers hold device pointers.  One launch builds
  * the 6j tables of all configurations, one per kernel variant takes their work items longest
  * first, one reduces; the layout is kept while the configurations and the algorithm stay the
- * same (boosters and A may change freely).  Not capturable (EPRL_EHIP).  Results are bitwise equal to n calls of eprl_vertex_tensor. */
+ * same (boosters and A may change freely).  Not capturable (EPRL_EHIP).  The workspace holds the 6j
+ * tables and partial sums of all configurations and up to 8 GiB of derived tables; a batch that needs
+ * more of those, or finds less memory, takes its configurations in several passes, and with no memory
+ * for any the kernels of EPRL_ALGO_RING_VALU.  Except for that last case, results are bitwise equal to
+ * n calls of eprl_vertex_tensor. */
 int eprl_vertex_tensor_batched(eprl_ctx *ctx, int n, const int *two_j, const int *dl,
                                double gamma, const double *const *boosters, double *const *A);
 

@@ -60,6 +60,11 @@ struct BatchSeq {
   size_t items_off = 0, jobs_off = 0, counters_off = 0, dyn_off = 0, tables_off = 0, reduce_off = 0, dyn_end = 0;
 };
 
+// Most memory the derived tables of a batch's x-outer configurations take at a time (a pass; kept for
+// the context's life).  More passes cost little: 16 large configurations, 4.7 GB, in one pass 159.2 ms, in
+// three 159.5, in sixteen 161.8; 64 irregular ones, 2.3 GB, in one 34.6, in three 35.1, in five 35.4.
+constexpr size_t kDerivedBytes = size_t(8) << 30;
+
 // Streams beside the context's on which a batch's groups run concurrently (all at the default
 // priority).
 constexpr int kBatchSide = 3;
@@ -118,6 +123,7 @@ struct eprl_ctx {
     std::vector<int64_t> key;  // empty: no layout
     char *ws = nullptr;
     size_t ws_size = 0;
+    size_t derived = kDerivedBytes;  // of a pass
     hipStream_t side[kBatchSide] = {};
     hipEvent_t fork = nullptr, join[kBatchSide] = {};
     BatchSeq seq;
@@ -702,10 +708,6 @@ void booster_r_nodes(int n, const std::vector<double> (&gx)[2], const std::vecto
 // again, host work of 39 ms for 64 irregular configurations.)  Chunking per configuration equals the
 // single-configuration path, so every tensor is bitwise identical to a separate eprl_vertex_tensor call.
 
-
-// Most memory the derived tables of a batch's x-outer configurations take at a time.
-constexpr size_t kDerivedBytes = size_t(24) << 30;
-
 int batch_chunks(const Plan &p, bool ring, int target_wg, int &nchunk, int64_t &chunk,
                  std::vector<int> &bounds, std::vector<double> &ccost) {
   if (ring) {
@@ -874,33 +876,14 @@ int run_batch(eprl_ctx *c, const double *const *boosters, double *const *A, char
   return EPRL_OK;
 }
 
-// layout_dl (may be null): configuration q reads its boosters from a buffer packed for
-// layout_dl[q] >= dl[q] shells per link (the blocks of its own spins found by their offsets in
-// that larger layout).
-int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
-                 const double *const *boosters, double *const *A, const int *layout_dl = nullptr) {
-  std::vector<int64_t> key;
-  key.push_back(n);
-  key.push_back(c->algo);
-  key.push_back(layout_dl != nullptr);
-  if (layout_dl)
-    for (int q = 0; q < n; ++q) key.push_back(layout_dl[q]);
-  for (int q = 0; q < kRingClasses; ++q) {
-    key.push_back(c->tune_wg[q]);
-    key.push_back(c->tune_stg[q]);
-  }
-  for (int q = 0; q < n; ++q) {
-    for (int t = 0; t < 10; ++t) key.push_back(two_j[10 * q + t]);
-    key.push_back(dl[q]);
-    if (!boosters[q] || !A[q]) return fail(c, EPRL_EINVAL, "null booster or output pointer");
-  }
-  // The call uploads from host buffers that are used again: it cannot become part of a graph.
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  hipError_t ec = hipStreamIsCapturing(c->stream, &capture);
-  if (ec != hipSuccess) return hip_fail(c, ec, "hipStreamIsCapturing");
-  if (capture != hipStreamCaptureStatusNone) return hip_fail(c, hipErrorStreamCaptureUnsupported, "batched call");
-  if (!c->batch.key.empty() && key == c->batch.key) return run_batch(c, boosters, A, nullptr, 0);
-  // New batch shape: plan every configuration and lay out the workspace.
+// Lays out a batch of a new shape and runs it.  derived: most bytes the derived tables of a pass take;
+// chain: false evaluates every factorised configuration by the kernels without derived tables.
+// *no_room, if the workspace could not be allocated: the derived tables' bytes in it.  layout_dl (may be null):
+// configuration q reads its boosters from a buffer packed for layout_dl[q] >= dl[q] shells per link (the
+// blocks of its own spins found by their offsets in that larger layout).
+int layout_batch(eprl_ctx *c, int n, const int *two_j, const int *dl, const double *const *boosters,
+                 double *const *A, const int *layout_dl, size_t derived, bool chain, int64_t *no_room) {
+  // Plan every configuration and lay out the workspace.
   std::vector<BatchEntry> ent(n);
   size_t off = 0;
   int fact_max = 0;
@@ -931,10 +914,7 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     b.ring = c->algo != EPRL_ALGO_SHELL && p.ring_KW != 0;
     if ((c->algo == EPRL_ALGO_RING || c->algo == EPRL_ALGO_RING_VALU) && !b.ring)
       return fail(c, EPRL_ERANGE, "the factorised path does not apply to every configuration");
-    if (c->algo == EPRL_ALGO_RING_VALU) {
-      b.plan.ring_cls = b.plan.ring_cls8;
-      b.plan.chain = false;
-    }
+    if (c->algo == EPRL_ALGO_RING_VALU || (b.plan.chain && !chain)) b.plan = without_chain(b.plan);
     batch_chunks(p, b.ring, p.ring_cls >= 0 ? c->tune_wg[p.ring_cls] : 0, b.nchunk, b.chunk,
                  b.bounds, b.ccost);
     fact_max = std::max(fact_max, p.fact_max);
@@ -962,14 +942,14 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     while (ent[t].towner != t) t = ent[t].towner;
     ent[q].towner = t;
   }
-  // Passes: as many configurations at a time as keep their derived tables within kDerivedBytes; the
+  // Passes: as many configurations at a time as keep their derived tables within `derived` bytes; the
   // passes run one after the other on the same memory (offsets from its start for now).
   size_t dmax = 0, dsum = 0;
   int npass = 1;
   for (int q = 0; q < n; ++q) {
     if (!ent[q].ring || !ent[q].plan.chain) continue;
     const size_t need = align_up(chain_derived_bytes(ent[q].plan), 256);
-    if (dsum > 0 && dsum + need > kDerivedBytes) {
+    if (dsum > 0 && dsum + need > derived) {
       ++npass;
       dsum = 0;
     }
@@ -1101,6 +1081,7 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     if (hipMalloc(&c->batch.ws, off) != hipSuccess) {
       (void)hipGetLastError();
       c->batch.ws = nullptr;
+      *no_room = (int64_t)dmax;
       return fail(c, EPRL_ENOMEM, "batch workspace allocation failed");
     }
     c->batch.ws_size = off;
@@ -1184,14 +1165,58 @@ int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
     if (!c->batch.side[q]) HIP_TRY(c, hipStreamCreateWithFlags(&c->batch.side[q], hipStreamNonBlocking));
     if (!c->batch.join[q]) HIP_TRY(c, hipEventCreateWithFlags(&c->batch.join[q], hipEventDisableTiming));
   }
-  rc = run_batch(c, boosters, A, st, dyn_off);
-  if (rc == EPRL_OK) c->batch.key = std::move(key);
+  return run_batch(c, boosters, A, st, dyn_off);
+}
+
+int batched_impl(eprl_ctx *c, int n, const int *two_j, const int *dl,
+                 const double *const *boosters, double *const *A, const int *layout_dl = nullptr) {
+  std::vector<int64_t> key;
+  key.push_back(n);
+  key.push_back(c->algo);
+  key.push_back(layout_dl != nullptr);
+  if (layout_dl)
+    for (int q = 0; q < n; ++q) key.push_back(layout_dl[q]);
+  for (int q = 0; q < kRingClasses; ++q) {
+    key.push_back(c->tune_wg[q]);
+    key.push_back(c->tune_stg[q]);
+  }
+  for (int q = 0; q < n; ++q) {
+    for (int t = 0; t < 10; ++t) key.push_back(two_j[10 * q + t]);
+    key.push_back(dl[q]);
+    if (!boosters[q] || !A[q]) return fail(c, EPRL_EINVAL, "null booster or output pointer");
+  }
+  // The call uploads from host buffers that are used again: it cannot become part of a graph.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t ec = hipStreamIsCapturing(c->stream, &capture);
+  if (ec != hipSuccess) return hip_fail(c, ec, "hipStreamIsCapturing");
+  if (capture != hipStreamCaptureStatusNone) return hip_fail(c, hipErrorStreamCaptureUnsupported, "batched call");
+  if (!c->batch.key.empty() && key == c->batch.key) return run_batch(c, boosters, A, nullptr, 0);
+  // Less memory at each attempt: the derived tables in about four passes, one configuration to a pass,
+  // none.  (A layout without them is not kept: the next call tries for the x-outer kernel again, as plain
+  // calls do.)
+  size_t derived = c->batch.derived;
+  int rc = EPRL_OK;
+  for (int attempt = 0; attempt < 4; ++attempt) {
+    const bool chain = attempt < 3;
+    int64_t no_room = -1;
+    rc = layout_batch(c, n, two_j, dl, boosters, A, layout_dl, derived, chain, &no_room);
+    if (rc == EPRL_OK && chain) c->batch.key = std::move(key);
+    if (no_room < 0) break;
+    derived = attempt == 0 ? (size_t)no_room / 4 : 0;
+  }
   return rc;
 }
 
 }  // namespace
 
 extern "C" {
+
+int eprl_internal_batch_pass(eprl_ctx *c, size_t derived_bytes) {
+  if (check_ctx(c)) return EPRL_EINVAL;
+  c->batch.derived = derived_bytes;
+  c->batch.key.clear();
+  return EPRL_OK;
+}
 
 int eprl_create(eprl_ctx **out, int device, void *hip_stream) {
   if (!out) return EPRL_EINVAL;

@@ -9,6 +9,10 @@
 
 #include "../../include/eprl.h"
 
+// Not part of the interface, for tests: most bytes the derived tables of a batch's pass take on this
+// context.
+extern "C" int eprl_internal_batch_pass(eprl_ctx *ctx, size_t derived_bytes);
+
 namespace eprl {
 
 // A range of spins in two-units: values lo2, lo2 + 2, ..., lo2 + 2 (n - 1).

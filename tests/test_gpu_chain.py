@@ -7,6 +7,7 @@ shells over a few cores, on the oracle's shells.  Tolerance: an output entry is 
 16^2 shells of a core times 16 k3, k4 and x values each, every product rounded a few times:
 about 16^3 units of 2^-53 relative to the largest entry, 5e-13.
 """
+import ctypes
 import sys
 
 import numpy as np
@@ -95,6 +96,28 @@ def test_batch_follows_its_buffers(lib, torch, shape):
             out = lib.vertex_tensor_batched(shape, 1.2, sets[k])
         for a, p in zip(out, plain[k]):
             assert torch.equal(a, p)
+
+
+# A batch whose derived tables are taken in several passes (configurations of several kernel variants, one
+# to three of a variant) on the same memory, first in two or three passes, then one configuration to a
+# pass, equals the plain calls bit by bit, also where a layout is kept and the buffers change.
+def test_batch_in_passes(lib, torch):
+    shape = [([2] * 10, 3), ([4, 4, 5, 3, 5, 5, 6, 4, 3, 6], 2), ([9, 9, 7, 7, 9, 9, 7, 8, 10, 8], 1), ([2] * 10, 2),
+             ([13, 12, 8, 11, 14, 11, 14, 14, 8, 7], 0), ([1] * 10, 16), ([4, 4, 5, 3, 5, 5, 6, 4, 3, 6], 1)]
+    sets = [[torch.from_numpy(workloads.synthetic_boosters(700 + 10 * k + q, R.block_shapes(j, d))).cuda()
+             for q, (j, d) in enumerate(shape)] for k in range(2)]
+    plain = [[lib.vertex_tensor(j, d, 1.2, b) for (j, d), b in zip(shape, s)] for s in sets]
+    handle, bound = lib._ctx("cuda").handle, lib._lib.eprl_internal_batch_pass
+    bound.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
+    try:
+        for limit in (3 << 19, 1 << 19, 0):
+            assert bound(handle, limit) == 0
+            for k in (0, 1, 0):
+                print("batch in passes", limit, k, flush=True)
+                for a, p in zip(lib.vertex_tensor_batched(shape, 1.2, sets[k]), plain[k]):
+                    assert torch.equal(a, p)
+    finally:
+        bound(handle, 8 << 30)
 
 
 # Index arithmetic of the contractions at its edges: dimensions of one, powers of two, primes, and one

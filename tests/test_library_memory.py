@@ -123,7 +123,32 @@ def vertex_runs_without_memory_for_derived_tables(lib):
             lib.lib.eprl_destroy(ctx)
 
 
-SCENARIOS = [vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
+# A batch that does not fit takes its derived tables in several passes, then one configuration to a
+# pass, then the kernels without them; the last it does not keep.
+def batch_runs_with_less_memory(lib):
+    configs = [([6] * 10, 5), ([13, 10, 11, 12, 10, 14, 11, 13, 13, 10], 4), ([8] * 10, 4)] + SMALL
+    call = lambda ctx: lib.batch(configs, ctx)
+    most, least = needed(lib, call, 0), needed(lib, call, RING_VALU)
+    assert most > least
+    for need, passes in ((most - (1 << 20), True), (least, False)):
+        ctx = lib.context()
+        base = lib.stub.stub_live()
+        lib.stub.stub_limit(base + need)
+        for _ in range(2):
+            lib.stub.stub_clear()
+            assert call(ctx) == OK
+            assert lib.stub.stub_stale() == 0
+            assert (lib.launches("chain_prep_batch_kernel") > 1) == passes
+            assert (lib.launches("ring_batch_kernel") > 0) == (not passes)
+        lib.stub.stub_limit(1 << 40)
+        lib.stub.stub_clear()
+        assert call(ctx) == OK
+        assert (lib.launches("chain_prep_batch_kernel") > 1) == passes
+        assert lib.launches("ring_batch_kernel") == 0
+        lib.lib.eprl_destroy(ctx)
+
+
+SCENARIOS = [batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
