@@ -1,9 +1,9 @@
 """The x-outer kernel of the factorised order at the edges of its tiles, against the CPU oracle.
 
-One workload per row and column tile count (one and two row tiles per wavefront, one and two row
-blocks, one to sixteen column tiles), for one to fourteen shells per link (one to four groups of
-four spin values) and k windows of at most and of more than sixteen positions; the ones with many
-shells over a few cores, on the oracle's shells.  Tolerance: an output entry is a sum of at most
+Workloads over its row tiles (one and two per wavefront) and column tiles (one to eleven, in one or
+two column blocks), for one to fourteen shells per link (one to four groups of four spin values) and
+k windows of at most and of more than sixteen positions; the ones with many shells over a few cores,
+on the oracle's shells.  Tolerance: an output entry is a sum of at most
 16^2 shells of a core times 16 k3, k4 and x values each, every product rounded a few times:
 about 16^3 units of 2^-53 relative to the largest entry, 5e-13.
 """
@@ -70,6 +70,42 @@ def test_tile_edges(lib, torch, two_j, dl, cores, dims):
             shells += [(o23, o24, o25, o34, o35, o45) for o23 in range(nd) for o45 in range(nd)]
         a = lib.vertex_tensor_cores(two_j, dl, 1.2, bd, lo, hi)
         ref = V.vertex_tensor(two_j, dl, b, shells=shells)
+    scale = np.abs(ref).max()
+    assert scale > 0
+    assert np.abs(a.cpu().numpy() - ref).max() <= TOL * scale
+
+
+# The widest tiles at many shells: two row tiles by seven to eleven column tiles (two T row groups in
+# flight, and two columns of H from nine tiles on), one and two column blocks (thirteen tiles: the last of
+# the second block is padding), two to four groups of four spin values, an odd last group among them, and
+# windows of more than sixteen positions.  Each on the oracle's shells of the core with the widest window.
+# Tolerance: as above; an entry is a sum over at most 14^2 shells, and no sum of the chain (x, k3, k4, k5,
+# k2, l45, l23) is longer than 40.
+MANY = [([11, 14, 11, 10, 15, 15, 13, 15, 12, 15], 8, 2957, (10, 12, 13, 12, 11)),
+        ([13, 13, 13, 15, 12, 15, 16, 13, 12, 17], 9, 4067, (13, 13, 13, 13, 13)),
+        ([13, 13, 8, 8, 15, 15, 13, 15, 13, 8], 10, 5384, (9, 14, 14, 9, 9)),
+        ([13, 12, 8, 15, 9, 12, 12, 13, 14, 9], 8, 2216, (9, 10, 10, 9, 10)),
+        ([13, 12, 9, 8, 11, 10, 16, 14, 15, 9], 8, 3674, (9, 10, 12, 8, 9)),
+        ([15, 12, 15, 14, 16, 12, 9, 14, 16, 9], 8, 2945, (13, 10, 13, 10, 9)),
+        ([13, 8, 13, 8, 10, 16, 15, 9, 11, 8], 12, 6688, (9, 11, 9, 8, 7)),
+        ([14, 13, 15, 14, 12, 9, 13, 15, 12, 13], 13, 24788, (14, 10, 12, 10, 13)),
+        ([11, 15, 12, 12, 16, 10, 13, 13, 12, 11], 13, 24816, (11, 10, 13, 11, 12)),
+        ([15, 14, 15, 8, 12, 13, 16, 12, 12, 12], 13, 19313, (9, 13, 12, 12, 9)),
+        ([14, 14, 14, 10, 13, 12, 15, 13, 16, 13], 13, 19311, (11, 13, 13, 13, 11)),
+        ([13, 15, 10, 14, 18, 12, 17, 16, 15, 12], 12, 17673, (11, 13, 15, 10, 13)),
+        ([15, 12, 12, 13, 17, 17, 15, 16, 15, 15], 5, 14, (12, 16, 13, 13, 14))]
+
+
+@pytest.mark.parametrize("two_j,dl,core,dims", MANY)
+def test_widest_tiles_many_shells(lib, torch, two_j, dl, core, dims):
+    assert tuple(lib.layout(two_j, dl)[0]) == dims
+    nd = dl + 1
+    b = workloads.synthetic_boosters(600 + dl, R.block_shapes(two_j, dl))
+    print(f"widest tiles {two_j} dl={dl} core={core}", flush=True)
+    a = lib.vertex_tensor_cores(two_j, dl, 1.2, torch.from_numpy(b).cuda(), core, core + 1)
+    o24, o25, o34, o35 = core // nd ** 3, core // nd ** 2 % nd, core // nd % nd, core % nd
+    ref = V.vertex_tensor(two_j, dl, b, shells=[(o23, o24, o25, o34, o35, o45)
+                                                for o23 in range(nd) for o45 in range(nd)])
     scale = np.abs(ref).max()
     assert scale > 0
     assert np.abs(a.cpu().numpy() - ref).max() <= TOL * scale
