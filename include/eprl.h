@@ -93,8 +93,8 @@ int eprl_set_algorithm(eprl_ctx *ctx, int algo);
 
 /* Work split of the factorised order per tile class (the class is out[4] of eprl_count_work):
  * the shell sum is cut into chunks of equal estimated cost, about target_workgroups
- * workgroups per launch (0: the default, 6144 for the kernel with x outside the virtual spins,
- * 8192 for the others), and, for the others, staging_level picks how many booster blocks
+ * workgroups per launch (0: the default, 8192), and, except in the kernel with x outside the
+ * virtual spins, staging_level picks how many booster blocks
  * of a core are held in LDS (2: all four, 1: the two of the second stage, 0: none, -1: the
  * most that fits; a level that does not fit falls back to the next lower one).  The paper
  * adapts the split of its loops to the machine in the same spirit (Sec. 3.1,

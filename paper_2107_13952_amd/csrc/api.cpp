@@ -292,16 +292,16 @@ int plan_for(eprl_ctx *c, const int two_j[10], int dl, const Plan **out) {
   return EPRL_OK;
 }
 
-// Device-side state of one configuration: tables built, metadata uploaded.
 // Workgroups per launch of the factorised path: enough for several rounds of resident
 // workgroups on 256 CUs, so that cost-balanced chunks finish together.  A batch uses the same
 // schedule per configuration, which keeps its tensors bitwise equal to those of plain calls.
+// One default for both kernels: the tile classes share their setting, and the autotuner's targets hold it.
+// (x-outer kernel at 4096, 6144, 8192 and 12288: two_j = 6, 8 shells 1566, 1500, 1473, 1497 us; two_j = 8, 8
+// shells 7430, 7300, 7320, 7300; spins 3 .. 12 / 2, 5 shells 269, 284, 278, 303; two_j = 10 .. 14, 6 shells
+// 5660 for all; two_j = 7 .. 10, 3 shells 229, 252, 274, 274; 64 irregular configurations 34.5, 34.6, 34.9 ms.)
 constexpr int kRingTargetWG = 8192;
-// (x-outer kernel: j = 3, 8 shells 1.77, 1.70, 1.67, 1.69 ms at 4096, 6144, 8192, 12288; j = 5..7, 6 shells
-// 6.3 ms from 3072 on; 64 irregular configurations 56.6, 57.2, 58.5, 60.0 ms.)
-constexpr int kChainTargetWG = 6144;
-int default_target(const Plan &p) { return p.chain ? kChainTargetWG : kRingTargetWG; }
 
+// Device-side state of one configuration: tables built, metadata uploaded.
 struct Prepared {
   Plan plan;
   double *tables = nullptr;
@@ -506,7 +506,7 @@ int chain_impl(eprl_ctx *c, const int two_j[10], int dl, const double *B, int ac
 int ring_impl(eprl_ctx *c, const int two_j[10], int dl, const double *B, int accumulate,
               double *A, const Plan &probe, int core_lo = 0, int core_hi = -1) {
   const int cls = probe.ring_cls;
-  const int target = c->tune_wg[cls] > 0 ? c->tune_wg[cls] : default_target(probe);
+  const int target = c->tune_wg[cls] > 0 ? c->tune_wg[cls] : kRingTargetWG;
   std::vector<int> key(two_j, two_j + 10);
   key.push_back(dl);
   key.push_back(target);
@@ -711,7 +711,7 @@ void booster_r_nodes(int n, const std::vector<double> (&gx)[2], const std::vecto
 int batch_chunks(const Plan &p, bool ring, int target_wg, int &nchunk, int64_t &chunk,
                  std::vector<int> &bounds, std::vector<double> &ccost) {
   if (ring) {
-    const int target = target_wg > 0 ? target_wg : default_target(p);
+    const int target = target_wg > 0 ? target_wg : kRingTargetWG;
     nchunk = p.chain ? chain_schedule(p, target, bounds, &ccost) : ring_schedule(p, target, bounds, &ccost);
     chunk = 0;
   } else {
@@ -1310,7 +1310,7 @@ int eprl_autotune(eprl_ctx *c, const int two_j[10], int dl, const double *B, dou
     return hip_fail(c, hipGetLastError(), "hipEventCreate");
   }
   float best = 0.0f;
-  int best_wg = default_target(p), best_stg = -1;
+  int best_wg = kRingTargetWG, best_stg = -1;
   for (int li = 0; li < nl && rc == EPRL_OK; ++li) {
     for (int t : kTargets) {
       c->tune_wg[cls] = t;

@@ -1,7 +1,8 @@
 /* A HIP runtime without a device, for tests of the library's host code: loaded with RTLD_GLOBAL before
  * the library, its functions stand in for the runtime's.  Device memory is host memory reserved by
  * mmap, bounded by stub_limit; what has been freed is never handed out again, and an upload whose
- * words point into it is counted (stub_stale).  Launches are recorded by kernel name and run nothing. */
+ * words point into it is counted (stub_stale).  Launches are recorded by kernel name and run nothing;
+ * the time between two events is shortest when the watched kernel ran with the grid of stub_fastest. */
 #define _GNU_SOURCE
 #include <stddef.h>
 #include <stdint.h>
@@ -18,13 +19,17 @@ static int nranges, last_error, stale, nkernels, nlaunches;
 static size_t live_bytes, peak_bytes, limit = (size_t)1 << 46;
 static struct { const void *f; char name[256]; } kernels[4096];
 static int launched[65536];
-static const char *fail_name;
+static const char *fail_name, *watched;
+static long watched_grid, fastest_grid;
 
 void stub_limit(size_t n) { limit = n; }
 size_t stub_live(void) { return live_bytes; }
 size_t stub_peak(void) { size_t p = peak_bytes; peak_bytes = live_bytes; return p; }
 int stub_stale(void) { return stale; }
 void stub_fail(const char *name) { fail_name = name; }
+void stub_watch(const char *name) { watched = name; }
+long stub_grid(void) { return watched_grid; }
+void stub_fastest(long grid) { fastest_grid = grid; }
 void stub_clear(void) { nlaunches = 0; }
 /* Launches since stub_clear of kernels whose mangled name holds `name`. */
 int stub_launches(const char *name) {
@@ -85,6 +90,7 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t smem, voi
   for (int q = 0; q < nkernels; ++q) {
     if (kernels[q].f != f) continue;
     if (fail_name && strstr(kernels[q].name, fail_name)) return err(FAILED);
+    if (watched && strstr(kernels[q].name, watched)) watched_grid = (long)g.x * g.y * g.z;
     if (nlaunches < 65536) launched[nlaunches++] = q;
     return OK;
   }
@@ -118,7 +124,11 @@ int hipDeviceSynchronize(void) { return OK; }
 int hipEventCreate(void **e) { return (*e = malloc(8)) ? OK : NOMEM; }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; return (*e = malloc(8)) ? OK : NOMEM; }
 int hipEventDestroy(void *e) { free(e); return OK; }
-int hipEventElapsedTime(float *t, void *a, void *b) { (void)a; (void)b; *t = 1.0f; return OK; }
+int hipEventElapsedTime(float *t, void *a, void *b) {
+  (void)a; (void)b;
+  *t = 1.0f + (float)labs(watched_grid - fastest_grid);
+  return OK;
+}
 int hipEventRecord(void *e, void *s) { (void)e; (void)s; return OK; }
 int hipEventSynchronize(void *e) { (void)e; return OK; }
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; return (*s = malloc(8)) ? OK : NOMEM; }

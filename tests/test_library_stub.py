@@ -1,6 +1,6 @@
-"""The library's handling of device memory that runs out, on the CPU: its host code runs against a
-runtime without a device (hip_stub.c) whose memory the test bounds.  Each scenario in a process of its
-own, the stub loaded before the library."""
+"""The library's host code on the CPU, against a runtime without a device (hip_stub.c): what it does
+when device memory runs out or a launch fails, and what it launches.  Each scenario in a process of
+its own, the stub loaded before the library."""
 import ctypes
 import os
 import subprocess
@@ -29,6 +29,7 @@ class Library:
         self.stub = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)
         for name in ("stub_live", "stub_peak"):
             getattr(self.stub, name).restype = ctypes.c_size_t
+        self.stub.stub_grid.restype = ctypes.c_long
         self.stub.stub_limit.argtypes = [ctypes.c_size_t]
         self.lib = ctypes.CDLL(LIB)
         self.ctx = self.context()
@@ -148,11 +149,26 @@ def batch_runs_with_less_memory(lib):
         lib.lib.eprl_destroy(ctx)
 
 
-SCENARIOS = [batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
+# The autotuner tries the default split too: where that is the fastest, it stays.
+def autotune_tries_the_default(lib):
+    lib.stub.stub_watch(b"chain_kernel")
+    for two_j, dl in LARGE:
+        ctx = lib.context()
+        assert lib.vertex(two_j, dl, ctx) == OK
+        default = lib.stub.stub_grid()
+        lib.stub.stub_fastest(ctypes.c_long(default))
+        out = (ctypes.c_int * 3)()
+        assert lib.lib.eprl_autotune(ctx, (ctypes.c_int * 10)(*two_j), dl, lib.buf, lib.buf, out) == OK
+        assert lib.vertex(two_j, dl, ctx) == OK
+        assert lib.stub.stub_grid() == default
+        lib.lib.eprl_destroy(ctx)
+
+
+SCENARIOS = [autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
-def test_memory(stub, scenario):
+def test_library(stub, scenario):
     res = subprocess.run([sys.executable, os.path.abspath(__file__), stub, scenario], capture_output=True, text=True,
                          timeout=300)
     assert res.returncode == 0, res.stdout + res.stderr
