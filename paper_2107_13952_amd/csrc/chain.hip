@@ -96,6 +96,18 @@ struct FastDiv {
 
 constexpr int kPrepThreads = 256;
 
+// The pairs (o24, o25) of a core range, first .. first + n - 1, and how many o25 they hold (from that of
+// the first on, cyclic).
+struct PrepPairs {
+  int first, n, n25;
+  __host__ __device__ explicit PrepPairs(const RingParams &rp) {
+    const int nd2 = rp.nd * rp.nd;
+    first = rp.core_lo / nd2;
+    n = rp.core_hi > rp.core_lo ? (rp.core_hi + nd2 - 1) / nd2 - first : 0;
+    n25 = n < rp.nd ? n : rp.nd;
+  }
+};
+
 // T5, T2 and the weighted boosters M4, M3 of one configuration.
 //   T5[o25][x][o35][i1][o45][kap][S]: entry i5, k4 = max(|l45 - j14|, k4lo) + 2 kap
 //   T2[o24][o25][x][i1][o23][kap][S]: entry i2, k3 = max(|l23 - j13|, k3lo) + 2 kap
@@ -103,10 +115,12 @@ constexpr int kPrepThreads = 256;
 //   M3[o34][o35][pos][.], k3 = max(|l34 - l35|, k3lo) + 2 pos, the entries (o23, i3)
 // (x over the configuration's own range; entries outside a booster block or a triad are zeros; the
 // (x, i1) that do not close (i1 l25 x) are not written).  One block per T5 (o25, x, o35), per T2
-// (o24, o25, x), then the boosters.
+// (o24, o25, x), then the boosters.  T5 and T2 of the core range's pairs (o24, o25) only: a
+// call for one core at two_j = 14, 10 shells takes 1102 us, 3405 with all of them (ring.hip's kernels: 2722).
 __device__ __forceinline__ void chain_prep_block(const RingParams &rp, int b) {
   const int nd = rp.nd, nd3 = nd * nd * nd, nx = rp.nx, d1 = rp.i_n[0];
-  const int nb5 = nd * nx * nd, nb2 = nd * nd * nx, nbs = (nd * nx * nd + kPrepThreads - 1) / kPrepThreads;
+  const PrepPairs pr(rp);
+  const int nb5 = pr.n25 * nx * nd, nb2 = pr.n * nx, nbs = (nd * nx * nd + kPrepThreads - 1) / kPrepThreads;
   const int *J = rp.two_j;
   const int NX = rp.NX, nK2 = rp.K_n[0], nK3 = rp.K_n[1], nK4 = rp.K_n[2], nK5 = rp.K_n[3];
   const int S = rp.ts;
@@ -117,8 +131,10 @@ __device__ __forceinline__ void chain_prep_block(const RingParams &rp, int b) {
     if (five) {
       o35 = b % nd;
       xi = (b / nd) % nx;
-      o25 = b / (nd * nx);
+      o25 = (pr.first + b / (nd * nx)) % nd;
+      b = (o25 * nx + xi) * nd + o35;
     } else {
+      b += pr.first * nx;
       xi = b % nx;
       o25 = (b / nx) % nd;
       o24 = b / (nx * nd);
@@ -764,7 +780,8 @@ void chain_params(const Plan &p, double *derived, RingParams &rp) {
 
 int64_t chain_prep_blocks(const RingParams &rp) {
   const int64_t nd = rp.nd, m = nd * nd * (rp.wm + 3) * (rp.mr4 + rp.mr3);
-  return nd * rp.nx * nd + nd * nd * rp.nx + (nd * rp.nx * nd + kPrepThreads - 1) / kPrepThreads +
+  const PrepPairs pr(rp);
+  return pr.n25 * rp.nx * nd + pr.n * rp.nx + (nd * rp.nx * nd + kPrepThreads - 1) / kPrepThreads +
          (m + kPrepThreads - 1) / kPrepThreads;
 }
 

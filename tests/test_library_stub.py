@@ -164,7 +164,24 @@ def autotune_tries_the_default(lib):
         lib.lib.eprl_destroy(ctx)
 
 
-SCENARIOS = [autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
+# A core range makes the derived tables of its own (l24, l25) only: for one core T2 of one pair and T5 of
+# one l25, instead of those of all (dl + 1)^2 pairs and dl + 1 values.
+def core_range_makes_its_own_derived_tables(lib):
+    lib.stub.stub_watch(b"chain_prep_kernel")
+    for two_j, dl in LARGE:
+        js, nd = (ctypes.c_int * 10)(*two_j), dl + 1
+        grid = []
+        for lo, hi in ((0, nd ** 4), (nd ** 4 // 2, nd ** 4 // 2 + 1), (nd ** 2 - 1, nd ** 2 + 1), (5, 5)):
+            assert lib.lib.eprl_vertex_tensor_cores(lib.ctx, js, dl, ctypes.c_double(1.2), lib.buf, ctypes.c_int64(lo),
+                                                    ctypes.c_int64(hi), 0, lib.buf) == OK
+            grid.append(lib.stub.stub_grid())
+        whole, one, two, none = grid
+        # T5 blocks nd (x, l35) per l25, T2 blocks x per pair; the rest is the same for every range
+        assert two - one == one - none > 0
+        assert whole - none == (nd * nd + nd * nd) * (one - none) // (nd + 1)
+
+
+SCENARIOS = [core_range_makes_its_own_derived_tables, autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
