@@ -1868,7 +1868,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
   const size_t o_stat3 = take(3 * sizeof(double));
   const size_t o_var = off;
   const int n_max = 512;
-  char *ws_seen = nullptr;
+  size_t ws_seen = 0;  // size of the workspace that holds the call-independent data
   double st3[3] = {0.0, 0.0, 0.0};
   int n = 16;
   for (;;) {
@@ -1881,8 +1881,9 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     rc = ensure_workspace(c, off);
     if (rc) return rc;
     char *ws = c->ws;
-    if (ws != ws_seen) {
-      // (Re)load the call-independent data and the 4jm tables.
+    if (c->ws_size != ws_seen) {
+      // A new workspace (larger than the one before, perhaps at its address): (re)load the
+      // call-independent data and the 4jm tables.
       char *stg;
       rc = staging(c, static_bytes, &stg);
       if (rc) return rc;
@@ -1902,7 +1903,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
       HIP_TRY(c, launch_fourjm_tables(reinterpret_cast<const FourjmSet *>(ws + o_sets), (int)sets.size(),
                                       max_entries, reinterpret_cast<const int *>(ws + o_mt),
                                       reinterpret_cast<double *>(ws + o_coef), c->ft, c->stream));
-      ws_seen = ws;
+      ws_seen = c->ws_size;
     }
     {
       char *stg;

@@ -1,6 +1,7 @@
 /* A HIP runtime without a device, for tests of the library's host code: loaded with RTLD_GLOBAL before
  * the library, its functions stand in for the runtime's.  Device memory is host memory reserved by
- * mmap, bounded by stub_limit; what has been freed is never handed out again, and an upload whose
+ * mmap, bounded by stub_limit; what has been freed is never handed out again (unless stub_reuse asks
+ * for one address, whenever it is free, with memory of zeros), and an upload whose
  * words point into it is counted (stub_stale).  Launches are recorded by kernel name and run nothing;
  * the time between two events is shortest when the watched kernel ran with the grid of stub_fastest. */
 #define _GNU_SOURCE
@@ -21,6 +22,8 @@ static struct { const void *f; char name[256]; } kernels[4096];
 static int launched[65536];
 static const char *fail_name, *watched;
 static long watched_grid, fastest_grid;
+static char *reused;
+static double read_value;
 
 void stub_limit(size_t n) { limit = n; }
 size_t stub_live(void) { return live_bytes; }
@@ -38,6 +41,13 @@ int stub_launches(const char *name) {
   return n;
 }
 
+static const size_t kReused = (size_t)1 << 32;
+void stub_reuse(int on) {
+  reused = on ? mmap(NULL, kReused, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0) : NULL;
+}
+/* What copies to the host return. */
+void stub_read(double v) { read_value = v; }
+
 static int err(int e) {
   if (e) last_error = e;
   return e;
@@ -51,6 +61,15 @@ static struct range *find(const void *p) {
 int hipMalloc(void **p, size_t n) {
   if (live_bytes + n > limit || nranges == 4096) return err(NOMEM);
   n = (n + 4095) / 4096 * 4096;
+  struct range *last = reused ? find(reused) : NULL;
+  if (reused && n <= kReused && !(last && last->live)) {
+    if (last) last->n = 0;
+    mmap(reused, kReused, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE | MAP_FIXED, -1, 0);
+    ranges[nranges++] = (struct range){reused, n, 1};
+    live_bytes += n;
+    *p = reused;
+    return OK;
+  }
   char *m = mmap(NULL, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (m == MAP_FAILED) return err(NOMEM);
   ranges[nranges++] = (struct range){m, n, 1};
@@ -73,7 +92,10 @@ int hipHostFree(void *p) { free(p); return OK; }
 int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *stream) {
   (void)kind; (void)stream;
   struct range *r = find(dst);
-  if (find(src)) { memcpy(dst, src, n); return OK; }
+  if (find(src)) {
+    for (size_t q = 0; q + 8 <= n; q += 8) memcpy((char *)dst + q, &read_value, 8);
+    return OK;
+  }
   if (!r || !r->live || (char *)dst + n > r->p + r->n) return err(INVALID);
   for (size_t q = 0; q + 8 <= n; q += 8) {
     const void *w;

@@ -181,7 +181,25 @@ def core_range_makes_its_own_derived_tables(lib):
         assert whole - none == (nd * nd + nd * nd) * (one - none) // (nd + 1)
 
 
-SCENARIOS = [core_range_makes_its_own_derived_tables, autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
+# The booster builder loads its lists and 4jm tables again whenever a refinement replaces the workspace,
+# also by one at the same address.
+def boosters_follow_the_workspace(lib):
+    lib.stub.stub_read.argtypes = [ctypes.c_double]
+    lib.stub.stub_read(1.0)   # an error above the tolerance: n = 16, 32, ..., 512, each with a larger workspace
+    for reuse in (0, 1):
+        ctx = lib.context()
+        assert lib.lib.eprl_sixj_batch(ctx, 1, (ctypes.c_int * 6)(*[200] * 6), lib.buf) == OK
+        lib.stub.stub_reuse(reuse)
+        lib.stub.stub_clear()
+        info = (ctypes.c_double * 3)()
+        assert lib.lib.eprl_boosters(ctx, (ctypes.c_int * 10)(*[2] * 10), 1, ctypes.c_double(1.2), ctypes.c_double(0.5),
+                                     lib.buf, info) == OK
+        assert info[2] == 512 and lib.launches("booster_integrals_kernel") == 6
+        assert lib.launches("fourjm_table_kernel") == 6
+        lib.lib.eprl_destroy(ctx)
+
+
+SCENARIOS = [boosters_follow_the_workspace, core_range_makes_its_own_derived_tables, autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
