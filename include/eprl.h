@@ -133,11 +133,19 @@ int eprl_count_terms(const int two_j[10], int dl, int64_t *live_shells, double *
  *   out[0] = {15j} x booster terms (as eprl_count_terms);
  *   out[1] = FP64 flops of the per-shell order: 2 x (multiply-adds of the four mode products)
  *            + 6 per (term, allowed x) for the {15j} sums;
- *   out[2] = useful FP64 flops of the factorised order (active index ranges only);
+ *   out[2] = useful FP64 flops of the factorised order, core by core (active index ranges only);
  *   out[3] = FP64 flops its matrix-core tiles execute (16x16x4 tiles, padding included);
  *   out[4] = tile class of the factorised kernel for this configuration (0..8), or -1 when
  *            the configuration falls back to the per-shell order. */
 int eprl_count_work(const int two_j[10], int dl, double out[5]);
+
+/* out[2] of eprl_count_work takes the sums over k5 and k2 once per core (l24, l25, l34, l35) and x.
+ * The kernel with x outside the virtual spins makes them once per (l25, x, l35) and (l24, l25, x), in
+ * its derived tables; useful FP64 flops of that order:
+ *   out[0] = of the kernel itself (the sums over l45 and l23, over k4, and the update),
+ *   out[1] = of the derived tables.
+ * Zeros where another kernel evaluates the configuration. */
+int eprl_count_chain_work(const int two_j[10], int dl, double out[2]);
 
 /* The vertex tensor of eq. (vertex-ampl): the sum of the framed algorithm of Sec. 3.1 (6j
  * tables (step 4); per shell the {15j} tensor W (6(i)) contracted with the booster

@@ -52,6 +52,7 @@ _SIGS = {
     "eprl_layout": (ctypes.c_int, [_i32p, ctypes.c_int, _i32p, _i32p, _i64p]),
     "eprl_count_terms": (ctypes.c_int, [_i32p, ctypes.c_int, _i64p, ctypes.POINTER(ctypes.c_double)]),
     "eprl_count_work": (ctypes.c_int, [_i32p, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
+    "eprl_count_chain_work": (ctypes.c_int, [_i32p, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
     "eprl_vertex_tensor": (ctypes.c_int, [ctypes.c_void_p, _i32p, ctypes.c_int, ctypes.c_double, _dp, _dp]),
     "eprl_bf_vertex_tensor": (ctypes.c_int, [ctypes.c_void_p, _i32p, _dp]),
     "eprl_vertex_tensor_range": (ctypes.c_int, [ctypes.c_void_p, _i32p, ctypes.c_int, ctypes.c_double, _dp,
@@ -147,6 +148,17 @@ def count_work(two_j, dl):
         raise EprlError(rc, "inadmissible spins or shell count")
     return {"terms": out[0], "shell_flops": out[1], "ring_useful_flops": out[2],
             "ring_mfma_flops": out[3], "ring_class": int(out[4])}
+
+
+def count_chain_work(two_j, dl):
+    """(kernel, derived tables): useful FP64 flops of the kernel with x outside the virtual spins and of
+    the tables it reads, each made once (count_work's ring_useful_flops makes them once per core); zeros
+    where another kernel evaluates the configuration."""
+    out = (ctypes.c_double * 2)()
+    rc = _lib.eprl_count_chain_work(_ints(two_j, 10), int(dl), out)
+    if rc:
+        raise EprlError(rc, "inadmissible spins or shell count")
+    return out[0], out[1]
 
 
 # ---------------------------------------------------------------- device calls

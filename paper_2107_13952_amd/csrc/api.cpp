@@ -1405,6 +1405,16 @@ int eprl_count_work(const int two_j[10], int dl, double out[5]) {
   return EPRL_OK;
 }
 
+int eprl_count_chain_work(const int two_j[10], int dl, double out[2]) {
+  if (!out) return EPRL_EINVAL;
+  Plan p;
+  std::string err;
+  int rc = make_plan(two_j, dl, p, err);
+  if (rc) return rc;
+  count_chain_work(p, out);
+  return EPRL_OK;
+}
+
 int eprl_vertex_tensor(eprl_ctx *c, const int two_j[10], int dl, double gamma, const double *B,
                        double *A) {
   if (check_ctx(c)) return EPRL_EINVAL;

@@ -79,6 +79,8 @@ int make_plan(const int two_j[10], int dl, Plan &p, std::string &err);
 void count_terms(const Plan &p, int64_t &live, double &terms);
 // Exact work counts: terms, per-shell-order flops, factorised-order useful and executed flops.
 void count_work(const Plan &p, double out[5]);
+// Useful flops of the x-outer kernel and of its derived tables.
+void count_chain_work(const Plan &p, double out[2]);
 
 // ---- kernel-side parameter blocks (passed by value) ----
 

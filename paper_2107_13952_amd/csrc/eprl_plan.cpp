@@ -514,6 +514,59 @@ void count_work(const Plan &p, double out[5]) {
   out[4] = p.ring_cls;
 }
 
+void count_chain_work(const Plan &p, double out[2]) {
+  out[0] = out[1] = 0.0;
+  if (!p.chain) return;
+  const int nd = p.nd, nd3 = nd * nd * nd;
+  const int *J = p.two_j;
+  const int d1 = p.i[0].n, d2 = p.i[1].n, d3 = p.i[2].n, d4 = p.i[3].n, d5 = p.i[4].n;
+  const int xlo = p.X.lo2, xhi = xlo + 2 * (p.X.n - 1);
+  auto kr = [&](int e, int t) { return Range{p.kr[(e * nd3 + t) * 2], p.kr[(e * nd3 + t) * 2 + 1]}; };
+  // Values of k with the triads (a b k) and (c x k).
+  auto both = [](int a, int b, int c, int x) {
+    const int lo = std::max(std::abs(a - b), std::abs(c - x)), hi = std::min(a + b, c + x);
+    return hi < lo || ((a + b + c + x) & 1) ? 0 : (hi - lo) / 2 + 1;
+  };
+  auto add = [](Range &w, Range r) {  // hull of the windows of several spins
+    const int lo = w.n > 0 ? std::min(w.lo2, r.lo2) : r.lo2;
+    const int hi = std::max(w.n > 0 ? w.lo2 + 2 * (w.n - 1) : lo, r.lo2 + 2 * (r.n - 1));
+    w = Range{lo, (hi - lo) / 2 + 1};
+  };
+  for (int o25 = 0; o25 < nd; ++o25)
+    for (int x = xlo; x <= xhi; x += 2) {
+      const int n1 = triad_count(p.i[0].lo2, d1, J[L25] + 2 * o25, x);
+      if (n1 == 0) continue;
+      for (int o = 0; o < nd; ++o)
+        for (int q = 0; q < nd; ++q) {
+          // T5: (l25, x, l35 = q), l45 = o; T2: (l24 = q, l25, x), l23 = o
+          const Range k5 = kr(3, (o25 * nd + q) * nd + o), k2 = kr(0, (o * nd + q) * nd + o25);
+          out[1] += 3.0 * n1 * d5 * both(J[L45] + 2 * o, J[L14], J[L35] + 2 * q, x) * triad_count(k5.lo2, k5.n, J[L14], x);
+          out[1] += 3.0 * n1 * d2 * both(J[L23] + 2 * o, J[L13], J[L24] + 2 * q, x) * triad_count(k2.lo2, k2.n, J[L13], x);
+        }
+      for (int o24 = 0; o24 < nd; ++o24)
+        for (int o34 = 0; o34 < nd; ++o34)
+          for (int o35 = 0; o35 < nd; ++o35) {
+            const int l24 = J[L24] + 2 * o24, l35 = J[L35] + 2 * o35;
+            double g = 0.0, h = 0.0;
+            Range w4, w3;
+            for (int o = 0; o < nd; ++o) {
+              const Range k4 = kr(2, (o * nd + o24) * nd + o34), k3 = kr(1, (o34 * nd + o35) * nd + o);
+              if (k4.n > 0 && kr(3, (o25 * nd + o35) * nd + o).n > 0) {
+                add(w4, k4);
+                g += triad_count(k4.lo2, k4.n, l35, x);
+              }
+              if (k3.n > 0 && kr(0, (o * nd + o24) * nd + o25).n > 0) {
+                add(w3, k3);
+                h += triad_count(k3.lo2, k3.n, l24, x);
+              }
+            }
+            const double a4 = triad_count(w4.lo2, w4.n, l35, x), a3 = triad_count(w3.lo2, w3.n, l24, x);
+            if (a4 > 0 && a3 > 0)
+              out[0] += 2.0 * n1 * (d5 * d4 * g + d2 * d3 * h + d5 * d4 * a4 * a3 + (double)d5 * d4 * a3 * d3 * d2);
+          }
+    }
+}
+
 // Booster blocks of a configuration in packing order (eq. (booster); edges 2..5, offset
 // triples of their virtual links): the boundary and virtual spins of the edge's four links,
 // the intertwiner ranges and the block's offset in the packed buffer.  Empty blocks are left out.

@@ -62,6 +62,55 @@ def test_counts_match_oracle(two_j, dl):
     assert terms == ref
 
 
+def _triad(a, b, c):
+    return (a + b + c) % 2 == 0 and abs(a - b) <= c <= a + b
+
+
+@pytest.mark.parametrize("two_j,dl", [([2] * 10, 1), ([2, 3, 2, 1, 3, 2, 3, 1, 1, 3], 1),
+                                      ([4, 1, 1, 4, 4, 3, 3, 1, 4, 1], 2)])
+def test_chain_work_counts_derived_tables_once(two_j, dl):
+    # Brute force over (l24, l25, l34, l35, x): a multiply-add is 2 flops; T5 and T2 entries, three flops a
+    # term, once per (l25, x, l35) and (l24, l25, x).  Links 23, 24, 25, 34, 35, 45 are 4..9.
+    lib = _lib()
+    (i1lo, d1), *rest = R.boundary_ranges(two_j)
+    d2, d3, d4, d5 = (n for _, n in rest)
+    j12, j13, j14, j15 = two_j[:4]
+
+    def ks(e, **l):
+        two_l = [l.get(name, j) for name, j in zip(("a", "b", "c", "d", "l23", "l24", "l25", "l34", "l35", "l45"), two_j)]
+        lo, n = R.virtual_range(two_l, e)
+        return range(lo, lo + 2 * n, 2)
+
+    spins = lambda link: range(two_j[link], two_j[link] + 2 * dl + 1, 2)
+    kernel = tables = 0
+    for l25 in spins(6):
+        for x in range(0, 80):
+            n1 = sum(_triad(i1, l25, x) for i1 in range(i1lo, i1lo + 2 * d1, 2))
+            if n1 == 0:
+                continue
+            for l35 in spins(8):
+                for l45 in spins(9):
+                    k4 = sum(_triad(k, l45, j14) and _triad(k, l35, x) for k in range(80))
+                    tables += 3 * n1 * d5 * k4 * sum(_triad(k, j14, x) for k in ks(5, l25=l25, l35=l35, l45=l45))
+            for l24 in spins(5):
+                for l23 in spins(4):
+                    k3 = sum(_triad(k, l23, j13) and _triad(k, l24, x) for k in range(80))
+                    tables += 3 * n1 * d2 * k3 * sum(_triad(k, j13, x) for k in ks(2, l23=l23, l24=l24, l25=l25))
+                for l34 in spins(7):
+                    for l35 in spins(8):
+                        k4 = [list(ks(4, l45=l, l24=l24, l34=l34)) for l in spins(9) if len(ks(5, l25=l25, l35=l35, l45=l))]
+                        k3 = [list(ks(3, l34=l34, l35=l35, l23=l)) for l in spins(4) if len(ks(2, l23=l, l24=l24, l25=l25))]
+                        k4 = [[k for k in v if _triad(k, l35, x)] for v in k4]
+                        k3 = [[k for k in v if _triad(k, l24, x)] for v in k3]
+                        n4, n3 = len(set(sum(k4, []))), len(set(sum(k3, [])))
+                        if n4 and n3:
+                            kernel += 2 * n1 * (d5 * d4 * sum(map(len, k4)) + d2 * d3 * sum(map(len, k3))
+                                                + d5 * d4 * n4 * n3 + d5 * d4 * n3 * d3 * d2)
+    assert kernel > 0 and tables > 0
+    assert lib.count_chain_work(two_j, dl) == (kernel, tables)
+    assert lib.count_chain_work([1] * 10, 16) == (0, 0)
+
+
 def test_cfg1_counts():
     lib = _lib()
     live, terms = lib.count_terms([2] * 10, 3)
