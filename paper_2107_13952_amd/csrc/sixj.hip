@@ -17,63 +17,14 @@
 //    products and sum are carried in double-double, which removes the effect of the
 //    alternating-sign cancellation at the spins handled here.
 // Double-double primitives follow Dekker (1971) and Knuth (TAOCP vol. 2, 4.2.2).
+#include "dd.hpp"
 #include "eprl_internal.hpp"
 
-// The error-free transformations below need every product and sum rounded exactly as
-// written: fusing p = a*b into a later p + e (the default contraction of device code) would
-// destroy the error terms.
-#pragma clang fp contract(off)
+#pragma clang fp contract(off)  // (dd.hpp)
 
 namespace eprl {
 
 namespace {
-
-struct dd {
-  double hi, lo;
-};
-
-__device__ __forceinline__ dd two_sum(double a, double b) {
-  double s = a + b;
-  double bb = s - a;
-  double e = (a - (s - bb)) + (b - bb);
-  return {s, e};
-}
-
-__device__ __forceinline__ dd fast_two_sum(double a, double b) {
-  double s = a + b;
-  return {s, b - (s - a)};
-}
-
-__device__ __forceinline__ dd dd_add(dd a, dd b) {
-  dd s = two_sum(a.hi, b.hi);
-  dd t = two_sum(a.lo, b.lo);
-  s.lo += t.hi;
-  s = fast_two_sum(s.hi, s.lo);
-  s.lo += t.lo;
-  return fast_two_sum(s.hi, s.lo);
-}
-
-__device__ __forceinline__ dd dd_mul(dd a, dd b) {
-  double p = a.hi * b.hi;
-  double e = __builtin_fma(a.hi, b.hi, -p);
-  e += a.hi * b.lo + a.lo * b.hi;
-  return fast_two_sum(p, e);
-}
-
-// Quotient of two exactly representable integers as a double-double.
-__device__ __forceinline__ dd dd_ratio(double num, double den) {
-  double inv = 1.0 / den;
-  double q = num * inv;                    // within two ulp
-  double r = __builtin_fma(-q, den, num);  // exact remainder
-  return fast_two_sum(q, r * inv);
-}
-
-// sqrt(q) of a small integer q as a double-double.
-__device__ __forceinline__ dd dd_sqrt_int(double q) {
-  double s = __builtin_sqrt(q);
-  double r = __builtin_fma(-s, s, q);
-  return fast_two_sum(s, r / (2.0 * s));
-}
 
 // Running product of factors sqrt(n!) and 1 / sqrt(n!): m * 2^e.
 struct FactProduct {
