@@ -48,17 +48,6 @@ __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
 constexpr int AT = 512;  // threads per workgroup
 
-// Division by a size that is the same for the whole kernel, as a multiply-high by the rounded-up
-// reciprocal: exact for dividends and divisors below 2^16 (the item indices of the loops below),
-// and one instruction where the generic integer division takes dozens.
-struct FastDiv {
-  uint32_t m;
-  int d;
-  __device__ explicit FastDiv(int d_)
-      : m(d_ > 1 ? (uint32_t)((0x100000000ull + (uint64_t)d_ - 1) / (uint64_t)d_) : 0u), d(d_) {}
-  __device__ int operator()(int q) const { return d > 1 ? (int)__umulhi((uint32_t)q, m) : q; }
-};
-
 // The five boundary vectors (device, complex interleaved), passed by value.
 struct PsiPtrs {
   const double *p[5];

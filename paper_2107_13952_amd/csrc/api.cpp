@@ -34,7 +34,7 @@ struct BatchEntry {
 struct BatchSeq {
   std::vector<BatchEntry> ent;
   std::vector<RingParams> params;  // of the factorised configurations (BatchEntry::index)
-  int nring = 0, ncu = 256;
+  int ncu = 256;
   // One launch per group of items [begin, end) of the work list, estimated cost (sum of item costs):
   // a variant and workgroup size of the x-outer kernel within a pass, one workgroup per item; or a
   // tile class and nd of ring.hip's kernels, persistent, work-queue counter `group index`.
@@ -1147,7 +1147,6 @@ int layout_batch(eprl_ctx *c, int n, const int *two_j, const int *dl, const doub
   seq.ent = std::move(ent);
   seq.params = std::move(params);
   seq.npass = npass;
-  seq.nring = nring;
   seq.groups = std::move(groups);
   seq.tables = jtables;
   seq.reduce = jreduce;
@@ -1685,7 +1684,7 @@ int eprl_threejm_batch(eprl_ctx *c, int n, const int *args, double *out) {
   std::memcpy(st, args, bytes);
   rc = upload(c, c->ws, bytes);
   if (rc) return rc;
-  HIP_TRY(c, launch_threejm_batch(reinterpret_cast<int *>(c->ws), n, out, c->ft, c->fact_max, c->stream));
+  HIP_TRY(c, launch_threejm_batch(reinterpret_cast<int *>(c->ws), n, out, c->ft, c->stream));
   return EPRL_OK;
 }
 

@@ -85,15 +85,6 @@ __device__ __forceinline__ d4v mfma(double a, double b, d4v c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Quotient by a divisor that is the same for the whole kernel, dividends below 2^16.
-struct FastDiv {
-  uint32_t m;
-  int d;
-  __device__ explicit FastDiv(int d_)
-      : m(d_ > 1 ? (uint32_t)((0x100000000ull + (uint64_t)d_ - 1) / (uint64_t)d_) : 0u), d(d_) {}
-  __device__ int operator()(int q) const { return d > 1 ? (int)__umulhi((uint32_t)q, m) : q; }
-};
-
 constexpr int kPrepThreads = 256;
 
 // The pairs (o24, o25) of a core range, first .. first + n - 1, and how many o25 they hold (from that of

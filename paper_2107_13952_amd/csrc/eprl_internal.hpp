@@ -184,6 +184,17 @@ struct IndexDiv {
 };
 
 #ifdef __HIPCC__
+// Division by a size that is the same for the whole kernel, as a multiply-high by the rounded-up
+// reciprocal: exact for dividends and divisors below 2^16, and one instruction where the generic integer
+// division takes dozens.
+struct FastDiv {
+  uint32_t m;
+  int d;
+  __device__ explicit FastDiv(int d_)
+      : m(d_ > 1 ? (uint32_t)((0x100000000ull + (uint64_t)d_ - 1) / (uint64_t)d_) : 0u), d(d_) {}
+  __device__ int operator()(int q) const { return d > 1 ? (int)__umulhi((uint32_t)q, m) : q; }
+};
+
 // The job of block b (the last whose first block is not past it); b becomes the block within the job.
 __device__ __forceinline__ int batch_job(const BatchJob *jobs, int njobs, int &b) {
   int lo = 0, hi = njobs - 1;
@@ -308,7 +319,7 @@ struct FourjmSet {
 };
 hipError_t launch_fourjm_tables(const FourjmSet *sets_dev, int nsets, int max_entries,
                                 const int *mtuples_dev, double *out, FactTables fact, hipStream_t s);
-hipError_t launch_threejm_batch(const int *args, int n, double *out, FactTables fact, int fact_max, hipStream_t s);
+hipError_t launch_threejm_batch(const int *args, int n, double *out, FactTables fact, hipStream_t s);
 // A boost matrix element d^{(rho, k = j)}_{j l m}(r): spins, the Y-map rho = gamma (j + 1), the
 // phase factor of the basis convention, and the Jacobi-form constants of the two SU(2) d
 // functions it integrates, d^j_{j m} and d^l_{j m}.

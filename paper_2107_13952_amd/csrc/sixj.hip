@@ -163,7 +163,7 @@ __global__ void fourjm_table_kernel(const FourjmSet *sets, const int *mtuples, d
   out[st.out + idx] = fourjm_device(st.j, mtuples + st.mt + 4 * m, st.two_lo + 2 * i, ft);
 }
 
-__global__ void threejm_batch_kernel(const int *args, int n, double *out, FactTables ft, int fact_max) {
+__global__ void threejm_batch_kernel(const int *args, int n, double *out, FactTables ft) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n) return;
   const int *a = args + 6 * idx;
@@ -418,9 +418,9 @@ hipError_t launch_fourjm_tables(const FourjmSet *sets_dev, int nsets, int max_en
   return hipGetLastError();
 }
 
-hipError_t launch_threejm_batch(const int *args, int n, double *out, FactTables ft, int fact_max, hipStream_t s) {
+hipError_t launch_threejm_batch(const int *args, int n, double *out, FactTables ft, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  threejm_batch_kernel<<<(n + 255) / 256, 256, 0, s>>>(args, n, out, ft, fact_max);
+  threejm_batch_kernel<<<(n + 255) / 256, 256, 0, s>>>(args, n, out, ft);
   return hipGetLastError();
 }
 
