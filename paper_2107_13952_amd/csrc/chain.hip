@@ -297,8 +297,10 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
   const int sig0 = cb * rp.ctb * 16, CW = imin(C - sig0, rp.ctb * 16);  // columns of this block
   const int S = rp.ts, t5n = nd * rp.n4t * S, t2n = nd * rp.n3t * S;
   // LDS: T rows of the unit between zero rows (a k outside a spin's rows reads another spin's or a zero
-  // row, times a zero booster entry), G, H.
-  double *T5s = smem + rp.tpre * S, *T2s = T5s + t5n;
+  // row, times a zero booster entry; never a row of the other table, whose infinities or NaN, from a
+  // booster entry of another edge, would then show up in entries that do not depend on it), G, H.
+  const int t2at = t5n + rp.tmid * S;
+  double *T5s = smem + rp.tpre * S, *T2s = T5s + t2at;
   double *Gs = T2s + t2n + rp.tpost * S, *Hs = Gs + rp.sp * 8 * R;
   const int nK3 = rp.K_n[1];
   const double *U3 = rp.U3;
@@ -510,7 +512,7 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
     for (;;) {
       // ---- G and H, the wavefronts' chunks of G from the first on, of H from the last
       side_stage(sg, Gs, st.t5, st.n4, st.m4, w, mg);
-      side_stage(sh, Hs, t5n + st.t2, st.n3, st.m3, nw - 1 - w, mh);
+      side_stage(sh, Hs, t2at + st.t2, st.n3, st.m3, nw - 1 - w, mh);
       ChainStep sn = st;
       bool more = st.more != 0;
       if (more) {
@@ -680,15 +682,20 @@ bool chain_plan(Plan &p) {
   const int R = d5 * d4, C = d3 * d2, RT = (R + 15) / 16;
   g.wm = w;
   // Rows that row offsets reach before the first T5 row and past the last T2 row (positions run up to
-  // fifteen past a window's end).
-  g.tpre = g.tpost = 0;
+  // fifteen past a window's end), and between the tables: past T5 and before T2 for the positions that are
+  // used, up to three past a window's end.
+  g.tpre = g.tmid = g.tpost = 0;
   const int wlo[2] = {p.K[1].lo2, p.K[2].lo2}, whi[2] = {hi2(p.K[1]), hi2(p.K[2])};
+  for (int o = 0; o < nd; ++o) {
+    g.tmid = std::max(g.tmid, (whi[1] + 6 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t);
+    g.tmid = std::max(g.tmid, (chain_klo(J, wlo, whi, true, o) - wlo[0]) / 2 - o * g.n3t);
+  }
   for (int o = 0; o < nd; ++o) {
     g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, false, o) - wlo[1]) / 2 - o * g.n4t);
     g.tpost = std::max(g.tpost, (whi[0] + 30 - chain_klo(J, wlo, whi, true, o)) / 2 + 1 - (nd - o) * g.n3t + 1);
-    // T5's offsets past its rows and T2's before them stay inside the T rows.
-    g.tpost = std::max(g.tpost, (whi[1] + 30 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t - nd * g.n3t + 1);
-    g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, true, o) - wlo[0]) / 2 - o * g.n3t - nd * g.n4t);
+    // T5's offsets past its rows (unused positions) and T2's before them stay inside the T rows.
+    g.tpost = std::max(g.tpost, (whi[1] + 30 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t - g.tmid - nd * g.n3t + 1);
+    g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, true, o) - wlo[0]) / 2 - o * g.n3t - g.tmid - nd * g.n4t);
   }
   g.ts = (std::max(d5, d2) + 1) & ~1;
   g.mr4 = chain_mrow(nd, d4);
@@ -728,7 +735,7 @@ size_t chain_smem_bytes(const Plan &p) {
   const int R = p.i[4].n * p.i[3].n, C = p.i[2].n * p.i[1].n;
   const int CW = std::min(C, g.ctb * 16);
   // The last row of G or H is read past its end by up to 31 columns (results never used).
-  return sizeof(double) * ((size_t)(p.nd * (g.n4t + g.n3t) + g.tpre + g.tpost) * g.ts + (size_t)g.sp * 8 * (R + CW) + 64);
+  return sizeof(double) * ((size_t)(p.nd * (g.n4t + g.n3t) + g.tpre + g.tmid + g.tpost) * g.ts + (size_t)g.sp * 8 * (R + CW) + 64);
 }
 
 hipError_t chain_init_attributes() {
@@ -754,6 +761,7 @@ void chain_params(const Plan &p, double *derived, RingParams &rp) {
   rp.sp = g.sp;
   rp.wm = g.wm;
   rp.tpre = g.tpre;
+  rp.tmid = g.tmid;
   rp.tpost = g.tpost;
   rp.lds = g.lds;
   rp.mr4 = g.mr4;

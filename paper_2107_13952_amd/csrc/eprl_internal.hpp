@@ -29,7 +29,7 @@ struct ChainGeom {
   int n4t = 0, n3t = 0;   // k4 (k3) values per l45 (l23) of its derived tables
   int ts = 0;             // entries of a row of those tables (i5 or i2, padded)
   int wm = 0, sp = 0;     // widest k4 or k3 window; eights of positions of G and H
-  int tpre = 0, tpost = 0;  // zero rows before and after the T rows in LDS
+  int tpre = 0, tmid = 0, tpost = 0;  // zero rows before, between and after the T rows in LDS
   int nrb = 1, ctb = 1;   // column blocks, column tiles per block
   int waves = 1;          // wavefronts per workgroup
   int lds = 0;            // LDS of a workgroup, in doubles
@@ -146,7 +146,7 @@ struct RingParams {
   // (0) and k4 (1), range of cores; bounds then holds units (l24, l25, x, l35).
   double *T5, *T2, *M4, *M3;
   ChainStep *steps;
-  int n4t, n3t, ts, wm, sp, tpre, tpost, ctb, nx, lds, mr4, mr3;
+  int n4t, n3t, ts, wm, sp, tpre, tmid, tpost, ctb, nx, lds, mr4, mr3;
   int wlo[2], whi[2];
   int core_lo, core_hi;
 };

@@ -111,6 +111,31 @@ def test_widest_tiles_many_shells(lib, torch, two_j, dl, core, dims):
     assert np.abs(a.cpu().numpy() - ref).max() <= TOL * scale
 
 
+# A tensor entry A(i1..i5) depends on the booster entries of its own i2..i5 only: with one infinite or NaN
+# booster entry every other entry has the bits of the call without it (zeros that pad the tables meet no
+# infinity of another edge).
+@pytest.mark.parametrize("two_j,dl", [([9, 8, 12, 9, 5, 11, 3, 10, 7, 7], 3), ([4] * 10, 2), ([3, 2, 3, 2, 4, 3, 4, 3, 3, 3], 4),
+                                      ([13, 10, 11, 12, 10, 14, 11, 13, 13, 10], 2), ([2, 3, 2, 1, 3, 2, 3, 1, 1, 3], 2)])
+def test_infinities_stay_in_their_entries(lib, torch, two_j, dl):
+    dims, _, offs = lib.layout(two_j, dl)
+    n3 = (dl + 1) ** 3
+    b = workloads.synthetic_boosters(800 + dl, R.block_shapes(two_j, dl))
+    clean = lib.vertex_tensor(two_j, dl, 1.2, torch.from_numpy(b).cuda())
+    rng = np.random.default_rng(800 + dl)
+    for trial in range(24):
+        at = int(rng.integers(len(b)))
+        block = int(np.searchsorted(offs, at, side="right")) - 1
+        edge, columns = block // n3, int(offs[block + 1] - offs[block]) // dims[block // n3 + 1]
+        row = (at - int(offs[block])) // columns
+        print(f"infinities {two_j} dl={dl} entry {at} edge {edge + 2} row {row}", flush=True)
+        c = b.copy()
+        c[at] = (np.nan, np.inf, -np.inf)[trial % 3]
+        a = lib.vertex_tensor(two_j, dl, 1.2, torch.from_numpy(c).cuda())
+        rest = [q for q in range(dims[edge + 1]) if q != row]
+        assert torch.equal(a.index_select(edge + 1, torch.tensor(rest, dtype=torch.int64, device="cuda")),
+                           clean.index_select(edge + 1, torch.tensor(rest, dtype=torch.int64, device="cuda")))
+
+
 # A layout kept from call to call must follow the buffers of each call: two batches of one shape
 # (factorised configurations of both kinds of tables and a per-shell one), called in turn with other
 # boosters and outputs, on the default and on a side stream, equal the plain calls bit by bit.
