@@ -1808,12 +1808,14 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     fact = std::max(fact, std::max(b.lb[0] + b.lb[1], b.lb[2] + b.lb[3]) + kmax);
   }
   groups.push_back((int)keys.size());
-  // The blocks of each edge as a matrix over pairs of key bases.
+  // The blocks of each edge as a matrix over pairs of key bases, in tiles; a tile costs as much as about
+  // sixteen blocks by themselves (spins 7, an edge: 153 us; eight blocks 71, sixteen about 150).
+  constexpr int kBoosterTileBlocks = 16;
   BoosterGrid grid[4];
-  std::vector<int> pairs, bmap, tiles;
+  std::vector<int> pairs, bmap, tiles, singles;
   for (int e = 0; e < 4; ++e) {
     std::map<std::pair<int, int>, int> id[2];
-    std::vector<int> list[2], cell;  // (row, column, offset in I) of each block
+    std::vector<int> list[2], cell;  // (row, column, block) of each block
     for (int q = 0; q < nb; ++q) {
       const int *bi = &binfo[9 * (size_t)q];
       if (bi[0] != e || bi[3] == 0) continue;
@@ -1823,7 +1825,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
         if (it.second) list[h].insert(list[h].end(), {k.first, k.second});
         cell.push_back(it.first->second);
       }
-      cell.push_back(bi[4]);
+      cell.push_back(q);
     }
     BoosterGrid &g = grid[e];
     g.M = M_edge[e];
@@ -1835,14 +1837,15 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     pairs.insert(pairs.end(), list[1].begin(), list[1].end());
     g.map = (int)bmap.size();
     bmap.resize(bmap.size() + (size_t)g.nrow * g.ncol, -1);
-    for (size_t k = 0; k < cell.size(); k += 3) bmap[g.map + (size_t)cell[k] * g.ncol + cell[k + 1]] = cell[k + 2];
-    for (int r = 0; r < g.nrow; r += 16)
-      for (int cl = 0; cl < g.ncol; cl += 16) {
-        bool any = false;
-        for (int i = r; i < std::min(r + 16, g.nrow) && !any; ++i)
-          for (int j = cl; j < std::min(cl + 16, g.ncol) && !any; ++j) any = bmap[g.map + (size_t)i * g.ncol + j] >= 0;
-        if (any) tiles.insert(tiles.end(), {e, r, cl, 0});
-      }
+    const int tcols = (g.ncol + 15) / 16;
+    std::vector<int> held((size_t)((g.nrow + 15) / 16) * tcols, 0);  // blocks of each tile
+    auto tile_of = [&](size_t k) -> int & { return held[(size_t)(cell[k] / 16) * tcols + cell[k + 1] / 16]; };
+    for (size_t k = 0; k < cell.size(); k += 3) ++tile_of(k);
+    for (size_t k = 0; k < cell.size(); k += 3)
+      if (tile_of(k) < kBoosterTileBlocks) singles.push_back(cell[k + 2]);
+      else bmap[g.map + (size_t)cell[k] * g.ncol + cell[k + 1]] = binfo[9 * (size_t)cell[k + 2] + 4];
+    for (size_t t = 0; t < held.size(); ++t)
+      if (held[t] >= kBoosterTileBlocks) tiles.insert(tiles.end(), {e, (int)(t / tcols) * 16, (int)(t % tcols) * 16, 0});
   }
   if (fact / 2 + 2 > 2 * kSixjMaxTwo + 2) return fail(c, EPRL_ERANGE, "spins beyond the 3jm range");
   rc = ensure_fact(c, fact / 2 + 2);
@@ -1869,7 +1872,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
   const size_t o_sets = take(sets.size() * sizeof(FourjmSet));
   const size_t o_groups = take(groups.size() * sizeof(int));
   const size_t o_pairs = take(pairs.size() * sizeof(int)), o_bmap = take(bmap.size() * sizeof(int));
-  const size_t o_tiles = take(tiles.size() * sizeof(int));
+  const size_t o_tiles = take(tiles.size() * sizeof(int)), o_singles = take(singles.size() * sizeof(int));
   const size_t static_bytes = off;
   const size_t o_coef = take((size_t)(ci_total + ck_total) * sizeof(double));
   const size_t o_I = take((size_t)I_total * 4 * sizeof(double));
@@ -1907,6 +1910,7 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
       if (!pairs.empty()) std::memcpy(stg + o_pairs, pairs.data(), pairs.size() * sizeof(int));
       if (!bmap.empty()) std::memcpy(stg + o_bmap, bmap.data(), bmap.size() * sizeof(int));
       if (!tiles.empty()) std::memcpy(stg + o_tiles, tiles.data(), tiles.size() * sizeof(int));
+      if (!singles.empty()) std::memcpy(stg + o_singles, singles.data(), singles.size() * sizeof(int));
       rc = upload(c, ws, static_bytes);
       if (rc) return rc;
       HIP_TRY(c, launch_fourjm_tables(reinterpret_cast<const FourjmSet *>(ws + o_sets), (int)sets.size(),
@@ -1957,6 +1961,8 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     bp.bmap = reinterpret_cast<const int *>(ws + o_bmap);
     bp.tiles = reinterpret_cast<const int *>(ws + o_tiles);
     bp.ntiles = (int)tiles.size() / 4;
+    bp.singles = reinterpret_cast<const int *>(ws + o_singles);
+    bp.nsingles = (int)singles.size();
     HIP_TRY(c, launch_booster_dfun(bp, c->stream));
     HIP_TRY(c, launch_booster_integrals(bp, c->stream));
     HIP_TRY(c, launch_booster_assemble(bp, reinterpret_cast<double *>(ws + o_stat3), c->stream));

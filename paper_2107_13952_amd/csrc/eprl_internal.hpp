@@ -358,12 +358,12 @@ struct BoosterParams {
   int nblocks, Mmax;
   // grouped for the kernels: keys of one (j, l) together, group g from groups[g]; the blocks' matrices,
   // bmap[row][column] the block's offset in I (-1: no block), and their 16 x 16 tiles (edge, row,
-  // column, 0)
+  // column, 0); the blocks of sparse tiles by themselves
   const int *groups;
   int ngroups;
   BoosterGrid grid[4];
-  const int *pairs, *bmap, *tiles;
-  int ntiles;
+  const int *pairs, *bmap, *tiles, *singles;
+  int ntiles, nsingles;
 };
 hipError_t launch_booster_dfun(const BoosterParams &bp, hipStream_t s);
 hipError_t launch_booster_integrals(const BoosterParams &bp, hipStream_t s);

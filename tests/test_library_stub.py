@@ -184,8 +184,7 @@ def core_range_makes_its_own_derived_tables(lib):
 # The booster builder loads its lists and 4jm tables again whenever a refinement replaces the workspace,
 # also by one at the same address.
 def boosters_follow_the_workspace(lib):
-    lib.stub.stub_read.argtypes = [ctypes.c_double]
-    lib.stub.stub_read(1.0)   # an error above the tolerance: n = 16, 32, ..., 512, each with a larger workspace
+    lib.stub.stub_read(ctypes.c_double(1.0))   # an error above the tolerance: n = 16, 32, ..., 512, each with a larger workspace
     for reuse in (0, 1):
         ctx = lib.context()
         assert lib.lib.eprl_sixj_batch(ctx, 1, (ctypes.c_int * 6)(*[200] * 6), lib.buf) == OK
@@ -194,12 +193,29 @@ def boosters_follow_the_workspace(lib):
         info = (ctypes.c_double * 3)()
         assert lib.lib.eprl_boosters(ctx, (ctypes.c_int * 10)(*[2] * 10), 1, ctypes.c_double(1.2), ctypes.c_double(0.5),
                                      lib.buf, info) == OK
-        assert info[2] == 512 and lib.launches("booster_integrals_kernel") == 6
+        assert info[2] == 512 and lib.launches("integrals_kernel") == 6
         assert lib.launches("fourjm_table_kernel") == 6
         lib.lib.eprl_destroy(ctx)
 
 
-SCENARIOS = [boosters_follow_the_workspace, core_range_makes_its_own_derived_tables, autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
+# Edges of few blocks (one at dl = 0, eight at dl = 1) take their r integrals block by block, not by tiles of
+# 16 x 16 blocks; edges of many by tiles, but for a remainder of fewer than sixteen blocks.
+def boosters_of_few_blocks(lib):
+    lib.stub.stub_read(ctypes.c_double(0.0))
+    lib.stub.stub_watch(b"booster_block_integrals_kernel")
+    for two_j, dl, tiles, blocks in ((14, 0, 0, 4), (2, 1, 0, 32), (2, 3, 1, 0), (1, 6, 1, 18)):  # (18 of 28 not empty)
+        lib.stub.stub_clear()
+        assert lib.lib.eprl_boosters(lib.ctx, (ctypes.c_int * 10)(*[two_j] * 10), dl, ctypes.c_double(1.2),
+                                     ctypes.c_double(0.5), lib.buf, None) == OK
+        assert lib.launches("booster_integrals_kernel") == tiles
+        assert lib.launches("booster_block_integrals_kernel") == (1 if blocks else 0)
+        if blocks:
+            m = sum(abs(a + b + c) <= two_j for a in range(-two_j, two_j + 1, 2) for b in range(-two_j, two_j + 1, 2)
+                    for c in range(-two_j, two_j + 1, 2))
+            assert lib.stub.stub_grid() == blocks * ((m + 3) // 4)
+
+
+SCENARIOS = [boosters_of_few_blocks, boosters_follow_the_workspace, core_range_makes_its_own_derived_tables, autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
