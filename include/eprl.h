@@ -92,8 +92,9 @@ int eprl_set_stream(eprl_ctx *ctx, void *hip_stream);
 int eprl_set_algorithm(eprl_ctx *ctx, int algo);
 
 /* Work split of the factorised order per tile class (the class is out[4] of eprl_count_work):
- * the shell sum is cut into chunks of equal estimated cost, about target_workgroups
- * workgroups per launch (0: the default, 8192), and, except in the kernel with x outside the
+ * the shell sum is cut into chunks of equal estimated cost, at most about target_workgroups
+ * workgroups per launch (0: the default, 8192; the kernel with x outside the virtual spins takes
+ * fewer where a chunk's work would not pay for its partial sums), and, except in the kernel with x outside the
  * virtual spins, staging_level picks how many booster blocks
  * of a core are held in LDS (2: all four, 1: the two of the second stage, 0: none, -1: the
  * most that fits; a level that does not fit falls back to the next lower one).  The paper

@@ -1,6 +1,7 @@
 // Host planner: admissibility, intertwiner ranges, packed booster layout, global index
 // windows of the 6j tables (Sec. 2 eq. (vertex-ampl); Sec. 3.1 framed algorithm, steps 1-4).
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <sstream>
 
@@ -28,6 +29,17 @@ Range coupled(int a, int b, int c, int d) {
   r.lo2 = lo;
   r.n = (hi - lo) / 2 + 1;
   return r;
+}
+
+// Number of values v = lo, lo + 2, ... (n of them) with |a - v| <= x <= a + v, i.e. in the
+// triad (a, v, x).  All two-units.
+int triad_count(int lo, int n, int a, int x) {
+  if (n <= 0) return 0;
+  const int hi = lo + 2 * (n - 1);
+  const int vlo = std::max(lo, std::abs(x - a)), vhi = std::min(hi, x + a);
+  if (vlo > vhi) return 0;
+  if (((vlo - lo) & 1) != 0) return 0;  // parity mismatch: no value closes the triad
+  return (vhi - vlo) / 2 + 1;
 }
 
 // Smallest |a - b| and largest a + b over a in range ra and fixed b.
@@ -319,6 +331,26 @@ int chain_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
   // Units of a core range: those of its (l24, l25) pairs; a partial pair keeps the whole pair's cost.
   const int pair_lo = core_lo / nd2, pair_hi = core_hi > core_lo ? (core_hi + nd2 - 1) / nd2 : pair_lo;
   const int u_lo = pair_lo * nx * nd, u_hi = (all ? nd2 : pair_hi) * nx * nd;
+  // Every workgroup writes a slice of A that the reduction reads: about 3.6 ps an entry for both.  A step of
+  // one wavefront takes 65 ps of the whole chip (256 CUs).  With nwg = r rounds of the resident workgroups
+  // the last round is half empty on average, so r = sqrt(work / (2 slices of a round)) balances the two, one
+  // round at least.  (All of target_wg, or every unit by itself, for whatever work: two_j = 12, 1 shell 343 us
+  // at 1300 workgroups, 208 at 256 (ring.hip's kernels 246); two_j = 6, 3 shells 158 us at 5800, 100 at 1024;
+  // two_j = 8, 3 shells 393 at 5100, 302 at 2048; two_j = 6, 8 shells and two_j = 10 .. 14, 6 shells are
+  // fastest, and flat, from 4096 to 16384.)
+  double work = 0.0;
+  for (int o24 = pair_lo / nd; o24 < nd && o24 * nd < pair_hi; ++o24)
+    for (int xi = 0; xi < nx; ++xi) {
+      double c = 0.0;
+      for (int o35 = 0; o35 < nd; ++o35) c += unit[((size_t)o24 * nx + xi) * nd + o35];
+      for (int o25 = 0; o25 < nd; ++o25)
+        if (o24 * nd + o25 >= pair_lo && o24 * nd + o25 < pair_hi)
+          work += c * triad_count(p.i[0].lo2, d1, J[L25] + 2 * o25, p.X.lo2 + 2 * xi);
+    }
+  const int resident = 256 * std::max(1, std::min(8 / g.waves, (int)(kChainMaxLds / chain_smem_bytes(p))));
+  const double slices = 3.6e-3 * resident * ((double)p.a_size / (d1 * g.nrb));
+  const double rounds = std::sqrt(65e-3 * work * g.nrb * g.waves / (2.0 * slices));
+  target_wg = (int)std::min<double>(target_wg, resident * std::max(1.0, rounds));
   int nchunk = std::max(1, target_wg / (d1 * g.nrb));
   nchunk = (int)std::min<int64_t>(nchunk, std::max<int64_t>(1, (int64_t)(kRingMaxPartialBytes / ((size_t)p.a_size * sizeof(double)))));
   nchunk = std::min(nchunk, std::max(1, u_hi - u_lo));
@@ -385,21 +417,6 @@ void count_terms(const Plan &p, int64_t &live, double &terms) {
     terms += prod;
   }
 }
-
-namespace {
-
-// Number of values v = lo, lo + 2, ... (n of them) with |a - v| <= x <= a + v, i.e. in the
-// triad (a, v, x).  All two-units.
-int triad_count(int lo, int n, int a, int x) {
-  if (n <= 0) return 0;
-  const int hi = lo + 2 * (n - 1);
-  const int vlo = std::max(lo, std::abs(x - a)), vhi = std::min(hi, x + a);
-  if (vlo > vhi) return 0;
-  if (((vlo - lo) & 1) != 0) return 0;  // parity mismatch: no value closes the triad
-  return (vhi - vlo) / 2 + 1;
-}
-
-}  // namespace
 
 void count_work(const Plan &p, double out[5]) {
   const int nd = p.nd, nd3 = nd * nd * nd;

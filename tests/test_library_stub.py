@@ -215,7 +215,24 @@ def boosters_of_few_blocks(lib):
             assert lib.stub.stub_grid() == blocks * ((m + 3) // 4)
 
 
-SCENARIOS = [boosters_of_few_blocks, boosters_follow_the_workspace, core_range_makes_its_own_derived_tables, autotune_tries_the_default, batch_runs_with_less_memory, vertex_runs_without_memory_for_derived_tables, factorial_table_stays_when_it_cannot_grow]
+# Few shells at large spins: no more workgroups than their partial sums are worth (one to two rounds of the
+# chip); many shells: the full number (11 x 208 where the partial sums reach their 256 MB).
+def small_sums_are_split_less(lib):
+    lib.stub.stub_watch(b"chain_kernel")
+    for two_j, dl, lo, hi in (([12] * 10, 1, 200, 512), ([10] * 10, 1, 200, 768), ([14] * 10, 0, 200, 512),
+                              ([6] * 10, 3, 1024, 3072), ([6] * 10, 8, 8000, 8192), (LARGE[1][0], 6, 2288, 2288)):
+        assert lib.vertex(two_j, dl) == OK
+        assert lo <= lib.stub.stub_grid() <= hi, (two_j, dl, lib.stub.stub_grid())
+
+
+SCENARIOS = [factorial_table_stays_when_it_cannot_grow,
+             vertex_runs_without_memory_for_derived_tables,
+             batch_runs_with_less_memory,
+             autotune_tries_the_default,
+             core_range_makes_its_own_derived_tables,
+             boosters_follow_the_workspace,
+             boosters_of_few_blocks,
+             small_sums_are_split_less]
 
 
 @pytest.mark.parametrize("scenario", [f.__name__ for f in SCENARIOS])
