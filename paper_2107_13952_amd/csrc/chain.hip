@@ -681,10 +681,11 @@ bool chain_plan(Plan &p) {
   if (w > 32) return false;
   const int R = d5 * d4, C = d3 * d2, RT = (R + 15) / 16;
   g.wm = w;
-  // Rows that row offsets reach before the first T5 row and past the last T2 row (positions run up to
-  // fifteen past a window's end), and between the tables: past T5 and before T2 for the positions that are
-  // used, up to three past a window's end.
+  // Rows that row offsets reach before the first T5 row, and past T5, before T2 and past T2 at the positions
+  // that are used, up to three past a window's end.  Positions run up to fifteen past it: `over` rows past
+  // T2's last, where G and H may lie.
   g.tpre = g.tmid = g.tpost = 0;
+  int over = 0;
   const int wlo[2] = {p.K[1].lo2, p.K[2].lo2}, whi[2] = {hi2(p.K[1]), hi2(p.K[2])};
   for (int o = 0; o < nd; ++o) {
     g.tmid = std::max(g.tmid, (whi[1] + 6 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t);
@@ -692,9 +693,9 @@ bool chain_plan(Plan &p) {
   }
   for (int o = 0; o < nd; ++o) {
     g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, false, o) - wlo[1]) / 2 - o * g.n4t);
-    g.tpost = std::max(g.tpost, (whi[0] + 30 - chain_klo(J, wlo, whi, true, o)) / 2 + 1 - (nd - o) * g.n3t + 1);
-    // T5's offsets past its rows (unused positions) and T2's before them stay inside the T rows.
-    g.tpost = std::max(g.tpost, (whi[1] + 30 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t - g.tmid - nd * g.n3t + 1);
+    g.tpost = std::max(g.tpost, (whi[0] + 6 - chain_klo(J, wlo, whi, true, o)) / 2 + 1 - (nd - o) * g.n3t);
+    over = std::max(over, (whi[0] + 30 - chain_klo(J, wlo, whi, true, o)) / 2 + 1 - (nd - o) * g.n3t + 1);
+    over = std::max(over, (whi[1] + 30 - chain_klo(J, wlo, whi, false, o)) / 2 + 1 - (nd - o) * g.n4t - g.tmid - nd * g.n3t + 1);
     g.tpre = std::max(g.tpre, (chain_klo(J, wlo, whi, true, o) - wlo[0]) / 2 - o * g.n3t - g.tmid - nd * g.n4t);
   }
   g.ts = (std::max(d5, d2) + 1) & ~1;
@@ -706,9 +707,11 @@ bool chain_plan(Plan &p) {
   // column blocks as keep the tiles of a wavefront and the LDS in bounds.
   const int CT = (C + 15) / 16, rt = RT > 1 ? 2 : 1;
   g.nrb = (CT + kChainCT - 1) / kChainCT;
+  const int tpost = g.tpost;
   for (;; ++g.nrb) {
     if (g.nrb > CT) return false;
     g.ctb = (CT + g.nrb - 1) / g.nrb;
+    g.tpost = std::max(tpost, over - g.sp * 8 * (R + std::min(C, g.ctb * 16)) / g.ts);
     if (chain_smem_bytes(p) <= kChainMaxLds) break;
   }
   g.waves = (RT + rt - 1) / rt;
