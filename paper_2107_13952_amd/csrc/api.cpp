@@ -700,10 +700,10 @@ void booster_r_nodes(int n, const std::vector<double> (&gx)[2], const std::vecto
 //
 // All configurations of a batch share one dedicated workspace laid out once per batch shape:
 // for each configuration its 6j tables, booster offsets and k ranges, and its per-chunk partial
-// sums; then the RingParams array and the work list of the persistent ring kernel.  The
-// device work (one launch each for the 6j tables, the derived tables and the reductions of every
-// configuration, one per group of work items) is enqueued on each call; the layout is kept while the
-// shape of the batch (spins, shell counts, algorithm, tuning) stays the same, the pointers are uploaded
+// sums; then the RingParams array and the work lists.  The device work (one launch each for the 6j
+// tables, the derived tables and the reductions of every configuration, one per group of work items)
+// is enqueued on each call; the layout is kept while the shape of the batch (spins, shell counts,
+// algorithm, tuning) stays the same, the pointers are uploaded
 // with each call.  (A captured graph held the pointers: a call with other buffers planned and captured
 // again, host work of 39 ms for 64 irregular configurations.)  Chunking per configuration equals the
 // single-configuration path, so every tensor is bitwise identical to a separate eprl_vertex_tensor call.

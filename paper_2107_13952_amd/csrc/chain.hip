@@ -31,8 +31,9 @@
 // here (2.61 ms for the kernel with the half chains inside the core loop), at two_j = 10 .. 14, 6
 // shells 5.35 ms (12.3).  The matrix cores are busy 38 % of the cycles; a wavefront spends a third of
 // its time in waits (the LDS operands of the 4 x 4 products, U3, two barriers a step) and issues 230
-// scalar and 260 vector instructions a step around 52 matrix instructions.  The accumulators allow two
-// wavefronts per SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no
+// scalar and 260 vector instructions a step around 52 matrix instructions.  Every variant spills 94 to 130
+// scalar registers (two sides, two steps, the unit's counters, pointers and strides are live at once), and
+// each reload of one is a vector instruction.  The accumulators allow two wavefronts per SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no
 // change, fewer workgroups fit), 16 x 16 tiles for G and H of large dimensions (6.3 -> 6.7 ms), row
 // blocks (each repeats H: 6.3 -> 11.0 ms for two), one wavefront per workgroup without barriers (1.49
 // -> 1.69 ms), rt = 1 (6.95 -> 8.36 ms: each H operand then serves one row tile).
@@ -603,9 +604,12 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
 // Wavefronts per SIMD the registers are budgeted for, and the most wavefronts of a workgroup.
 template <int RT, int CT, int KS>
 constexpr int chain_waves() {
-  // Accumulators and P; booster operands; U3, addresses, operands in flight.  The last is what leaves no
-  // spills: 80 (one wavefront more for the small tiles) was slower, 244 against 205 us for spins 3 .. 12 / 2,
-  // 5 shells.
+  // Accumulators and P; booster operands; U3, addresses, operands in flight.  With 80 for the last, one
+  // wavefront more for the small tiles, these spilled: 244 against 205 us for spins 3 .. 12 / 2, 5 shells.
+  // Vector registers spilled as it is, of two row tiles: none up to eight column tiles with one or two spin
+  // groups, from nine on 3 to 84; with three groups 2 to 20 from five column tiles on (none at seven), 122
+  // and 136 at ten and eleven; with four 5 to 78 from three on, 93 and 188 at ten and eleven.  Of one row
+  // tile, four for <1, 2, 2> and <1, 5, 1>, none else with up to two groups.
   constexpr int need = 8 * RT * CT + 8 * RT + (RT * CT >= 14 ? 12 : 24) * KS + 104;
   return need <= 128 ? 4 : need <= 176 ? 3 : 2;
 }
@@ -634,8 +638,10 @@ void chain_kernel(const RingParams *__restrict__ cfgs, const int *__restrict__ i
 }
 
 // Kernel variants: row tiles per wavefront, column tiles, groups of four spin values.
-// Most column tiles of a workgroup: a second column block repeats G; past ten tiles the registers spill
-// (16 large configurations, up to eleven tiles: 189, 169, 161, 159 ms with at most 8, 9, 10, 11).
+// Most column tiles of a workgroup: a second column block repeats G, more tiles spill more (chain_waves).
+// 16 large configurations (two spin groups, up to eleven tiles): 189, 169, 161, 159 ms with at most 8, 9, 10,
+// 11.  With at most 8 against 11, ranges of cores: three groups, ten tiles 5.76 against 5.44 ms, eleven 11.38
+// against 12.14; four groups, ten tiles 21.0 against 18.0 ms, eleven 36.5 against 32.2.
 constexpr int kChainCT = 11;
 constexpr int chain_key(int rt, int ct, int ks) { return ((rt - 1) * 16 + ct) * 4 + ks - 1; }
 constexpr int kChainKeys = 2 * 64;

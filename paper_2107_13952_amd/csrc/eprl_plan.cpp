@@ -70,7 +70,7 @@ int make_plan(const int two_j[10], int dl, Plan &p, std::string &err) {
     p.two_j[n] = two_j[n];
   }
   // Spin limit: the largest virtual spin 2 (j + dl) must keep every factorial argument of
-  // the 6j evaluation below the prime-exponent table limit.
+  // the 6j evaluation within the factorial table.
   int maxtwo = 0;
   for (int n = 0; n < 10; ++n) maxtwo = std::max(maxtwo, two_j[n] + 2 * dl);
   if (maxtwo > kSixjMaxTwo) {
@@ -212,8 +212,8 @@ int make_plan(const int two_j[10], int dl, Plan &p, std::string &err) {
   if (p.ring_DI == 0 || p.ring_DK == 0 || p.ring_KW == 0 || nd > kRingMaxNd) p.ring_KW = 0;
   p.ring_cls = p.ring_KW ? ring_class(p.ring_DI, p.ring_DK, p.ring_KW) : -1;
   p.ring_cls8 = p.ring_cls;
-  // The x-outer kernel for every class whose tiles fit, except the 16-wide ones with all boundary
-  // dimensions at most 8 that ring_DI already tells apart; boundary dimensions above 8 are class 8.
+  // The x-outer kernel for every class whose tiles fit; it runs the 16-wide classes (4..7, a boundary
+  // dimension above 8) as class 8.
   if (p.ring_cls >= 0 && chain_plan(p) && p.ring_cls >= 4) p.ring_cls = kWideClass;
   return EPRL_OK;
 }

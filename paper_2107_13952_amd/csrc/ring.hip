@@ -586,7 +586,7 @@ __global__ __launch_bounds__(RT, (ring_waves<DI, DK, KW>())) void ring_batch_ker
   }
 }
 
-// Resets the work-queue counters of a batch (a kernel, so that graph replays start from 0).
+// Resets the work-queue counters of a batch.
 __global__ void reset_counters(int *c, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) c[i] = 0;
 }
