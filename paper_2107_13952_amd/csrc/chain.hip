@@ -101,7 +101,8 @@ struct PrepPairs {
 };
 
 // T5, T2 and the weighted boosters M4, M3 of one configuration.
-//   T5[o25][x][o35][i1][o45][kap][S]: entry i5, k4 = max(|l45 - j14|, k4lo) + 2 kap
+//   T5[o25][x][o35][i1][o45][kap][S]: entry i5, k4 = max(|l45 - j14|, k4lo) + 2 kap, and zero rows behind
+//   the last o45 (ChainGeom::tmid)
 //   T2[o24][o25][x][i1][o23][kap][S]: entry i2, k3 = max(|l23 - j13|, k3lo) + 2 kap
 //   M4[o24][o34][pos][.], k4 = max(|l24 - l34|, k4lo) + 2 pos, the entries (o45, i4) as chain_mrow says
 //   M3[o34][o35][pos][.], k3 = max(|l34 - l35|, k3lo) + 2 pos, the entries (o23, i3)
@@ -132,7 +133,7 @@ __device__ __forceinline__ void chain_prep_block(const RingParams &rp, int b) {
       o24 = b / (nx * nd);
     }
     const int x = rp.xlo2 + 2 * xi, xg = (x - rp.X_lo2) / 2, l25 = J[L25] + 2 * o25;
-    const int nt = five ? rp.n4t : rp.n3t, per = nd * nt;
+    const int nt = five ? rp.n4t : rp.n3t, per = five ? rp.t5r : nd * nt;
     const int khi = five ? rp.whi[1] : rp.whi[0], jq = five ? J[L14] : J[L13];
     const int di = five ? rp.i_n[4] : rp.i_n[1];
     double *out = (five ? rp.T5 : rp.T2) + (int64_t)b * d1 * per * S;
@@ -141,13 +142,17 @@ __device__ __forceinline__ void chain_prep_block(const RingParams &rp, int b) {
       const int n1 = by_per(q), r = q - n1 * per, o = by_nt(r), kap = r - o * nt;
       const int i1 = rp.i_lo2[0] + 2 * n1;
       if (x < iabs(i1 - l25) || x > i1 + l25) continue;
+      double *row = out + (int64_t)q * S;
+      if (o >= nd) {  // the zero rows behind a slice of T5
+        for (int i = 0; i < S; ++i) row[i] = 0.0;
+        continue;
+      }
       const int lo = chain_klo(J, rp.wlo, rp.whi, !five, o), k = lo + 2 * kap;
       const int t = five ? (o25 * nd + o35) * nd + o : (o * nd + o24) * nd + o25;  // block of M5 / M2
       const int e = five ? 3 : 0;
       const int klb = rp.kr[(e * nd3 + t) * 2], kn = rp.kr[(e * nd3 + t) * 2 + 1];
       // summed k (k5 or k2): the block's range and the triad with j14 (j13) and x
       const int ka = imax(klb, iabs(x - jq)), kb = imin(klb + 2 * (kn - 1), x + jq);
-      double *row = out + (int64_t)q * S;
       const int c = k <= khi && kn > 0 && kb >= ka ? (kb - ka) / 2 + 1 : 0;
       double a[16];
       if (c > 0) {
@@ -296,12 +301,11 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
   const int d1 = rp.i_n[0], d2 = rp.i_n[1], d3 = rp.i_n[2], d4 = rp.i_n[3], d5 = rp.i_n[4];
   const int R = d5 * d4, C = d3 * d2;
   const int sig0 = cb * rp.ctb * 16, CW = imin(C - sig0, rp.ctb * 16);  // columns of this block
-  const int S = rp.ts, t5n = nd * rp.n4t * S, t2n = nd * rp.n3t * S;
+  const int S = rp.ts, t5n = rp.t5r * S, t2n = nd * rp.n3t * S;
   // LDS: T rows of the unit between zero rows (a k outside a spin's rows reads another spin's or a zero
   // row, times a zero booster entry; never a row of the other table, whose infinities or NaN, from a
   // booster entry of another edge, would then show up in entries that do not depend on it), G, H.
-  const int t2at = t5n + rp.tmid * S;
-  double *T5s = smem + rp.tpre * S, *T2s = T5s + t2at;
+  double *T5s = smem + rp.tpre * S, *T2s = T5s + t5n;
   double *Gs = T2s + t2n + rp.tpost * S, *Hs = Gs + rp.sp * 8 * R;
   const int nK3 = rp.K_n[1];
   const double *U3 = rp.U3;
@@ -513,7 +517,7 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
     for (;;) {
       // ---- G and H, the wavefronts' chunks of G from the first on, of H from the last
       side_stage(sg, Gs, st.t5, st.n4, st.m4, w, mg);
-      side_stage(sh, Hs, t2at + st.t2, st.n3, st.m3, nw - 1 - w, mh);
+      side_stage(sh, Hs, t5n + st.t2, st.n3, st.m3, nw - 1 - w, mh);
       ChainStep sn = st;
       bool more = st.more != 0;
       if (more) {
@@ -602,15 +606,14 @@ __device__ __forceinline__ void chain_item(const RingParams &rp, int chunk, int 
 }
 
 // Wavefronts per SIMD the registers are budgeted for, and the most wavefronts of a workgroup.
-template <int RT, int CT, int KS>
-constexpr int chain_waves() {
+constexpr int chain_waves(int RT, int CT, int KS) {
   // Accumulators and P; booster operands; U3, addresses, operands in flight.  With 80 for the last, one
   // wavefront more for the small tiles, these spilled: 244 against 205 us for spins 3 .. 12 / 2, 5 shells.
   // Vector registers spilled as it is, of two row tiles: none up to eight column tiles with one or two spin
   // groups, from nine on 3 to 84; with three groups 2 to 20 from five column tiles on (none at seven), 122
   // and 136 at ten and eleven; with four 5 to 78 from three on, 93 and 188 at ten and eleven.  Of one row
   // tile, four for <1, 2, 2> and <1, 5, 1>, none else with up to two groups.
-  constexpr int need = 8 * RT * CT + 8 * RT + (RT * CT >= 14 ? 12 : 24) * KS + 104;
+  const int need = 8 * RT * CT + 8 * RT + (RT * CT >= 14 ? 12 : 24) * KS + 104;
   return need <= 128 ? 4 : need <= 176 ? 3 : 2;
 }
 constexpr int kChainWg = 8;  // wavefronts of a workgroup
@@ -618,7 +621,7 @@ constexpr int kChainWg = 8;  // wavefronts of a workgroup
 // Block b runs item b of the list (configuration, chunk, i1, column block), or, without a list,
 // configuration 0's chunk b / (d1 nrb), i1 and column block from b % (d1 nrb).
 template <int RT, int CT, int KS>
-__global__ __launch_bounds__(kChainWg * 64, (chain_waves<RT, CT, KS>()))
+__global__ __launch_bounds__(kChainWg * 64, chain_waves(RT, CT, KS))
 void chain_kernel(const RingParams *__restrict__ cfgs, const int *__restrict__ items) {
   extern __shared__ double smem[];
   int q0 = 0, q1, q2, q3;
@@ -723,9 +726,11 @@ bool chain_plan(Plan &p) {
   g.waves = (RT + rt - 1) / rt;
   g.key = chain_key(rt, g.ctb, (nd + 3) / 4);
   g.lds = (int)(chain_smem_bytes(p) / sizeof(double));
+  const int fit = std::min(4 * chain_waves(rt, g.ctb, (nd + 3) / 4) / g.waves, (int)(kChainMaxLds / chain_smem_bytes(p)));
+  g.resident = 256 * std::max(1, fit);
   const int64_t nx = p.X.n, d1 = p.i[0].n;
   auto pad = [](int64_t v) { return (v + 31) / 32 * 32; };
-  g.t5 = pad((int64_t)nd * nx * nd * d1 * nd * g.n4t * g.ts);
+  g.t5 = pad((int64_t)nd * nx * nd * d1 * (nd * g.n4t + g.tmid) * g.ts);
   g.t2 = pad((int64_t)nd * nd * nx * d1 * nd * g.n3t * g.ts);
   // Booster rows per (l24, l34) or (l34, l35); reads run up to 16 positions past the last.
   const int64_t rows = w + 3;
@@ -770,8 +775,8 @@ void chain_params(const Plan &p, double *derived, RingParams &rp) {
   rp.sp = g.sp;
   rp.wm = g.wm;
   rp.tpre = g.tpre;
-  rp.tmid = g.tmid;
   rp.tpost = g.tpost;
+  rp.t5r = p.nd * g.n4t + g.tmid;
   rp.lds = g.lds;
   rp.mr4 = g.mr4;
   rp.mr3 = g.mr3;

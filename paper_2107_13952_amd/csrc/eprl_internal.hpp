@@ -32,6 +32,7 @@ struct ChainGeom {
   int tpre = 0, tmid = 0, tpost = 0;  // zero rows before, between and after the T rows in LDS
   int nrb = 1, ctb = 1;   // column blocks, column tiles per block
   int waves = 1;          // wavefronts per workgroup
+  int resident = 256;     // workgroups the chip (256 CUs) holds at a time
   int lds = 0;            // LDS of a workgroup, in doubles
   int mr4 = 0, mr3 = 0;   // entries of a row of M4, M3
   int key = 0;            // kernel variant
@@ -146,9 +147,12 @@ struct RingParams {
   // (0) and k4 (1), range of cores; bounds then holds units (l24, l25, x, l35).
   double *T5, *T2, *M4, *M3;
   ChainStep *steps;
-  int n4t, n3t, ts, wm, sp, tpre, tmid, tpost, ctb, nx, lds, mr4, mr3;
+  int n4t, n3t, ts, wm, sp, tpre, tpost, ctb, nx, lds, mr4, mr3;
   int wlo[2], whi[2];
   int core_lo, core_hi;
+  // Rows of a slice of T5.  (Last: with the fields before it at other offsets the scalar loads group
+  // differently, which cost chain_kernel<2, 11, 2> eight spilled registers, 17.9 -> 18.5 ms at two_j = 12.)
+  int t5r;
 };
 
 // One launch over several configurations: job q has the blocks from jobs[q].first to the next job's

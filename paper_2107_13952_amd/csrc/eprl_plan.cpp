@@ -331,13 +331,16 @@ int chain_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
   // Units of a core range: those of its (l24, l25) pairs; a partial pair keeps the whole pair's cost.
   const int pair_lo = core_lo / nd2, pair_hi = core_hi > core_lo ? (core_hi + nd2 - 1) / nd2 : pair_lo;
   const int u_lo = pair_lo * nx * nd, u_hi = (all ? nd2 : pair_hi) * nx * nd;
-  // Every workgroup writes a slice of A that the reduction reads: about 3.6 ps an entry for both.  A step of
-  // one wavefront takes 65 ps of the whole chip (256 CUs).  With nwg = r rounds of the resident workgroups
-  // the last round is half empty on average, so r = sqrt(work / (2 slices of a round)) balances the two, one
-  // round at least.  (All of target_wg, or every unit by itself, for whatever work: two_j = 12, 1 shell 343 us
-  // at 1300 workgroups, 208 at 256 (ring.hip's kernels 246); two_j = 6, 3 shells 158 us at 5800, 100 at 1024;
-  // two_j = 8, 3 shells 393 at 5100, 302 at 2048; two_j = 6, 8 shells and two_j = 10 .. 14, 6 shells are
-  // fastest, and flat, from 4096 to 16384.)
+  // Every workgroup writes a slice of A that the reduction reads: about 3.6 ps an entry for both, and 10 ns a
+  // chunk for the serial part of the reduction.  A step of one wavefront takes 65 ps of the whole chip (256
+  // CUs).  With r rounds of the resident workgroups about half a chunk's time is lost at the end, so
+  // r = sqrt(work / (2 slices of a round)) balances the two; whole rounds, as the chunks cost about the same
+  // (two_j = 12 .. 14, 1 shell 260 us at 1.1 rounds, 212 at one), and one where r is below two (r = 1.9:
+  // two_j = 1, 9 shells 154 us at one, 179 at two; spins 2 .. 11 / 2, 6 shells 131 and 139).  With all of
+  // target_wg, or every unit by itself, for whatever work: two_j = 12, 1 shell 343 us at 1300 workgroups, 204
+  // at 256 (ring.hip's kernels 246); two_j = 6, 3 shells 158 us at 5800, 100 at 1024; two_j = 8, 3 shells 393
+  // at 5100, 302 at 2048; two_j = 6, 8 shells and two_j = 10 .. 14, 6 shells are fastest, and flat, from 4096
+  // to 16384.
   double work = 0.0;
   for (int o24 = pair_lo / nd; o24 < nd && o24 * nd < pair_hi; ++o24)
     for (int xi = 0; xi < nx; ++xi) {
@@ -347,10 +350,10 @@ int chain_schedule(const Plan &p, int target_wg, std::vector<int> &bounds,
         if (o24 * nd + o25 >= pair_lo && o24 * nd + o25 < pair_hi)
           work += c * triad_count(p.i[0].lo2, d1, J[L25] + 2 * o25, p.X.lo2 + 2 * xi);
     }
-  const int resident = 256 * std::max(1, std::min(8 / g.waves, (int)(kChainMaxLds / chain_smem_bytes(p))));
-  const double slices = 3.6e-3 * resident * ((double)p.a_size / (d1 * g.nrb));
+  const double slices = g.resident * (3.6e-3 * ((double)p.a_size / (d1 * g.nrb)) + 10.0 / (d1 * g.nrb));
   const double rounds = std::sqrt(65e-3 * work * g.nrb * g.waves / (2.0 * slices));
-  target_wg = (int)std::min<double>(target_wg, resident * std::max(1.0, rounds));
+  if (target_wg >= g.resident)
+    target_wg = g.resident * (rounds < 2.0 ? 1 : (int)std::min<double>(rounds + 0.5, target_wg / g.resident));
   int nchunk = std::max(1, target_wg / (d1 * g.nrb));
   nchunk = (int)std::min<int64_t>(nchunk, std::max<int64_t>(1, (int64_t)(kRingMaxPartialBytes / ((size_t)p.a_size * sizeof(double)))));
   nchunk = std::min(nchunk, std::max(1, u_hi - u_lo));
