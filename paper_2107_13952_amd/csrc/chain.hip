@@ -31,7 +31,7 @@
 // here (2.61 ms for the kernel with the half chains inside the core loop), at two_j = 10 .. 14, 6
 // shells 5.35 ms (12.3).  The matrix cores are busy 38 % of the cycles; a wavefront spends a third of
 // its time in waits (the LDS operands of the 4 x 4 products, U3, two barriers a step) and issues 230
-// scalar and 260 vector instructions a step around 52 matrix instructions.  Every variant spills 94 to 130
+// scalar and 260 vector instructions a step around 52 matrix instructions.  Every variant spills 94 to 123
 // scalar registers (two sides, two steps, the unit's counters, pointers and strides are live at once), and
 // each reload of one is a vector instruction.  The accumulators allow two wavefronts per SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no
 // change, fewer workgroups fit), 16 x 16 tiles for G and H of large dimensions (6.3 -> 6.7 ms), row
@@ -610,7 +610,7 @@ constexpr int chain_waves(int RT, int CT, int KS) {
   // Accumulators and P; booster operands; U3, addresses, operands in flight.  With 80 for the last, one
   // wavefront more for the small tiles, these spilled: 244 against 205 us for spins 3 .. 12 / 2, 5 shells.
   // Vector registers spilled as it is, of two row tiles: none up to eight column tiles with one or two spin
-  // groups, from nine on 3 to 84; with three groups 2 to 20 from five column tiles on (none at seven), 122
+  // groups, from nine on 3 to 76; with three groups 2 to 20 from five column tiles on (none at seven), 122
   // and 136 at ten and eleven; with four 5 to 78 from three on, 93 and 188 at ten and eleven.  Of one row
   // tile, four for <1, 2, 2> and <1, 5, 1>, none else with up to two groups.
   const int need = 8 * RT * CT + 8 * RT + (RT * CT >= 14 ? 12 : 24) * KS + 104;

@@ -216,7 +216,8 @@ def boosters_of_few_blocks(lib):
 
 
 # Few shells at large spins: no more workgroups than their partial sums are worth (one to two rounds of the
-# chip, down to a multiple of the i1 values); many shells: the full number (11 x 208 where the partial sums reach their 256 MB).
+# chip, down to a multiple of the i1 values); many shells: the full number (11 x 208 where the partial sums
+# reach their 256 MB).
 def small_sums_are_split_less(lib):
     lib.stub.stub_watch(b"chain_kernel")
     for two_j, dl, lo, hi in (([12] * 10, 1, 200, 512), ([10] * 10, 1, 200, 768), ([14] * 10, 0, 200, 512),
