@@ -27,16 +27,17 @@
 //   * the update, one matrix-core step per (four k3, column tile).
 // Operand entries past a window need no masks: k4 (k3) beyond a triad has a zero T row or a zero
 // booster entry, so G and H are zero there and meet finite values of U3.
-// What bounds it: at two_j = 6, 8 shells (7^5 outputs, 303 k steps over all i1) a call takes 1.37 ms
+// What bounds it: at two_j = 6, 8 shells (7^5 outputs, 303 k steps over all i1) a call takes 1.33 ms
 // here (2.61 ms for the kernel with the half chains inside the core loop), at two_j = 10 .. 14, 6
 // shells 5.35 ms (12.3).  The matrix cores are busy 38 % of the cycles; a wavefront spends a third of
 // its time in waits (the LDS operands of the 4 x 4 products, U3, two barriers a step) and issues 230
-// scalar and 260 vector instructions a step around 52 matrix instructions.  Every variant spills 94 to 123
-// scalar registers (two sides, two steps, the unit's counters, pointers and strides are live at once), and
-// each reload of one is a vector instruction.  The accumulators allow two wavefronts per SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no
-// change, fewer workgroups fit), 16 x 16 tiles for G and H of large dimensions (6.3 -> 6.7 ms), row
-// blocks (each repeats H: 6.3 -> 11.0 ms for two), one wavefront per workgroup without barriers (1.49
-// -> 1.69 ms), rt = 1 (6.95 -> 8.36 ms: each H operand then serves one row tile).
+// scalar and 270 vector instructions a step around 52 matrix instructions.  Every variant spills 94 to
+// 123 scalar registers (two sides, two steps, the unit's counters, pointers and strides are live at
+// once), and each reload of one is a vector instruction.  The accumulators allow two wavefronts per
+// SIMD.  Measured and not taken: G and H twice in LDS and one barrier a step (no change, fewer
+// workgroups fit), 16 x 16 tiles for G and H of large dimensions (6.3 -> 6.7 ms), row blocks (each
+// repeats H: 6.3 -> 11.0 ms for two), one wavefront per workgroup without barriers (1.49 -> 1.69 ms),
+// rt = 1 (6.95 -> 8.36 ms: each H operand then serves one row tile).
 // Lane layout (lane l = 16 g + c, measured on the device): v_mfma_f64_16x16x4 operand A[c][g],
 // operand B[g][c], result register r = D[g + 4 r][c]; v_mfma_f64_4x4x4 block b = c >> 2, operand
 // A[c & 3][g], operand B[g][c & 3], result D[g][c & 3].
