@@ -1808,14 +1808,17 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     fact = std::max(fact, std::max(b.lb[0] + b.lb[1], b.lb[2] + b.lb[3]) + kmax);
   }
   groups.push_back((int)keys.size());
-  // The blocks of each edge as a matrix over pairs of key bases, in tiles; a tile costs as much as about
-  // sixteen blocks by themselves (spins 7, an edge: 153 us; eight blocks 71, sixteen about 150).
+  // The blocks of each edge as a matrix over pairs of key bases, in tiles; or, where no tile holds sixteen,
+  // block by block: a tile costs as much as about sixteen blocks by themselves (spins 7, an edge: 153 us; eight
+  // blocks 71, sixteen about 150).  Not the sparse tiles beside full ones: a second launch costs more than it
+  // saves (spins 1/2 and 1, 5 shells 1305 us, 1348 with it).
   constexpr int kBoosterTileBlocks = 16;
+  int most = 0;
   BoosterGrid grid[4];
   std::vector<int> pairs, bmap, tiles, singles;
   for (int e = 0; e < 4; ++e) {
     std::map<std::pair<int, int>, int> id[2];
-    std::vector<int> list[2], cell;  // (row, column, block) of each block
+    std::vector<int> list[2], cell;  // (row, column, offset in I) of each block
     for (int q = 0; q < nb; ++q) {
       const int *bi = &binfo[9 * (size_t)q];
       if (bi[0] != e || bi[3] == 0) continue;
@@ -1825,7 +1828,8 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
         if (it.second) list[h].insert(list[h].end(), {k.first, k.second});
         cell.push_back(it.first->second);
       }
-      cell.push_back(q);
+      cell.push_back(bi[4]);
+      singles.push_back(q);
     }
     BoosterGrid &g = grid[e];
     g.M = M_edge[e];
@@ -1837,16 +1841,18 @@ int eprl_boosters(eprl_ctx *c, const int two_j[10], int dl, double gamma, double
     pairs.insert(pairs.end(), list[1].begin(), list[1].end());
     g.map = (int)bmap.size();
     bmap.resize(bmap.size() + (size_t)g.nrow * g.ncol, -1);
-    const int tcols = (g.ncol + 15) / 16;
-    std::vector<int> held((size_t)((g.nrow + 15) / 16) * tcols, 0);  // blocks of each tile
-    auto tile_of = [&](size_t k) -> int & { return held[(size_t)(cell[k] / 16) * tcols + cell[k + 1] / 16]; };
-    for (size_t k = 0; k < cell.size(); k += 3) ++tile_of(k);
-    for (size_t k = 0; k < cell.size(); k += 3)
-      if (tile_of(k) < kBoosterTileBlocks) singles.push_back(cell[k + 2]);
-      else bmap[g.map + (size_t)cell[k] * g.ncol + cell[k + 1]] = binfo[9 * (size_t)cell[k + 2] + 4];
-    for (size_t t = 0; t < held.size(); ++t)
-      if (held[t] >= kBoosterTileBlocks) tiles.insert(tiles.end(), {e, (int)(t / tcols) * 16, (int)(t % tcols) * 16, 0});
+    for (size_t k = 0; k < cell.size(); k += 3) bmap[g.map + (size_t)cell[k] * g.ncol + cell[k + 1]] = cell[k + 2];
+    for (int r = 0; r < g.nrow; r += 16)
+      for (int cl = 0; cl < g.ncol; cl += 16) {
+        int held = 0;
+        for (int i = r; i < std::min(r + 16, g.nrow); ++i)
+          for (int j = cl; j < std::min(cl + 16, g.ncol); ++j) held += bmap[g.map + (size_t)i * g.ncol + j] >= 0;
+        if (held > 0) tiles.insert(tiles.end(), {e, r, cl, 0});
+        most = std::max(most, held);
+      }
   }
+  if (most < kBoosterTileBlocks) tiles.clear();
+  else singles.clear();
   if (fact / 2 + 2 > 2 * kSixjMaxTwo + 2) return fail(c, EPRL_ERANGE, "spins beyond the 3jm range");
   rc = ensure_fact(c, fact / 2 + 2);
   if (rc) return rc;

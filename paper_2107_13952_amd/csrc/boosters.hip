@@ -199,9 +199,9 @@ __global__ __launch_bounds__(64 * kIntWaves) void booster_integrals_kernel(Boost
   out[3] = v[1].y;
 }
 
-// (2) for single blocks (bp.singles[blockIdx.y]) and m-tuples: one wavefront each, lanes over the r nodes.  For
-// the tiles with few blocks (below 16 of 256): a tile costs the same however many it holds, at spins 7 153 us
-// an edge against 10 us a block here (dl = 0, one block to an edge, 610 -> 41 us for all four).
+// (2) block by block (bp.singles[blockIdx.y]) and m-tuple: one wavefront each, lanes over the r nodes.  For
+// calls whose tiles hold few blocks (below 16 of 256): a tile costs the same however many it holds, at spins 7
+// 153 us an edge against 10 us a block here (dl = 0, one block to an edge, 610 -> 41 us for all four).
 __global__ __launch_bounds__(256) void booster_block_integrals_kernel(BoosterParams bp) {
   const int *bi = bp.binfo + 9 * bp.singles[blockIdx.y];
   const int lane = threadIdx.x & 63;

@@ -362,7 +362,7 @@ struct BoosterParams {
   int nblocks, Mmax;
   // grouped for the kernels: keys of one (j, l) together, group g from groups[g]; the blocks' matrices,
   // bmap[row][column] the block's offset in I (-1: no block), and their 16 x 16 tiles (edge, row,
-  // column, 0); the blocks of sparse tiles by themselves
+  // column, 0); or, where the tiles would be sparse, the blocks by themselves
   const int *groups;
   int ngroups;
   BoosterGrid grid[4];

@@ -133,7 +133,7 @@ def test_booster_integral_tiles(lib, two_j, dl):
     _check(lib, two_j, dl, ref)
 
 
-# Blocks by themselves: one and eight to an edge, and seven beside three full tiles.
+# Blocks by themselves, one and eight to an edge; and a tile of at most seven beside three full ones.
 @pytest.mark.parametrize("two_j,dl", [([6] * 10, 0), ([2, 3, 2, 1, 3, 2, 3, 1, 1, 3], 1), ([1] * 10, 6)])
 def test_booster_integral_blocks(lib, two_j, dl):
     ref, imag, err = Bo.boosters(two_j, dl, 1.2)
